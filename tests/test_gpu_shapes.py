@@ -1,0 +1,48 @@
+"""GPU parity at the sizes where the kernels' tiles, splits and dispatch
+rules have edges: small models against the float64 oracle."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import Oracle
+from tests.gpu_util import check_readout, make_session, row_err, to_np
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+F32_TOL = 1e-5    # fp32 bar of the parity tests (a 1024-term fp32 sum: ~32 x 6e-8 typical)
+
+
+def prompts_and_steps(shape, lens, tol, steps=2):
+    """Prompts, the boundary and a few greedy steps on the oracle's tokens."""
+    W = synth.make_weights(shape, seed=0)
+    prompts = [synth.make_tokens(1, 10 + i, (L,), shape.vocab) for i, L in enumerate(lens)]
+    orc = Oracle(shape, W.values)
+    obs = orc.prefill(prompts, run_boundary=True)
+    sess = make_session(shape, W, max_batch=len(lens), max_pos=max(lens) + steps + 1, max_prompt=max(lens))
+    t = sess.prefill(prompts, run_boundary=True)
+    check_readout(t, obs, tol, "boundary")
+    toks = [o["next"] for o in obs]
+    for step in range(steps):
+        outs = orc.decode_step(tokens=toks)
+        t = sess.decode(tokens=toks)
+        check_readout(t, outs, tol, f"step {step}")
+        for key, ref in (("h1_out", "h1"), ("h2_out", "h2")):
+            assert row_err(to_np(t[key]), np.stack([o[ref] for o in outs])).max() <= tol, (step, key)
+        toks = [o["next"] for o in outs]
+    sess.close()
+
+
+# widths around the fp32 projection's 32-element units and eight waves (a
+# lone partial unit, one unit, a partial ninth), 16-column tiles with odd
+# segment ends, and row blocks of 16, 32 and 64
+@pytest.mark.parametrize("d,dh,f,vocab,lens", [
+    (20, 4, 7, 17, [3]),
+    (32, 8, 33, 31, [1, 17]),
+    (260, 64, 95, 130, [33, 5, 16]),
+    (288, 32, 1025, 4100, [65, 64]),
+])
+def test_f32_projection_edges(d, dh, f, vocab, lens):
+    shape = synth.ModelShape(n_layers=2, d_model=d, n_q_heads=4, n_kv_heads=2, head_dim=dh, d_ff=f, vocab=vocab,
+                             dtype="f32", has_embeddings=True, std=0.1, coupling_std=0.5)
+    prompts_and_steps(shape, lens, F32_TOL)
