@@ -50,7 +50,7 @@ constexpr int kPage = 16;
 // takes shorter splits, down to 16 pages, so that its longest caches fill
 // about 512 workgroups.  The target is fixed when the model is created, so a
 // row's result depends only on its own query and cache.
-// The fp32 kernel holds a split's scores in LDS (at most 64 pages).
+// fp32 splits are 64 pages long.
 constexpr int kSplitTargetBf16 = 86, kSplitMinBf16 = 16, kSplitTargetF32 = 64, kSplitWideMin = 256;
 constexpr int kMixChunk = 4096;
 
@@ -398,7 +398,9 @@ bool input_fold(const dbt_model *m, const dbt_kv *kv, int B);
 
 bool attn_finishes_qkv(const dbt_model *m, int B, int maxlen, bool *single_out) {
   const dbt_config &cf = m->cfg;
-  const bool single = cf.dtype == DBT_BF16 && B * cf.n_kv_heads >= 256 && (maxlen + kPage - 1) / kPage <= 1024;
+  const int npages = (maxlen + kPage - 1) / kPage;
+  // fp32: no sequence needs a second split (no partials to merge)
+  const bool single = cf.dtype == DBT_BF16 ? B * cf.n_kv_heads >= 256 && npages <= 1024 : npages <= m->L.split_target;
   if (single_out) *single_out = single;
   return cf.dtype == DBT_BF16 && cf.head_dim == 128 && cf.n_q_heads / cf.n_kv_heads <= (single || m->L.wide ? 8 : 4);
 }

@@ -1,6 +1,7 @@
 // Causal attention over a prompt (primary prefill, Sec. 4.4): every prompt
 // position attends to the cache positions at or before it, which the prefill
 // has just written.  Query rows are prompt positions of one sequence.
+#include "attn_f32.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -395,77 +396,24 @@ __global__ __launch_bounds__(1024) void k_attn_prefill_wide(const float *Q, int 
   }
 }
 
-// Causal attention over the prompt of one sequence: workgroup per
-// (position t, KV head), keys 0..t in chunks of 256 with an online softmax.
-template <typename T>
-__global__ __launch_bounds__(256) void k_attn_prefill(const float *Q, int ldq, KVRef kv, int seq, int n_q,
-                                                      T *O, int ldo) {
-  constexpr int CH = 256;
-  __shared__ float qs[16][128];
-  __shared__ float sc[16][CH];
-  __shared__ float red[16];
-  const int t = blockIdx.x, g = blockIdx.y;
-  const int n_kv = kv.n_kv, DH = kv.d_h;
-  const int G = n_q / n_kv;
-  const float scale = kLog2e / sqrtf((float)DH);
-  const T *kb = (const T *)kv.k;
-  const T *vb = (const T *)kv.v;
-  const int *ptab = kv.page_table + (size_t)seq * kv.mpps;
-  for (int e = threadIdx.x; e < G * DH; e += blockDim.x)
-    qs[e / DH][e % DH] = Q[(size_t)t * ldq + (g * G + e / DH) * DH + e % DH];
-  float acc[8], mrun[16], lrun[16];
-  for (int k = 0; k < 8; ++k) acc[k] = 0.f;
-  for (int j = 0; j < 16; ++j) { mrun[j] = -INFINITY; lrun[j] = 0.f; }
-  const int nel = G * DH;  // <= 2048: thread owns elements threadIdx.x + 256k
-  for (int c0 = 0; c0 <= t; c0 += CH) {
-    const int nk = min(CH, t + 1 - c0);
-    __syncthreads();
-    if ((int)threadIdx.x < nk) {
-      const int pos = c0 + threadIdx.x;
-      const T *kr = kb + (((size_t)ptab[pos >> 4] * n_kv + g) * 16 + (pos & 15)) * DH;
-      for (int j = 0; j < G; ++j) {
-        float s = 0.f;
-        for (int dh = 0; dh < DH; ++dh) s = fmaf(ld<T>(kr, dh), qs[j][dh], s);
-        sc[j][threadIdx.x] = s * scale;
-      }
-    }
-    __syncthreads();
-    float corr[16];
-    for (int j = 0; j < G; ++j) {
-      float mx = -INFINITY;
-      for (int k = threadIdx.x; k < nk; k += blockDim.x) mx = fmaxf(mx, sc[j][k]);
-      mx = block_max(mx, red);
-      const float mn = fmaxf(mrun[j], mx);
-      corr[j] = exp2f(mrun[j] - mn);
-      float l = 0.f;
-      __syncthreads();
-      for (int k = threadIdx.x; k < nk; k += blockDim.x) {
-        const float pv = exp2f(sc[j][k] - mn);
-        sc[j][k] = pv;
-        l += pv;
-      }
-      l = block_sum(l, red);
-      lrun[j] = lrun[j] * corr[j] + l;
-      mrun[j] = mn;
-    }
-    __syncthreads();
-    for (int k = 0; k < 8; ++k) {
-      const int e = threadIdx.x + 256 * k;
-      if (e >= nel) break;
-      const int j = e / DH, dh = e % DH;
-      float o = acc[k] * corr[j];
-      for (int kk = 0; kk < nk; ++kk) {
-        const int pos = c0 + kk;
-        o = fmaf(sc[j][kk], ld<T>(vb, (((size_t)ptab[pos >> 4] * n_kv + g) * DH + dh) * 16 + (pos & 15)), o);
-      }
-      acc[k] = o;
-    }
-  }
-  for (int k = 0; k < 8; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    if (e >= nel) break;
-    const int j = e / DH, dh = e % DH;
-    st<T>(O, (size_t)t * ldo + (g * G + j) * DH + dh, acc[k] / lrun[j]);
+// fp32 cache: workgroup per (16 query positions, query head), longest tiles
+// first (attn_f32.h); the waves share the pages up to the tile's last position.
+template <int NC>
+__global__ __launch_bounds__(64 * kWavesF32Attn) void k_attn_prefill_f32(const float *Q, int ldq, int T, KVRef kv,
+                                                                         int seq, int n_q, float *O, int ldo) {
+  const int q0 = (((T + 15) >> 4) - 1 - (int)blockIdx.x) * 16, head = blockIdx.y;
+  const int g = head / (n_q / kv.n_kv), DH = kv.d_h;
+  const int qpos = q0 + (threadIdx.x & 15);
+  __shared__ F32Merge<NC> mg;
+  attn_f32<NC>(mg, Q + (size_t)min(qpos, T - 1) * ldq + head * DH, qpos < T, qpos + 1, T, (const float *)kv.k,
+               (const float *)kv.v, kv.page_table + (size_t)seq * kv.mpps, 0, (min(q0 + 15, T - 1) >> 4) + 1, kv.n_kv,
+               g, DH);
+  for (int e = threadIdx.x; e < 16 * DH; e += 64 * kWavesF32Attn) {
+    const int qr = e / DH, dh = e % DH;
+    if (q0 + qr >= T) continue;
+    float o, l, mx;
+    mg.merged(qr, dh, o, l, mx);
+    O[(size_t)(q0 + qr) * ldo + head * DH + dh] = o / l;
   }
 }
 
@@ -492,11 +440,19 @@ hipError_t launch_attn_prefill(const float *Q, int ldq, int T, KVRef kv, int seq
     }
     return hipGetLastError();
   }
-  dim3 grid(T, kv.n_kv);
-  if (dtype == 1)
-    hipLaunchKernelGGL(k_attn_prefill<uint16_t>, grid, dim3(256), 0, st, Q, ldq, kv, seq, n_q, (uint16_t *)O, ldo);
-  else
-    hipLaunchKernelGGL(k_attn_prefill<float>, grid, dim3(256), 0, st, Q, ldq, kv, seq, n_q, (float *)O, ldo);
+  if (dtype == 1) return hipErrorInvalidValue;  // (bf16 caches have d_h = 128 and G <= 16, checked at creation)
+  const dim3 grid((T + 15) / 16, n_q), block(64 * kWavesF32Attn);
+  float *Of = (float *)O;
+  switch ((kv.d_h + 15) / 16) {
+    case 1: hipLaunchKernelGGL(k_attn_prefill_f32<1>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
+    case 2: hipLaunchKernelGGL(k_attn_prefill_f32<2>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
+    case 3: hipLaunchKernelGGL(k_attn_prefill_f32<3>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
+    case 4: hipLaunchKernelGGL(k_attn_prefill_f32<4>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
+    case 5: hipLaunchKernelGGL(k_attn_prefill_f32<5>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
+    case 6: hipLaunchKernelGGL(k_attn_prefill_f32<6>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
+    case 7: hipLaunchKernelGGL(k_attn_prefill_f32<7>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
+    default: hipLaunchKernelGGL(k_attn_prefill_f32<8>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
+  }
   return hipGetLastError();
 }
 

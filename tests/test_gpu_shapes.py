@@ -20,6 +20,8 @@ def prompts_and_steps(shape, lens, tol, steps=2):
     orc = Oracle(shape, W.values)
     obs = orc.prefill(prompts, run_boundary=True)
     sess = make_session(shape, W, max_batch=len(lens), max_pos=max(lens) + steps + 1, max_prompt=max(lens))
+    sess.k_pages.fill_(0xFF)  # slots no position has written hold NaN
+    sess.v_pages.fill_(0xFF)
     t = sess.prefill(prompts, run_boundary=True)
     check_readout(t, obs, tol, "boundary")
     toks = [o["next"] for o in obs]
@@ -46,3 +48,19 @@ def test_f32_projection_edges(d, dh, f, vocab, lens):
     shape = synth.ModelShape(n_layers=2, d_model=d, n_q_heads=4, n_kv_heads=2, head_dim=dh, d_ff=f, vocab=vocab,
                              dtype="f32", has_embeddings=True, std=0.1, coupling_std=0.5)
     prompts_and_steps(shape, lens, F32_TOL)
+
+
+# head sizes that are and are not whole 16-dimension pieces, groups of one to
+# four query heads, prompt tiles and pages around 16, more pages than waves
+# (8 x 16 positions), and caches on both sides of one 64-page split in a batch
+@pytest.mark.parametrize("dh,nq,nkv,lens", [
+    (4, 3, 3, [1, 15, 16, 17]),
+    (12, 6, 2, [2, 31]),
+    (128, 4, 4, [129, 130]),
+    (100, 8, 2, [127]),
+    (16, 2, 1, [1022, 1040, 7]),
+])
+def test_f32_attention_edges(dh, nq, nkv, lens):
+    shape = synth.ModelShape(n_layers=1, d_model=64, n_q_heads=nq, n_kv_heads=nkv, head_dim=dh, d_ff=96, vocab=64,
+                             dtype="f32", has_embeddings=True, std=0.2, coupling_std=0.5)
+    prompts_and_steps(shape, lens, F32_TOL, steps=4)
