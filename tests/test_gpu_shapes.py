@@ -64,3 +64,43 @@ def test_f32_attention_edges(dh, nq, nkv, lens):
     shape = synth.ModelShape(n_layers=1, d_model=64, n_q_heads=nq, n_kv_heads=nkv, head_dim=dh, d_ff=96, vocab=64,
                              dtype="f32", has_embeddings=True, std=0.2, coupling_std=0.5)
     prompts_and_steps(shape, lens, F32_TOL, steps=4)
+
+
+# fills that start and end inside pages, one position, whole pages, sources on
+# and off 16-byte boundaries: every filled slot is the source's bits, every
+# other slot keeps what it held
+@pytest.mark.parametrize("dtype,dh,nkv,start,count,off", [
+    ("bf16", 128, 2, 0, 48, 0),
+    ("bf16", 128, 2, 5, 1, 0),
+    ("bf16", 128, 1, 13, 40, 0),
+    ("bf16", 128, 2, 3, 61, 1),
+    ("f32", 64, 3, 16, 35, 0),
+    ("f32", 12, 2, 1, 30, 0),
+    ("f32", 12, 2, 1, 30, 1),
+])
+def test_kv_fill_edges(dtype, dh, nkv, start, count, off):
+    from paper_2608_12385_amd import binding
+    shape = synth.ModelShape(n_layers=2, d_model=128, n_q_heads=nkv, n_kv_heads=nkv, head_dim=dh, d_ff=128, vocab=0,
+                             dtype=dtype, has_embeddings=False)
+    sess = make_session(shape, synth.make_weights(shape), max_batch=2, max_pos=80)
+    wt = torch.int16 if dtype == "bf16" else torch.int32
+    binding.dbt_kv_reserve(sess.kv, 0, 17)
+    pages = binding.dbt_kv_reserve(sess.kv, 1, 64)
+    g = torch.Generator().manual_seed(1)
+    src = [torch.randint(-30000, 30000, (off + count * nkv * dh,), generator=g).to(wt).cuda() for _ in range(2)]
+    sess.k_pages.fill_(0x55)
+    sess.v_pages.fill_(0x55)
+    want = []
+    for pool, s, kdim in ((sess.k_pages, src[0], True), (sess.v_pages, src[1], False)):
+        w = pool.view(wt).view(2, -1, nkv, 16 * dh).clone()
+        rows = s[off:].view(count, nkv, dh)
+        for i in range(count):
+            pos = start + i
+            blk = w[1, pages[pos // 16]]
+            (blk.view(nkv, 16, dh)[:, pos % 16] if kdim else blk.view(nkv, dh, 16)[:, :, pos % 16]).copy_(rows[i])
+        want.append(w)
+    binding.dbt_kv_fill(sess.kv, 1, 1, start, count, src[0][off:].data_ptr(), src[1][off:].data_ptr(), sess.stream)
+    torch.cuda.synchronize()
+    for pool, w in ((sess.k_pages, want[0]), (sess.v_pages, want[1])):
+        assert torch.equal(pool.view(wt).view(w.shape), w)
+    sess.close()
