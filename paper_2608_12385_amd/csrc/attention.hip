@@ -381,9 +381,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
           q1 = rope_pair(x[0], x[1], csi);
           qs[hh][i] = q1.x;
           qs[hh][i + DH / 2] = q1.y;
-          const Retain &rt = f.ret;
-          if (rt.ptr && (rt.src_row < 0 || rt.src_row == b)) {
-            float *kp = rt.ptr + (size_t)(rt.src_row < 0 ? b : rt.dst_row) * dq;
+          const int kept = f.ret.row(b);
+          if (kept >= 0) {
+            float *kp = f.ret.ptr + (size_t)kept * dq;
             kp[c0] = q1.x;
             kp[c1] = q1.y;
           }

@@ -53,6 +53,12 @@ constexpr int kPage = 16;
 // fp32 splits are 64 pages long.
 constexpr int kSplitTargetBf16 = 86, kSplitMinBf16 = 16, kSplitTargetF32 = 64, kSplitWideMin = 256;
 constexpr int kMixChunk = 4096;
+// Prompts are prefilled in packed passes of up to max(max_prompt, kPackRows)
+// rows, so that each weight is read once for many short prompts and the tiled
+// projections fill the chip: a W_O of 2048 columns has 8 x 32 tiles at 8192
+// rows, one for each compute unit.  24 prompts of 17-300 positions through two
+// layers of width 2048: 7.74 ms one by one, 1.13 ms packed.
+constexpr int kPackRows = 8192;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 int round16(int x) { return (x + 15) / 16 * 16; }
@@ -61,7 +67,7 @@ int n_branches(const dbt_config &c) { return c.n_branches > 1 ? c.n_branches : 1
 
 // Offsets (bytes) of every workspace buffer.
 struct Layout {
-  int Bp_max = 0, R_max = 0, rows_max = 0, max_in = 0, nqkv = 0, f = 0;
+  int Bp_max = 0, R_max = 0, rows_max = 0, pack_rows = 0, max_in = 0, nqkv = 0, f = 0;
   GemmConfig g_qkv{1, 1, 1}, g_o{1, 1, 1}, g_gu{1, 1, 1}, g_d{1, 1, 1}, g_lm{1, 1, 1};
   int split_target = 0, max_splits = 0, nch = 0, nstat = 0;
   bool wide = false;  // attention splits in eight-wave workgroups (see the layout set-up)
@@ -74,9 +80,11 @@ struct Layout {
   GemmConfig g_sgu{1, 1, 1}, g_sd{1, 1, 1};
   size_t moe_idx = 0, moe_logits = 0, moe_w = 0, moe_aslot = 0, moe_counts = 0, moe_offsets = 0, moe_arow = 0, moe_h = 0,
          moe_y = 0, ret_idx = 0;
+  size_t prow = 0, ptiles = 0;  // prompt passes: row map, attention tiles
   size_t rope = 0, pos = 0, S = 0, Xn = 0, Xh = 0, Q = 0, O = 0, P = 0, apart = 0, astat = 0,
          logits = 0, mstats = 0, xss = 0, ret_q = 0, ret_h = 0, ret_m = 0, ret_a = 0, btok = 0, slast = 0,
-         state_total = 0, total = 0;  // [0, state_total): state; [state_total, total): step buffers
+         // [0, state_total): state; [state_total, step_total): step buffers; [step_total, total): prompt passes
+         state_total = 0, step_total = 0, total = 0;
 };
 
 dbt_status check_config(const dbt_config *c) {
@@ -125,7 +133,24 @@ dbt_status check_config(const dbt_config *c) {
   return DBT_OK;
 }
 
-Layout make_layout(const dbt_config *c) {
+// Reduction splits of a streaming projection over M prompt rows (fewer than
+// the tiled projection needs): the decode splits, fewer where the second
+// block of 128 rows doubles the workgroups.
+int prompt_splits(const GemmConfig &g, int M) { return std::max(1, g.S / ((M + 127) / 128)); }
+
+// fp32 output elements a projection N x K of a prompt pass of up to `rows`
+// rows can need: plain outputs, or the slabs of a short pass.  fused: the
+// tiled kernel's epilogue writes no fp32 output.
+size_t prompt_part(const GemmConfig &g, int N, int K, int dtype, int rows, bool fused) {
+  const bool tiled = dtype == DBT_BF16 && (long long)N * K < (1LL << 32) && (long long)rows * K < (1LL << 32);
+  const size_t slabs = dtype == DBT_BF16 ? (size_t)std::max(g.S, 2) * std::min(rows, 128) * N : 0;
+  return std::max(slabs, tiled && fused ? (size_t)0 : (size_t)rows * N);
+}
+
+// The workspace of a model: the state, the buffers of a call over stacked
+// sequences (rows_min: at least that many rows in each), and the buffers of
+// the packed prompt passes.
+Layout make_layout(const dbt_config *c, int rows_min = 0) {
   Layout L;
   const int d = c->d_model, dq = c->n_q_heads * c->head_dim, dkv = c->n_kv_heads * c->head_dim;
   L.moe = c->n_experts > 0;
@@ -134,7 +159,7 @@ Layout make_layout(const dbt_config *c) {
   L.f = L.moe ? std::max(L.fs, 128) : c->d_ff;
   L.Bp_max = round16(c->max_batch);
   L.R_max = (1 + n_branches(*c)) * L.Bp_max;
-  L.rows_max = std::max(L.R_max, c->max_prompt);
+  L.rows_max = std::max(L.R_max, rows_min);
   L.max_in = std::max(std::max(d, dq), L.f);
   L.nqkv = dq + 2 * dkv;
   L.g_qkv = gemm_config(L.nqkv, d, c->dtype, std::gcd(dq, dkv), L.R_max);
@@ -167,10 +192,13 @@ Layout make_layout(const dbt_config *c) {
   }
   L.max_splits = (maxpages + L.split_target - 1) / L.split_target;
   L.nch = c->vocab > 0 ? (c->vocab + kMixChunk - 1) / kMixChunk : 0;
+  L.pack_rows = c->max_prompt > 0
+                    ? (int)std::max<long long>(c->max_prompt, std::min<long long>((long long)c->max_batch * c->max_prompt, kPackRows))
+                    : 0;
   size_t part = std::max({(size_t)L.g_qkv.S * L.R_max * L.nqkv, (size_t)L.g_o.S * L.R_max * d,
                           (size_t)L.g_gu.S * L.R_max * 2 * L.f, (size_t)L.g_d.S * L.R_max * d});
   if (L.moe) part = std::max({part, (size_t)L.g_sgu.S * L.R_max * 2 * L.f, (size_t)L.g_sd.S * L.R_max * d});
-  part = std::max(part, (size_t)c->max_prompt * std::max({L.nqkv, d, 2 * L.f}));
+  part = std::max(part, (size_t)rows_min * std::max({L.nqkv, d, 2 * L.f}));
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += align256(bytes); return at; };
   // State kept between calls: the RoPE table, positions, the primary
@@ -215,6 +243,41 @@ Layout make_layout(const dbt_config *c) {
     L.moe_h = take((size_t)L.amax * L.fe * 2);
     L.moe_y = take((size_t)L.amax * d * 4);
   }
+  L.step_total = L.total = o;
+  return L;
+}
+
+// The same buffers for the packed prompt passes, behind those of L.
+Layout make_prompt_layout(const dbt_config *c, const Layout &step) {
+  Layout L = step;
+  const int d = c->d_model, dq = c->n_q_heads * c->head_dim, R = L.pack_rows;
+  const size_t es = c->dtype == DBT_BF16 ? 2 : 4;
+  if (R == 0) return L;
+  size_t o = step.total;
+  auto take = [&](size_t bytes) { size_t at = o; o += align256(bytes); return at; };
+  L.prow = take((size_t)R * sizeof(PromptRow));
+  L.ptiles = take((size_t)R * sizeof(PromptTile));
+  L.S = take((size_t)R * d * 4);
+  L.Xn = take((size_t)R * d * es);
+  L.Xh = take((size_t)R * L.f * es);
+  L.Q = take((size_t)R * dq * 4);
+  L.O = take((size_t)R * dq * es);
+  size_t part = std::max(prompt_part(L.g_qkv, L.nqkv, d, c->dtype, R, true), prompt_part(L.g_o, d, dq, c->dtype, R, false));
+  if (L.moe)
+    part = std::max({part, (size_t)R * 2 * L.fs, (size_t)R * d * (size_t)std::max(L.g_sd.S, 1)});
+  else
+    part = std::max({part, prompt_part(L.g_gu, 2 * L.f, d, c->dtype, R, true), prompt_part(L.g_d, d, L.f, c->dtype, R, false)});
+  L.P = take(part * 4);
+  if (L.moe) {
+    L.amax = R * c->top_k1;  // (the primary alone)
+    L.moe_idx = take((size_t)R * 8 * 4);
+    L.moe_logits = take((size_t)R * 256 * 4);
+    L.moe_w = take((size_t)R * 8 * 4);
+    L.moe_aslot = take((size_t)R * 8 * 4);
+    L.moe_arow = take((size_t)L.amax * 4);
+    L.moe_h = take((size_t)L.amax * L.fe * 2);
+    L.moe_y = take((size_t)L.amax * d * 4);
+  }
   L.total = o;
   return L;
 }
@@ -249,7 +312,8 @@ struct dbt_model {
   dbt_weights w;
   std::vector<dbt_layer_weights> layers;
   char *ws = nullptr;
-  Layout L;
+  Layout L, Lp;  // Lp: the buffers of the packed prompt passes
+  size_t noalloc_bytes = 0;  // see step_bytes
   std::vector<float> rope_host;
   bool dev_ready = false;
   // boundary state: set by dbt_prefill(run_boundary = 0)
@@ -258,7 +322,9 @@ struct dbt_model {
   // Step buffers of the current call: the workspace's own step region, or
   // memory a call supplies for them (see decode_step_in).
   char *step = nullptr;
-  char *p(size_t off) const { return off >= L.state_total ? step + (off - L.state_total) : ws + off; }
+  char *p(size_t off) const {
+    return off >= L.state_total && off < L.step_total ? step + (off - L.state_total) : ws + off;
+  }
   template <typename T> T *at(size_t off) const { return (T *)p(off); }
 };
 
@@ -326,39 +392,65 @@ KVRef kv_layer(const dbt_kv *kv, int l) {
 
 dbt_status ensure_device(dbt_model *m, hipStream_t st) {
   if (m->dev_ready) return DBT_OK;
-  HIPCHK(hipMemsetAsync(m->ws, 0, m->L.total, st));
+  HIPCHK(hipMemsetAsync(m->ws, 0, m->L.state_total, st));  // (step buffers need no clearing)
   HIPCHK(hipMemcpyAsync(m->p(m->L.rope), m->rope_host.data(), m->rope_host.size() * sizeof(float),
                         hipMemcpyHostToDevice, st));
   m->dev_ready = true;
   return DBT_OK;
 }
 
-// Enqueue pending page-table entries and (optionally) per-sequence positions.
-// With `fold` the last block is returned there instead of launched, for the
-// caller to pass to the step's first kernel.
+// Enqueue pending page-table entries and (optionally) per-sequence positions:
+// runs of consecutive pages (new sequences) as one launch of up to kPageRuns
+// runs, single entries with the positions.  With `fold` the last block of
+// those is returned there instead of launched, for the caller to pass to the
+// step's first kernel.
 dbt_status flush(dbt_kv *kv, const int *h_pos, int npos, hipStream_t st, StepBegin *fold = nullptr) {
   dbt_model *m = kv->m;
-  size_t ip = 0;
-  int ipos = 0;
   if (fold) {
     fold->n_pos = fold->n_pt = 0;
     fold->b0 = 0;
   }
-  while (ip < kv->pending.size() || ipos < npos) {
+  PageRuns pr;
+  pr.n = 0;
+  size_t single = 0;  // single entries, moved to the front of the list
+  for (size_t i = 0; i < kv->pending.size();) {
+    const dbt_kv::Upd u = kv->pending[i];
+    size_t e = i + 1;
+    while (e < kv->pending.size() && kv->pending[e].b == u.b && kv->pending[e].slot == u.slot + (int)(e - i) &&
+           kv->pending[e].page == u.page + (int)(e - i))
+      ++e;
+    if (e == i + 1) {
+      kv->pending[single++] = u;
+    } else {
+      pr.b[pr.n] = u.b;
+      pr.slot[pr.n] = u.slot;
+      pr.page[pr.n] = u.page;
+      pr.count[pr.n] = (int)(e - i);
+      if (++pr.n == kPageRuns) {
+        HIPCHK(launch_page_runs(pr, kv->page_table, kv->mpps, st));
+        pr.n = 0;
+      }
+    }
+    i = e;
+  }
+  HIPCHK(launch_page_runs(pr, kv->page_table, kv->mpps, st));
+  size_t ip = 0;
+  int ipos = 0;
+  while (ip < single || ipos < npos) {
     StepBegin sb;
     std::memset(&sb, 0, sizeof sb);
     sb.b0 = ipos;
     sb.n_pos = std::min(64, npos - ipos);
     for (int i = 0; i < sb.n_pos; ++i) sb.pos[i] = h_pos[ipos + i];
     ipos += sb.n_pos;
-    sb.n_pt = (int)std::min<size_t>(64, kv->pending.size() - ip);
+    sb.n_pt = (int)std::min<size_t>(64, single - ip);
     for (int i = 0; i < sb.n_pt; ++i) {
       sb.pt_b[i] = kv->pending[ip + i].b;
       sb.pt_slot[i] = kv->pending[ip + i].slot;
       sb.pt_page[i] = kv->pending[ip + i].page;
     }
     ip += sb.n_pt;
-    if (fold && ip >= kv->pending.size() && ipos >= npos) {
+    if (fold && ip >= single && ipos >= npos) {
       *fold = sb;
       break;
     }
@@ -373,10 +465,9 @@ struct LayerCall {
   Rows rows;
   int mode;
   bool retain;
-  int ret_src, ret_dst;
   bool prefill;
-  int seq;           // prefill: the sequence
-  int rows_layout;   // prefill: T; decode: (1 + n_branches)*Bp
+  PromptAttn tiles;  // prefill: the pass's attention tiles (list, count, positions per tile)
+  int rows_layout;   // prefill: rows of the pass; decode: (1 + n_branches)*Bp
   bool last_norm;    // apply the next norm after the layer
   const dbt_step_out *out;  // routing outputs (MoE), may be NULL
   // layer 0 reads its rows straight from the step inputs (XNorm; no norm
@@ -420,7 +511,8 @@ bool input_fold(const dbt_model *m, const dbt_kv *kv, int B) {
 // shared expert (with the b coupling), combine (with the c coupling).
 dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) {
   const dbt_config &cf = m->cfg;
-  const Layout &L = m->L;
+  const Layout &L = c.prefill ? m->Lp : m->L;
+  const PromptRow *map = c.prefill ? m->at<PromptRow>(L.prow) : nullptr;
   const dbt_layer_weights &W = m->layers[l];
   const int d = cf.d_model, fs = L.fs;
   const int xrow0 = c.rows.p0 * c.rows.Bp;
@@ -459,8 +551,7 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
     ro.out_lg2 = c.out->route_logits2 ? c.out->route_logits2 + (size_t)l * B * E : nullptr;
   }
   ro.ret_idx = c.retain ? ret_idx : nullptr;
-  ro.ret_src = c.ret_src;
-  ro.ret_dst = c.ret_dst;
+  ro.ret_map = map;
   // The shared expert needs only the normed rows: it runs on a second stream
   // beside the routing chain (router, top-k, dispatch: short kernels that
   // leave most compute units idle) and the routed experts; the combine waits
@@ -507,7 +598,7 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
     HIPCHK(launch_gemm(gu, 2 * fs, d, cf.dtype, m->p(L.Xn) + (size_t)sxrow0 * d * es, d, sM,
                        P + (size_t)sxrow0 * 2 * fs, 2 * fs, st_gu, g_sgu, sst));
     HIPCHK(launch_swiglu_finish(P, st_gu, g_sgu.S, 2 * fs, fs, smode, srows, W.b, ret_h,
-                                Retain{c.retain && !cm ? ret_h : nullptr, c.ret_src, c.ret_dst}, cf.dtype,
+                                Retain{c.retain && !cm ? ret_h : nullptr, map}, cf.dtype,
                                 m->p(L.Xh), fs, sst));
     WSegs sd{{W.s_down, nullptr, nullptr}, {d, 0, 0}};
     HIPCHK(launch_gemm(sd, d, fs, cf.dtype, m->p(L.Xh) + (size_t)sxrow0 * fs * es, fs, sM, P + (size_t)sxrow0 * d,
@@ -583,7 +674,7 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
   cb.S_sh = S_sh;
   cb.c = W.c;
   cb.M1_in = ret_m;  // compute-matched: the kept G1
-  cb.ret = Retain{c.retain ? ret_m : nullptr, c.ret_src, c.ret_dst};
+  cb.ret = Retain{c.retain ? ret_m : nullptr, map};
   cb.gG = cm ? W.g_shared_copy : nullptr;
   cb.S = S;
   cb.g_next = g_next;
@@ -596,7 +687,8 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
 
 dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStream_t st) {
   const dbt_config &cf = m->cfg;
-  const Layout &L = m->L;
+  const Layout &L = c.prefill ? m->Lp : m->L;
+  const PromptRow *map = c.prefill ? m->at<PromptRow>(L.prow) : nullptr;
   const dbt_layer_weights &W = m->layers[l];
   const int d = cf.d_model, dq = cf.n_q_heads * cf.head_dim, dkv = cf.n_kv_heads * cf.head_dim, f = L.f;
   const size_t es = esize(cf);
@@ -604,8 +696,12 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
   const int M = c.rows.np * c.rows.Bp;
   char *Xn = m->p(L.Xn), *Xh = m->p(L.Xh), *O = m->p(L.O);
   float *P = m->at<float>(L.P), *S = m->at<float>(L.S), *Q = m->at<float>(L.Q);
-  // prompt-wide rows: no reduction split (plenty of row tiles)
-  auto cfg = [&](GemmConfig g) { if (c.prefill) g.S = 1; return g; };
+  // prompt-wide rows: no reduction split (plenty of row tiles), but for a
+  // short pass, which the streaming kernel runs like a step
+  auto cfg = [&](GemmConfig g) {
+    if (c.prefill) g.S = M < kTileRows && cf.dtype == DBT_BF16 ? prompt_splits(g, M) : 1;
+    return g;
+  };
   // A projection of the active rows: the 256-row tiled kernel over a whole
   // prompt, the weight-streaming kernel otherwise.
   auto project = [&](const WSegs &segs, int N, int K, const char *X, int ldx, int rows_M, float *Y, int ldy,
@@ -674,10 +770,8 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
     tq.rope = m->at<float2>(L.rope);
     tq.Qout = Q;
     tq.kv = kvl;
-    tq.seq = c.seq;
-    tq.ret = c.retain && !cm ? ret_q : nullptr;
-    tq.ret_src = c.ret_src;
-    tq.ret_dst = c.ret_dst;
+    tq.prompt = map;
+    tq.ret = Retain{c.retain && !cm ? ret_q : nullptr, map};
   }
   const bool qkv_fused = tq.rope && gemm_tile_args_ok(tq, false);
   // Decode on the bf16 cache: the attention kernel finishes the queries and
@@ -724,11 +818,11 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
   qf.mode = amode;
   qf.rope = m->at<float2>(L.rope);
   qf.pos_arr = c.prefill ? nullptr : m->at<int>(L.pos);
-  qf.seq_fixed = c.seq;
+  qf.prompt = map;
   qf.a = W.a;
   qf.Q = Q;
   qf.Q1_in = ret_q;
-  qf.ret = Retain{c.retain && !cm ? ret_q : nullptr, c.ret_src, c.ret_dst};
+  qf.ret = Retain{c.retain && !cm ? ret_q : nullptr, map};
   qf.kv = kvl;
   qf.dtype = cf.dtype;
   if (xin) {
@@ -742,7 +836,15 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
 
   // 2. attention over the primary cache
   if (c.prefill) {
-    HIPCHK(launch_attn_prefill(Q, dq, c.rows.B, kvl, c.seq, cf.n_q_heads, cf.dtype, O, dq, st));
+    PromptAttn pa = c.tiles;
+    pa.Q = Q;
+    pa.ldq = dq;
+    pa.kv = kvl;
+    pa.n_q = cf.n_q_heads;
+    pa.dtype = cf.dtype;
+    pa.O = O;
+    pa.ldo = dq;
+    HIPCHK(launch_attn_prefill(pa, st));
   } else {
     AttnArgs aa{};
     aa.Q = Q;
@@ -778,7 +880,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
     Timed tm(m, DBT_STAGE_WO, st);
     HIPCHK(project(wo, d, dq, O + (size_t)axrow0 * dq * es, dq, aM, P + (size_t)axrow0 * d, d, stride, g_o));
   }
-  const GatedCopy gca = cm ? GatedCopy{W.g_attn_copy, ret_a, Retain{c.retain ? ret_a : nullptr, c.ret_src, c.ret_dst}}
+  const GatedCopy gca = cm ? GatedCopy{W.g_attn_copy, ret_a, Retain{c.retain ? ret_a : nullptr, map}}
                            : GatedCopy{};
   HIPCHK(launch_resid_norm(P, stride, S_o, d, S, W.mlp_norm, cf.rms_eps, d, cf.dtype, c.rows, Xn, d, st, gca, hin0));
 
@@ -786,7 +888,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
 
   // 4. gate/up + SwiGLU + b coupling (fused into the projection's epilogue
   // when the tiles fill the chip)
-  const Retain ret_h_keep{c.retain ? ret_h : nullptr, c.ret_src, c.ret_dst};
+  const Retain ret_h_keep{c.retain ? ret_h : nullptr, map};
   TileGemm tg{};
   if (c.prefill && c.mode == MODE_PRIMARY && c.rows.np == 1 && cf.dtype == DBT_BF16) {
     tg.w[0] = (const uint16_t *)W.w_gate;
@@ -799,9 +901,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
     tg.M = M;
     tg.H = (uint16_t *)(Xh + (size_t)xrow0 * f * es);
     tg.ldh = f;
-    tg.ret = ret_h_keep.ptr;
-    tg.ret_src = ret_h_keep.src_row;
-    tg.ret_dst = ret_h_keep.dst_row;
+    tg.ret = ret_h_keep;
   }
   if (tg.w[0] && gemm_tile_args_ok(tg, true)) {
     Timed tm(m, DBT_STAGE_GATEUP, st);
@@ -834,7 +934,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
   if (l + 1 < cf.n_layers) g_next = m->layers[l + 1].attn_norm;
   else if (cf.vocab > 0 && c.last_norm) g_next = m->w.final_norm;
   HIPCHK(launch_down_finish(P, stride, S_d, d, d, c.mode, c.rows, W.c, ret_m,
-                            Retain{c.retain ? ret_m : nullptr, c.ret_src, c.ret_dst}, S, g_next, cf.rms_eps,
+                            Retain{c.retain ? ret_m : nullptr, map}, S, g_next, cf.rms_eps,
                             cf.dtype, Xn, d, st));
   return DBT_OK;
 }
@@ -968,8 +1068,6 @@ dbt_status branch_pass(dbt_model *m, dbt_kv *kv, int B, int Bp, hipStream_t st, 
   lc.rows = Rows{B, Bp, 1, nb};
   lc.mode = MODE_BRANCH;
   lc.retain = false;
-  lc.ret_src = -1;
-  lc.ret_dst = 0;
   lc.prefill = false;
   lc.rows_layout = (1 + nb) * Bp;
   lc.last_norm = true;
@@ -1009,7 +1107,6 @@ dbt_status decode_step_impl(dbt_model *m, dbt_kv *kv, const dbt_step_in *in, int
   lc.rows = rows;
   lc.mode = on ? MODE_GROUPED : MODE_PRIMARY;
   lc.retain = false;
-  lc.ret_src = -1;
   lc.prefill = false;
   lc.rows_layout = (1 + nb) * Bp;
   lc.last_norm = true;
@@ -1036,7 +1133,7 @@ const char *dbt_last_error(void) { return g_err.c_str(); }
 
 size_t dbt_workspace_bytes(const dbt_config *cfg) {
   if (check_config(cfg) != DBT_OK) return 0;
-  return make_layout(cfg).total;
+  return make_prompt_layout(cfg, make_layout(cfg)).total;
 }
 
 size_t dbt_kv_pages_bytes(const dbt_config *cfg, int32_t num_pages) {
@@ -1073,6 +1170,9 @@ dbt_status dbt_create(const dbt_config *cfg, const dbt_weights *w, void *workspa
   m->w.h_layers = nullptr;
   m->ws = (char *)workspace;
   m->L = make_layout(cfg);
+  m->Lp = make_prompt_layout(cfg, m->L);
+  const Layout with_prompt = make_layout(cfg, cfg->max_prompt);
+  m->noalloc_bytes = with_prompt.step_total - with_prompt.state_total;
   m->step = m->ws + m->L.state_total;
   // RoPE table (Eq. (8)): angle pos * theta^(-2i/d_h), evaluated in double.
   const int half = cfg->head_dim / 2;
@@ -1219,7 +1319,6 @@ dbt_status dbt_decode_step_ungrouped(dbt_model *m, dbt_kv *kv, const dbt_step_in
   lc.rows = prim;
   lc.mode = MODE_PRIMARY;
   lc.retain = true;
-  lc.ret_src = -1;
   lc.prefill = false;
   lc.rows_layout = (1 + n_branches(cf)) * Bp;
   lc.last_norm = true;
@@ -1271,27 +1370,42 @@ dbt_status dbt_prefill(dbt_model *m, dbt_kv *kv, const int32_t *tokens, const in
   const Layout &L = m->L;
   const int d = cf.d_model;
   const int Bp = round16(batch);
-  size_t off = 0;
-  for (int b = 0; b < batch; ++b) {
-    const int T = h_prompt_lens[b];
+  // Packed passes over consecutive prompts: as few as the rows of the prompt
+  // buffers allow, of about equal size.
+  const Layout &Lp = m->Lp;
+  size_t off = 0, left = 0;
+  for (int b = 0; b < batch; ++b) left += h_prompt_lens[b];
+  for (int b = 0; b < batch;) {
+    const size_t passes = (left + Lp.pack_rows - 1) / Lp.pack_rows, share = (left + passes - 1) / passes;
+    Pack pk;
+    pk.n = 0;
+    pk.seq0 = b;
+    pk.off[0] = 0;
+    int T = 0, longest = 0;
+    while (b < batch && pk.n < kPackSeqs && (pk.n == 0 || ((size_t)T < share && T + h_prompt_lens[b] <= Lp.pack_rows))) {
+      T += h_prompt_lens[b];
+      longest = std::max(longest, h_prompt_lens[b]);
+      pk.off[++pk.n] = T;
+      ++b;
+    }
+    left -= T;
     const Rows rows{T, T, 0, 1};
-    HIPCHK(launch_embed(tokens + off, cf.vocab, m->w.emb1, m->w.emb2, m->w.emb_norm, m->layers[0].attn_norm, cf.rms_eps, d,
-                        cf.dtype, rows, m->at<float>(L.S), m->p(L.Xn), d, st));
     LayerCall lc{};
+    lc.tiles.tp = prompt_tile_positions(cf.n_q_heads, cf.n_kv_heads, longest, cf.dtype);
+    lc.tiles.long_prompt = prompt_is_long(longest);
+    lc.tiles.tiles = m->at<PromptTile>(Lp.ptiles);
+    HIPCHK(launch_prompt_plan(pk, lc.tiles.tp, m->at<PromptRow>(Lp.prow), m->at<PromptTile>(Lp.ptiles), &lc.tiles.ntiles, st));
+    HIPCHK(launch_embed(tokens + off, cf.vocab, m->w.emb1, m->w.emb2, m->w.emb_norm, m->layers[0].attn_norm, cf.rms_eps, d,
+                        cf.dtype, rows, m->at<float>(Lp.S), m->p(Lp.Xn), d, st));
     lc.rows = rows;
     lc.mode = MODE_PRIMARY;
     lc.retain = true;
-    lc.ret_src = T - 1;
-    lc.ret_dst = b;
     lc.prefill = true;
-    lc.seq = b;
     lc.rows_layout = T;
     lc.last_norm = false;
     for (int l = 0; l < cf.n_layers; ++l)
       if ((s = run_layer(m, kv, l, lc, st))) return s;
-    HIPCHK(hipMemcpyAsync(m->at<float>(L.slast) + (size_t)b * d, m->at<float>(L.S) + (size_t)(T - 1) * d, d * 4,
-                          hipMemcpyDeviceToDevice, st));
-    HIPCHK(hipMemcpyAsync(m->at<int>(L.btok) + b, tokens + off + T - 1, 4, hipMemcpyDeviceToDevice, st));
+    HIPCHK(launch_prompt_last(pk, m->at<float>(Lp.S), tokens + off, d, m->at<float>(L.slast), m->at<int>(L.btok), st));
     off += T;
   }
   // primary logits at each prompt's final position
@@ -1367,7 +1481,7 @@ namespace dbt {
 
 dbt_status set_error(dbt_status s, const char *msg) { return fail(s, "%s", msg); }
 
-size_t step_bytes(const dbt_model *m) { return m->L.total - m->L.state_total; }
+size_t step_bytes(const dbt_model *m) { return m->noalloc_bytes; }
 
 dbt_status decode_step_in(dbt_model *m, dbt_kv *kv, const dbt_step_in *in, int32_t branch_on, dbt_step_out *out,
                           dbt_stream stream, char *step_mem) {

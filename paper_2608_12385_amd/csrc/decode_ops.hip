@@ -27,6 +27,50 @@ __global__ void k_step_begin(StepBegin sb, int *pos_arr, int *page_table, int mp
   if (t < sb.n_pt) page_table[(size_t)sb.pt_b[t] * mpps + sb.pt_slot[t]] = sb.pt_page[t];
 }
 
+__global__ void k_page_runs(PageRuns pr, int *page_table, int mpps) {
+  const int i = blockIdx.x;
+  int *row = page_table + (size_t)pr.b[i] * mpps + pr.slot[i];
+  for (int j = threadIdx.x; j < pr.count[i]; j += blockDim.x) row[j] = pr.page[i] + j;
+}
+
+// Row map and attention tiles of a packed pass: thread i is row i, and also
+// the i-th (sequence, tile) pair in order, whose place in the list is the
+// number of tiles with a later position range (they see more keys and run
+// longer), then of equal ones of earlier sequences.
+__global__ __launch_bounds__(256) void k_prompt_plan(Pack pk, int tp, PromptRow *rows, PromptTile *tiles) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < pk.off[pk.n]) {
+    int lo = 0, hi = pk.n;  // off[lo] <= i < off[hi]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) / 2;
+      if (pk.off[mid] <= i) lo = mid;
+      else hi = mid;
+    }
+    const int seq = pk.seq0 + lo;
+    ((int4 *)rows)[i] = make_int4(i - pk.off[lo], seq, i + 1 == pk.off[lo + 1] ? seq : -1, 0);
+  }
+  int s = 0, j = i;
+  for (; s < pk.n; ++s) {
+    const int nt = (pk.off[s + 1] - pk.off[s] + tp - 1) / tp;
+    if (j < nt) break;
+    j -= nt;
+  }
+  if (s == pk.n) return;
+  int rank = 0;
+  for (int o = 0; o < pk.n; ++o) {
+    const int nt = (pk.off[o + 1] - pk.off[o] + tp - 1) / tp;
+    rank += max(0, nt - 1 - j) + (o < s && nt > j ? 1 : 0);
+  }
+  ((int4 *)tiles)[rank] = make_int4(pk.off[s], j * tp, pk.off[s + 1] - pk.off[s], pk.seq0 + s);
+}
+
+__global__ void k_prompt_last(Pack pk, const float *S, const int *tokens, int d, float *slast, int *btok) {
+  const int i = blockIdx.x, row = pk.off[i + 1] - 1, seq = pk.seq0 + i;
+  for (int j = threadIdx.x; j < d / 4; j += blockDim.x)
+    ((float4 *)(slast + (size_t)seq * d))[j] = ((const float4 *)(S + (size_t)row * d))[j];
+  if (threadIdx.x == 0) btok[seq] = tokens[row];
+}
+
 // Per-step positions and page-table entries travel as kernel arguments of
 // the step's first kernel (no host-to-device copy); block (0,0) writes them.
 __device__ __forceinline__ void apply_step_begin(const StepBegin &sb, int *pos_arr, int *page_table, int mpps) {
@@ -223,8 +267,8 @@ __global__ void k_qkv_finish(QKVFinish f) {
   const int total = prim ? nqp + 2 * nkp : nqp;
   const int pi = blockIdx.x * blockDim.x + threadIdx.x;
   if (pi >= total) return;
-  const int pos = f.pos_arr ? f.pos_arr[b] : b;
-  const int seq = f.pos_arr ? b : f.seq_fixed;
+  const int pos = f.pos_arr ? f.pos_arr[b] : f.prompt[b].pos;
+  const int seq = f.pos_arr ? b : f.prompt[b].seq;
   const int dq = f.n_q * f.d_h, dkv = f.n_kv * f.d_h;
   const int r1 = phys_row(f.rows, 0, b);
   const int pb0 = f.rows.p0 > 1 ? f.rows.p0 : 1, pb1 = f.rows.p0 + f.rows.np;  // branch paths of the call
@@ -240,10 +284,10 @@ __global__ void k_qkv_finish(QKVFinish f) {
       q1b = q1.y;
       f.Q[(size_t)r1 * dq + c0] = q1a;
       f.Q[(size_t)r1 * dq + c1] = q1b;
-      if (f.ret.ptr && (f.ret.src_row < 0 || f.ret.src_row == b)) {
-        const int dst = f.ret.src_row < 0 ? b : f.ret.dst_row;
-        f.ret.ptr[(size_t)dst * dq + c0] = q1a;
-        f.ret.ptr[(size_t)dst * dq + c1] = q1b;
+      const int kept = f.ret.row(b);
+      if (kept >= 0) {
+        f.ret.ptr[(size_t)kept * dq + c0] = q1a;
+        f.ret.ptr[(size_t)kept * dq + c1] = q1b;
       }
     } else {
       q1a = f.Q1_in[(size_t)b * dq + c0];
@@ -299,8 +343,9 @@ __global__ void k_resid_norm(const float *part, long long stride, int S, int ldp
   const float4 *sin = hin.h1 ? (const float4 *)((path == 0 ? hin.h1 : hin.h2 + (size_t)(path - 1) * hin.B * d) +
                                                 (size_t)b * d)
                              : s;
-  const bool keep = gc.g && path == 0 && gc.ret.ptr && (gc.ret.src_row < 0 || gc.ret.src_row == b);
-  float4 *kept = keep ? (float4 *)(gc.ret.ptr + (size_t)(gc.ret.src_row < 0 ? b : gc.ret.dst_row) * d) : nullptr;
+  const int kept_row = gc.g && path == 0 ? gc.ret.row(b) : -1;
+  const bool keep = kept_row >= 0;
+  float4 *kept = keep ? (float4 *)(gc.ret.ptr + (size_t)kept_row * d) : nullptr;
   const int r1 = phys_row(rows, 0, b);
   float4 v[R], gv[R];
 #pragma unroll
@@ -348,8 +393,8 @@ __global__ void k_swiglu_finish(const float *part, long long stride, int S, int 
     const float up = psum(part, stride, S, (size_t)r1 * ldp + f + j);
     h1 = gt / (1.0f + expf(-gt)) * up;
     st<T>(Xh, (size_t)r1 * ldh + j, h1);
-    if (ret.ptr && (ret.src_row < 0 || ret.src_row == b))
-      ret.ptr[(size_t)(ret.src_row < 0 ? b : ret.dst_row) * f + j] = h1;
+    const int kept = ret.row(b);
+    if (kept >= 0) ret.ptr[(size_t)kept * f + j] = h1;
   } else {
     h1 = H1_in[(size_t)b * f + j];
   }
@@ -378,8 +423,9 @@ __global__ void k_down_finish(const float *part, long long stride, int S, int ld
   if (path == 0 && !prim) return;
   const int r1 = phys_row(rows, 0, b), row = phys_row(rows, path, b);
   float4 *s = (float4 *)(Sres + (size_t)row * d);
-  const bool keep = path == 0 && ret.ptr && (ret.src_row < 0 || ret.src_row == b);
-  float4 *kept = keep ? (float4 *)(ret.ptr + (size_t)(ret.src_row < 0 ? b : ret.dst_row) * d) : nullptr;
+  const int kept_row = path == 0 ? ret.row(b) : -1;
+  const bool keep = kept_row >= 0;
+  float4 *kept = keep ? (float4 *)(ret.ptr + (size_t)kept_row * d) : nullptr;
   float4 v[R], gv[R];
 #pragma unroll
   for (int k = 0; k < R; ++k) {
@@ -741,6 +787,27 @@ __global__ __launch_bounds__(256) void k_mix_select(MixArgs m) {
 hipError_t launch_step_begin(const StepBegin &sb, int *pos_arr, int *page_table, int mpps, hipStream_t st) {
   if (sb.n_pos == 0 && sb.n_pt == 0) return hipSuccess;
   hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(64), 0, st, sb, pos_arr, page_table, mpps);
+  return hipGetLastError();
+}
+
+hipError_t launch_page_runs(const PageRuns &pr, int *page_table, int mpps, hipStream_t st) {
+  if (pr.n == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_page_runs, dim3(pr.n), dim3(64), 0, st, pr, page_table, mpps);
+  return hipGetLastError();
+}
+
+hipError_t launch_prompt_plan(const Pack &pk, int tp, PromptRow *rows, PromptTile *tiles, int *ntiles, hipStream_t st) {
+  if (pk.n < 1 || pk.n > kPackSeqs || tp < 1) return hipErrorInvalidValue;
+  int nt = 0;
+  for (int i = 0; i < pk.n; ++i) nt += (pk.off[i + 1] - pk.off[i] + tp - 1) / tp;
+  *ntiles = nt;  // (never more than the rows)
+  hipLaunchKernelGGL(k_prompt_plan, dim3((pk.off[pk.n] + 255) / 256), dim3(256), 0, st, pk, tp, rows, tiles);
+  return hipGetLastError();
+}
+
+hipError_t launch_prompt_last(const Pack &pk, const float *S, const int *tokens, int d, float *slast, int *btok,
+                              hipStream_t st) {
+  hipLaunchKernelGGL(k_prompt_last, dim3(pk.n), dim3(256), 0, st, pk, S, tokens, d, slast, btok);
   return hipGetLastError();
 }
 

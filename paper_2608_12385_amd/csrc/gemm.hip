@@ -342,9 +342,8 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_bf16(WSegs segs, int K, const 
       if (path == 0) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[i] = h[cb][i];
-        const Retain &rt = ep.ret;
-        if (rt.ptr && (rt.src_row < 0 || rt.src_row == b))
-          *(float4 *)&rt.ptr[(size_t)(rt.src_row < 0 ? b : rt.dst_row) * ep.f + n] = make_float4(o[0], o[1], o[2], o[3]);
+        const int kept = ep.ret.row(b);
+        if (kept >= 0) *(float4 *)&ep.ret.ptr[(size_t)kept * ep.f + n] = make_float4(o[0], o[1], o[2], o[3]);
       } else {
         const float4 bv = *(const float4 *)&ep.bvec[n];
         float h1[4];

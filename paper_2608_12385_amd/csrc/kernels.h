@@ -26,12 +26,41 @@ struct Rows {
 
 enum Mode { MODE_GROUPED = 0, MODE_PRIMARY = 1, MODE_BRANCH = 2 };
 
-// Retention of primary intermediates for a later branch evaluation.
-// src_row < 0: row b of the call is kept at retained row b (all rows);
-// src_row >= 0: only that row is kept, at retained row dst_row.
+// Prompts of several sequences are packed into one pass: row r of the pass is
+// position pos of sequence seq; keep is the sequence at its prompt's last
+// row (whose primary intermediates are kept for the boundary) and -1 elsewhere.
+struct PromptRow {
+  int pos, seq, keep, unused;
+};
+// One attention tile of a packed pass: query positions q0 .. of a prompt of T
+// positions of sequence seq, whose position 0 is row row0 of the pass.
+struct PromptTile {
+  int row0, q0, T, seq;
+};
+// Sequences seq0 .. seq0 + n - 1 of a pass: rows off[i] .. off[i + 1] - 1.
+constexpr int kPackSeqs = 128;
+struct Pack {
+  int n, seq0;
+  int off[kPackSeqs + 1];
+};
+// Fills the row map of the pass and its attention tiles of tp positions,
+// longest first; returns their number through *ntiles.
+hipError_t launch_prompt_plan(const Pack &pk, int tp, PromptRow *rows, PromptTile *tiles, int *ntiles, hipStream_t st);
+// After the last layer: each prompt's final residual row to slast[seq], its
+// final token to btok[seq].
+hipError_t launch_prompt_last(const Pack &pk, const float *S, const int *tokens, int d, float *slast, int *btok,
+                              hipStream_t st);
+
+// Retention of primary intermediates for a later branch evaluation: row b of
+// the call is kept at retained row b, or, in a pass over prompts, at
+// map[b].keep when that is not negative.
 struct Retain {
   float *ptr;  // NULL: nothing kept
-  int src_row, dst_row;
+  const PromptRow *map;
+#ifdef __HIPCC__
+  // the retained row of row b, -1 when it is not kept
+  __device__ __forceinline__ int row(int b) const { return !ptr ? -1 : map ? map[b].keep : b; }
+#endif
 };
 
 struct KVRef {
@@ -80,13 +109,11 @@ int gemm_tile_rows(const GemmConfig &g);  // weight rows (output columns) per wo
 // multiple of 16, bf16): 256-row tiles on the matrix cores.  Plain: Y (fp32,
 // [M][ldy]) = X W^T with W the stacked segments w[0..2] (rows[0..2] rows).
 // GLU: w[0] = gate, w[1] = up (N = f rows each); writes H (bf16, [M][ldh]) =
-// silu(X Wg^T) * (X Wu^T), and row ret_src of H in fp32 to ret + ret_dst*N
-// when ret is not NULL (ret_src < 0: every row m to ret + m*N).
-// QKV (rope != NULL; bf16 cache, d_h 128, rows = positions of sequence seq,
-// w = W_Q, W_K, W_V): the rotary embedding on Q and K, Q (fp32, [M][rows[0]])
-// to Qout and its row ret_src to ret + ret_dst*rows[0] (when ret is not
-// NULL; ret_src < 0: every row m to ret + m*rows[0]), K and V into the cache
-// slots of their positions; no Y.
+// silu(X Wg^T) * (X Wu^T), and keeps rows of H in fp32 (ret).  QKV (rope !=
+// NULL; bf16 cache, d_h 128, rows = prompt positions by the map `prompt`, w =
+// W_Q, W_K, W_V): the rotary embedding on Q and K, Q (fp32, [M][rows[0]]) to
+// Qout and its kept rows to ret, K and V into the cache slots of their
+// positions; no Y.
 struct TileGemm {
   const uint16_t *w[3];
   int rows[3];
@@ -97,14 +124,15 @@ struct TileGemm {
   int ldy;
   uint16_t *H;
   int ldh;
-  float *ret;
-  int ret_src, ret_dst;
+  Retain ret;
   const float2 *rope;  // [max_pos][64] (cos, sin)
   float *Qout;
   KVRef kv;
-  int seq;
+  const PromptRow *prompt;
 };
 bool gemm_tile_ok(int N, int K, int M, int dtype);
+// Prompt rows from which launch_gemm_tile is used (its tile height).
+constexpr int kTileRows = 256;
 // Everything launch_gemm_tile requires of g (the shape test above, segment
 // sizes multiples of 8 summing to N, row strides multiples of 8, element
 // offsets within 32 bits); callers fall back to launch_gemm otherwise.
@@ -118,6 +146,14 @@ struct StepBegin {
   int n_pt;
   int pt_b[64], pt_slot[64], pt_page[64];
 };
+// Runs of consecutive page-table entries: slots slot .. slot + count - 1 of
+// sequence b hold pages page, page + 1, ...
+constexpr int kPageRuns = 128;
+struct PageRuns {
+  int n;
+  int b[kPageRuns], slot[kPageRuns], page[kPageRuns], count[kPageRuns];
+};
+hipError_t launch_page_runs(const PageRuns &pr, int *page_table, int mpps, hipStream_t st);
 hipError_t launch_step_begin(const StepBegin &sb, int *pos_arr, int *page_table, int mpps,
                              hipStream_t st);
 
@@ -168,7 +204,7 @@ struct QKVFinish {
   int mode;
   const float2 *rope;  // [max_pos][d_h/2] (cos, sin)
   const int *pos_arr;  // decode: position of sequence b (NULL: prefill)
-  int seq_fixed;       // prefill: the sequence; the row index is the position
+  const PromptRow *prompt;  // prefill: position and sequence of row b
   const float *a;
   float *Q;            // [2Bp][n_q*d_h]
   const float *Q1_in;  // branch mode: retained primary queries [*, n_q*d_h]
@@ -235,9 +271,25 @@ struct AttnArgs {
 hipError_t launch_attn_decode(const AttnArgs &a, hipStream_t st);
 hipError_t launch_attn_combine(const AttnArgs &a, void *O, int ldo, hipStream_t st);
 
-// Causal attention of prompt positions 0..T-1 of one sequence (rows = positions).
-hipError_t launch_attn_prefill(const float *Q, int ldq, int T, KVRef kv, int seq, int n_q,
-                               int dtype, void *O, int ldo, hipStream_t st);
+// Causal attention of the prompts of a packed pass (rows by tiles[0..ntiles)).
+struct PromptAttn {
+  const float *Q;
+  int ldq;
+  KVRef kv;
+  int n_q;
+  int dtype;
+  void *O;
+  int ldo;
+  const PromptTile *tiles;
+  int ntiles;
+  int tp;           // positions per tile: prompt_tile_positions of the pass
+  int long_prompt;  // a prompt has more pages than the kernel that shares K/V holds ids for
+};
+// Query positions per workgroup for prompts of at most max_len positions
+// (n_q / n_kv query heads per KV head).
+int prompt_tile_positions(int n_q, int n_kv, int max_len, int dtype);
+bool prompt_is_long(int max_len);  // for PromptAttn::long_prompt
+hipError_t launch_attn_prefill(const PromptAttn &a, hipStream_t st);
 
 // ---- cache fill ----
 hipError_t launch_kv_fill(KVRef kv, int seq, int start, int count, const void *ksrc,
@@ -276,8 +328,8 @@ struct MoeRoute {
   int *out_idx1, *out_idx2;
   float *out_w1, *out_w2;  // caller outputs [B][k] of this layer (may be NULL)
   float *out_lg1, *out_lg2;  // caller router logits [B][E] of this layer (may be NULL)
-  int *ret_idx;       // retained primary selections (may be NULL)
-  int ret_src, ret_dst;
+  int *ret_idx;       // retained primary selections (may be NULL), kept as Retain keeps rows
+  const PromptRow *ret_map;
 };
 struct MoeDispatch {
   const int *idx;

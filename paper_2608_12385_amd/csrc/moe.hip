@@ -172,8 +172,9 @@ __global__ __launch_bounds__(64) void k_moe_topk(MoeRoute a) {
       float *ow = p == 0 ? a.out_w1 : a.out_w2;
       if (oi) for (int j = 0; j < k; ++j) oi[(size_t)b * k + j] = sel[j];
       if (ow) for (int j = 0; j < k; ++j) ow[(size_t)b * k + j] = w[j] / den;
-      if (p == 0 && a.ret_idx && (a.ret_src < 0 || a.ret_src == b))
-        for (int j = 0; j < k; ++j) a.ret_idx[(size_t)(a.ret_src < 0 ? b : a.ret_dst) * 8 + j] = sel[j];
+      const int kept = p != 0 || !a.ret_idx ? -1 : a.ret_map ? a.ret_map[b].keep : b;
+      if (kept >= 0)
+        for (int j = 0; j < k; ++j) a.ret_idx[(size_t)kept * 8 + j] = sel[j];
     }
   }
 }
@@ -477,8 +478,9 @@ __global__ void k_moe_combine(MoeCombine a) {
   __syncthreads();
   float4 *s1 = (float4 *)(a.S + (size_t)r1 * d);
   float4 *s2 = (float4 *)(a.S + (size_t)r2 * d);
-  const bool keep = a.ret.ptr && (a.ret.src_row < 0 || a.ret.src_row == b);
-  float4 *kept = keep ? (float4 *)(a.ret.ptr + (size_t)(a.ret.src_row < 0 ? b : a.ret.dst_row) * d) : nullptr;
+  const int kept_row = a.ret.row(b);
+  const bool keep = kept_row >= 0;
+  float4 *kept = keep ? (float4 *)(a.ret.ptr + (size_t)kept_row * d) : nullptr;
   // routed experts, ascending id; all eight slots (weight 0 past k: adding
   // zeros leaves the sum unchanged) so the loads are in flight together
   auto experts = [&](int p, int k, int i) {

@@ -19,11 +19,13 @@ typedef __attribute__((address_space(3))) void lds_void;
 // (lane: eight consecutive key positions of one page for one query), masks
 // keys after the query (causal) and cache slots past the prompt, and keeps an
 // online softmax per query row.  Tiles are issued longest first.
-__global__ __launch_bounds__(1024) void k_attn_prefill_bf16(const float *Q, int ldq, int T, KVRef kv, int seq,
-                                                           int n_q, uint16_t *O, int ldo) {
+__global__ __launch_bounds__(1024) void k_attn_prefill_bf16(PromptAttn a) {
   constexpr int DH = 128;
-  const int ntiles = (T + 15) >> 4;
-  const int q0 = (ntiles - 1 - (int)blockIdx.x) * 16;  // longest tiles first
+  const PromptTile tile = a.tiles[blockIdx.x];  // longest tiles first
+  const int q0 = tile.q0, T = tile.T, seq = tile.seq, n_q = a.n_q, ldq = a.ldq, ldo = a.ldo;
+  const KVRef &kv = a.kv;
+  const float *Q = a.Q + (size_t)tile.row0 * ldq;
+  uint16_t *O = (uint16_t *)a.O + (size_t)tile.row0 * ldo;
   const int g = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, gq = lane >> 4;
@@ -165,8 +167,7 @@ constexpr float kLazyMargin = 8.f;
 // that need one; a wave skips pairs that start after its last position.
 // Position tiles are issued longest first.
 template <int G>
-__global__ __launch_bounds__(1024) void k_attn_prefill_wide(const float *Q, int ldq, int T, KVRef kv, int seq,
-                                                            int n_q, uint16_t *O, int ldo) {
+__global__ __launch_bounds__(1024) void k_attn_prefill_wide(PromptAttn a) {
   constexpr int DH = 128, QB = 16 / G, TP = 16 * QB;  // query blocks per head, positions per workgroup
   constexpr int SP = 2;                                // pairs per stage (one barrier per stage)
   constexpr int PB = 2 * 16 * DH;                      // elements of one pair buffer (two pages)
@@ -176,8 +177,11 @@ __global__ __launch_bounds__(1024) void k_attn_prefill_wide(const float *Q, int 
   __shared__ __attribute__((aligned(16))) uint16_t kl0[SP * PB], kl1[SP * PB];
   __shared__ __attribute__((aligned(16))) uint16_t vl0[SP * PB], vl1[SP * PB];
   __shared__ int pid_s[kPrefillMaxPages];  // the sequence's page ids
-  const int ntiles = (T + TP - 1) / TP;
-  const int q0 = (ntiles - 1 - (int)blockIdx.x) * TP;  // longest tiles first
+  const PromptTile tile = a.tiles[blockIdx.x];  // longest tiles first
+  const int q0 = tile.q0, T = tile.T, seq = tile.seq, ldq = a.ldq, ldo = a.ldo;
+  const KVRef &kv = a.kv;
+  const float *Q = a.Q + (size_t)tile.row0 * ldq;
+  uint16_t *O = (uint16_t *)a.O + (size_t)tile.row0 * ldo;
   const int g = blockIdx.y;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: per-wave conditions stay scalar branches
@@ -399,13 +403,16 @@ __global__ __launch_bounds__(1024) void k_attn_prefill_wide(const float *Q, int 
 // fp32 cache: workgroup per (16 query positions, query head), longest tiles
 // first (attn_f32.h); the waves share the pages up to the tile's last position.
 template <int NC>
-__global__ __launch_bounds__(64 * kWavesF32Attn) void k_attn_prefill_f32(const float *Q, int ldq, int T, KVRef kv,
-                                                                         int seq, int n_q, float *O, int ldo) {
-  const int q0 = (((T + 15) >> 4) - 1 - (int)blockIdx.x) * 16, head = blockIdx.y;
-  const int g = head / (n_q / kv.n_kv), DH = kv.d_h;
+__global__ __launch_bounds__(64 * kWavesF32Attn) void k_attn_prefill_f32(PromptAttn a) {
+  const PromptTile tile = a.tiles[blockIdx.x];
+  const int q0 = tile.q0, T = tile.T, seq = tile.seq, head = blockIdx.y;
+  const KVRef &kv = a.kv;
+  const int g = head / (a.n_q / kv.n_kv), DH = kv.d_h;
+  const float *Q = a.Q + (size_t)tile.row0 * a.ldq;
+  float *O = (float *)a.O + (size_t)tile.row0 * a.ldo;
   const int qpos = q0 + (threadIdx.x & 15);
   __shared__ F32Merge<NC> mg;
-  attn_f32<NC>(mg, Q + (size_t)min(qpos, T - 1) * ldq + head * DH, qpos < T, qpos + 1, T, (const float *)kv.k,
+  attn_f32<NC>(mg, Q + (size_t)min(qpos, T - 1) * a.ldq + head * DH, qpos < T, qpos + 1, T, (const float *)kv.k,
                (const float *)kv.v, kv.page_table + (size_t)seq * kv.mpps, 0, (min(q0 + 15, T - 1) >> 4) + 1, kv.n_kv,
                g, DH);
   for (int e = threadIdx.x; e < 16 * DH; e += 64 * kWavesF32Attn) {
@@ -413,45 +420,55 @@ __global__ __launch_bounds__(64 * kWavesF32Attn) void k_attn_prefill_f32(const f
     if (q0 + qr >= T) continue;
     float o, l, mx;
     mg.merged(qr, dh, o, l, mx);
-    O[(size_t)(q0 + qr) * ldo + head * DH + dh] = o / l;
+    O[(size_t)(q0 + qr) * a.ldo + head * DH + dh] = o / l;
   }
 }
 
 }  // namespace
 
-hipError_t launch_attn_prefill(const float *Q, int ldq, int T, KVRef kv, int seq, int n_q, int dtype, void *O,
-                               int ldo, hipStream_t st) {
-  const int G = n_q / kv.n_kv;
-  if (dtype == 1 && kv.d_h == 128 && G >= 1 && G <= 16) {
-    dim3 grid((T + 15) / 16, kv.n_kv);
-    switch ((T + 15) / 16 <= kPrefillMaxPages && ldq % 4 == 0 ? G : 0) {  // K/V shared by 16 waves through LDS when G divides 16
-      case 1: case 2: case 4: case 8: case 16: {
-        const int tp = 256 / G;  // positions per workgroup
-        const dim3 wgrid((T + tp - 1) / tp, kv.n_kv);
-        if (G == 1) hipLaunchKernelGGL(k_attn_prefill_wide<1>, wgrid, dim3(1024), 0, st, Q, ldq, T, kv, seq, n_q, (uint16_t *)O, ldo);
-        else if (G == 2) hipLaunchKernelGGL(k_attn_prefill_wide<2>, wgrid, dim3(1024), 0, st, Q, ldq, T, kv, seq, n_q, (uint16_t *)O, ldo);
-        else if (G == 4) hipLaunchKernelGGL(k_attn_prefill_wide<4>, wgrid, dim3(1024), 0, st, Q, ldq, T, kv, seq, n_q, (uint16_t *)O, ldo);
-        else if (G == 8) hipLaunchKernelGGL(k_attn_prefill_wide<8>, wgrid, dim3(1024), 0, st, Q, ldq, T, kv, seq, n_q, (uint16_t *)O, ldo);
-        else hipLaunchKernelGGL(k_attn_prefill_wide<16>, wgrid, dim3(1024), 0, st, Q, ldq, T, kv, seq, n_q, (uint16_t *)O, ldo);
-        break;
+// K/V shared by 16 waves through LDS when G divides 16 and the page ids of
+// the longest prompt fit: 256 query rows per workgroup; else 16 positions.
+bool prompt_is_long(int max_len) { return (max_len + 15) / 16 > kPrefillMaxPages; }
+
+int prompt_tile_positions(int n_q, int n_kv, int max_len, int dtype) {
+  const int G = n_q / n_kv;
+  return dtype == 1 && 16 % G == 0 && !prompt_is_long(max_len) ? 256 / G : 16;
+}
+
+hipError_t launch_attn_prefill(const PromptAttn &a, hipStream_t st) {
+  const int G = a.n_q / a.kv.n_kv;
+  if (a.ntiles < 1 || !a.tiles) return hipErrorInvalidValue;
+  if (a.dtype == 1) {
+    if (a.kv.d_h != 128 || G < 1 || G > 16 || a.ldq % 4) return hipErrorInvalidValue;
+    const dim3 grid(a.ntiles, a.kv.n_kv);
+    // (G = 16: tiles of 16 positions fit both kernels; its longest prompts
+    // are told apart by the page ids)
+    if (a.tp == 256 / G && 16 % G == 0 && !a.long_prompt) {
+      switch (G) {
+        case 1: hipLaunchKernelGGL(k_attn_prefill_wide<1>, grid, dim3(1024), 0, st, a); break;
+        case 2: hipLaunchKernelGGL(k_attn_prefill_wide<2>, grid, dim3(1024), 0, st, a); break;
+        case 4: hipLaunchKernelGGL(k_attn_prefill_wide<4>, grid, dim3(1024), 0, st, a); break;
+        case 8: hipLaunchKernelGGL(k_attn_prefill_wide<8>, grid, dim3(1024), 0, st, a); break;
+        default: hipLaunchKernelGGL(k_attn_prefill_wide<16>, grid, dim3(1024), 0, st, a);
       }
-      default:
-        hipLaunchKernelGGL(k_attn_prefill_bf16, grid, dim3(64 * G), 0, st, Q, ldq, T, kv, seq, n_q, (uint16_t *)O, ldo);
+    } else if (a.tp == 16) {
+      hipLaunchKernelGGL(k_attn_prefill_bf16, grid, dim3(64 * G), 0, st, a);
+    } else {
+      return hipErrorInvalidValue;
     }
     return hipGetLastError();
   }
-  if (dtype == 1) return hipErrorInvalidValue;  // (bf16 caches have d_h = 128 and G <= 16, checked at creation)
-  const dim3 grid((T + 15) / 16, n_q), block(64 * kWavesF32Attn);
-  float *Of = (float *)O;
-  switch ((kv.d_h + 15) / 16) {
-    case 1: hipLaunchKernelGGL(k_attn_prefill_f32<1>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
-    case 2: hipLaunchKernelGGL(k_attn_prefill_f32<2>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
-    case 3: hipLaunchKernelGGL(k_attn_prefill_f32<3>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
-    case 4: hipLaunchKernelGGL(k_attn_prefill_f32<4>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
-    case 5: hipLaunchKernelGGL(k_attn_prefill_f32<5>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
-    case 6: hipLaunchKernelGGL(k_attn_prefill_f32<6>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
-    case 7: hipLaunchKernelGGL(k_attn_prefill_f32<7>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
-    default: hipLaunchKernelGGL(k_attn_prefill_f32<8>, grid, block, 0, st, Q, ldq, T, kv, seq, n_q, Of, ldo); break;
+  if (a.tp != 16) return hipErrorInvalidValue;
+  const dim3 grid(a.ntiles, a.n_q), block(64 * kWavesF32Attn);
+  switch ((a.kv.d_h + 15) / 16) {
+    case 1: hipLaunchKernelGGL(k_attn_prefill_f32<1>, grid, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL(k_attn_prefill_f32<2>, grid, block, 0, st, a); break;
+    case 3: hipLaunchKernelGGL(k_attn_prefill_f32<3>, grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL(k_attn_prefill_f32<4>, grid, block, 0, st, a); break;
+    case 5: hipLaunchKernelGGL(k_attn_prefill_f32<5>, grid, block, 0, st, a); break;
+    case 6: hipLaunchKernelGGL(k_attn_prefill_f32<6>, grid, block, 0, st, a); break;
+    case 7: hipLaunchKernelGGL(k_attn_prefill_f32<7>, grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL(k_attn_prefill_f32<8>, grid, block, 0, st, a); break;
   }
   return hipGetLastError();
 }

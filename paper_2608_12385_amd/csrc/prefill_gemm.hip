@@ -35,7 +35,7 @@ namespace dbt {
 
 namespace {
 
-constexpr int kTM = 256, kTK = 64;
+constexpr int kTM = kTileRows, kTK = 64;
 
 __device__ __forceinline__ int swz(int row, int c) { return (c ^ (row & 7)) * 8; }
 
@@ -198,11 +198,12 @@ __global__ __launch_bounds__(512) void k_gemm_tile(TileGemm g) {
   for (int b = 0; b < 4; ++b) {
     const int m = m0 + 64 * wm + 16 * b + r;
     if (m >= g.M) continue;
+    const int kept_row = GLU || QKV ? g.ret.row(m) : -1;
     if (QKV) {
       // tile n0 is Q head n0/128, then K heads, then V heads
       const int dq = g.rows[0], dkv = g.rows[1];
-      const int pos = m;
-      const size_t page = (size_t)g.kv.page_table[(size_t)g.seq * g.kv.mpps + pos / 16];
+      const int pos = g.prompt[m].pos;
+      const size_t page = (size_t)g.kv.page_table[(size_t)g.prompt[m].seq * g.kv.mpps + pos / 16];
       const int slot = pos % 16;
 #pragma unroll
       for (int a = 0; a < NA / 2; ++a) {
@@ -225,8 +226,8 @@ __global__ __launch_bounds__(512) void k_gemm_tile(TileGemm g) {
           const int c0 = n0 + d0;
           *(float4 *)(g.Qout + (size_t)m * dq + c0) = float4{x0[0], x0[1], x0[2], x0[3]};
           *(float4 *)(g.Qout + (size_t)m * dq + c0 + 64) = float4{x1[0], x1[1], x1[2], x1[3]};
-          if (g.ret && (g.ret_src < 0 || m == g.ret_src)) {
-            float *kept = g.ret + (size_t)(g.ret_src < 0 ? m : g.ret_dst) * dq + c0;
+          if (kept_row >= 0) {
+            float *kept = g.ret.ptr + (size_t)kept_row * dq + c0;
             *(float4 *)kept = float4{x0[0], x0[1], x0[2], x0[3]};
             *(float4 *)(kept + 64) = float4{x1[0], x1[1], x1[2], x1[3]};
           }
@@ -246,8 +247,6 @@ __global__ __launch_bounds__(512) void k_gemm_tile(TileGemm g) {
         }
       }
     } else if (GLU) {
-      const bool keep = g.ret && (g.ret_src < 0 || m == g.ret_src);
-      const int kept_row = g.ret_src < 0 ? m : g.ret_dst;
 #pragma unroll
       for (int a = 0; a < NA / 2; ++a) {
         const int j = n0 + (BN / 4) * wn + 16 * a + 4 * gq;
@@ -263,7 +262,7 @@ __global__ __launch_bounds__(512) void k_gemm_tile(TileGemm g) {
         }
         *(u32x2 *)(g.H + (size_t)m * g.ldh + j) =
             u32x2{(uint32_t)f2bf(h[0]) | ((uint32_t)f2bf(h[1]) << 16), (uint32_t)f2bf(h[2]) | ((uint32_t)f2bf(h[3]) << 16)};
-        if (keep) *(float4 *)(g.ret + (size_t)kept_row * g.N + j) = float4{h[0], h[1], h[2], h[3]};
+        if (kept_row >= 0) *(float4 *)(g.ret.ptr + (size_t)kept_row * g.N + j) = float4{h[0], h[1], h[2], h[3]};
       }
     } else {
 #pragma unroll
@@ -287,7 +286,7 @@ bool gemm_tile_args_ok(const TileGemm &g, bool glu) {
   if (!glu && (g.rows[0] % 8 != 0 || g.rows[1] % 8 != 0 || g.rows[0] + g.rows[1] + g.rows[2] != g.N)) return false;
   // the QKV epilogue: heads of 128 dimensions, Q then K then V (as many V as K heads)
   if (g.rope && (g.kv.d_h != 128 || g.rows[0] % 128 != 0 || g.rows[1] != g.kv.n_kv * 128 || g.rows[2] != g.rows[1] ||
-                 !g.Qout || !g.kv.k || !g.kv.v || !g.kv.page_table))
+                 !g.Qout || !g.prompt || !g.kv.k || !g.kv.v || !g.kv.page_table))
     return false;
   // 32-bit element offsets
   return (long long)g.M * g.ldx < (1LL << 32) && (long long)g.N * g.K < (1LL << 32);

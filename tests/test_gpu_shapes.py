@@ -10,6 +10,7 @@ from tests.gpu_util import check_readout, make_session, row_err, to_np
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
+BF16_TOL = 2e-2
 F32_TOL = 1e-5    # fp32 bar of the parity tests (a 1024-term fp32 sum: ~32 x 6e-8 typical)
 
 
@@ -104,3 +105,21 @@ def test_kv_fill_edges(dtype, dh, nkv, start, count, off):
     for pool, w in ((sess.k_pages, want[0]), (sess.v_pages, want[1])):
         assert torch.equal(pool.view(wt).view(w.shape), w)
     sess.close()
+
+
+# packed prompt passes in bf16 on both sides of one and two 128-row blocks of
+# the streaming projections and of the tiled ones' 256 rows, prompts shorter
+# than a page, longer than an attention tile, tiles of unequal prompts
+@pytest.mark.parametrize("lens", [[1], [100, 27], [100, 1, 28], [200, 54, 1], [200, 55, 1], [3, 300, 16, 65, 129]])
+def test_bf16_packed_prompts(lens):
+    shape = synth.ModelShape(n_layers=2, d_model=256, n_q_heads=4, n_kv_heads=1, head_dim=128, d_ff=384, vocab=512,
+                             dtype="bf16", has_embeddings=True, std=0.05, coupling_std=0.5)
+    prompts_and_steps(shape, lens, BF16_TOL)
+
+
+# more sequences than one pass takes (128), and more rows (8192)
+@pytest.mark.parametrize("lens", [[1 + i % 3 for i in range(131)], [900 + 31 * i for i in range(9)]])
+def test_f32_several_prompt_passes(lens):
+    shape = synth.ModelShape(n_layers=1, d_model=32, n_q_heads=2, n_kv_heads=1, head_dim=16, d_ff=40, vocab=64,
+                             dtype="f32", has_embeddings=True, std=0.2, coupling_std=0.5)
+    prompts_and_steps(shape, lens, F32_TOL, steps=1)
