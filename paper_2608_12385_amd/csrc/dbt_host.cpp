@@ -474,6 +474,7 @@ struct LayerCall {
   // kernel before it) when set; sb is then applied by its QKV projection
   const HIn *hin;
   const StepBegin *sb;
+  HOut ho;  // where the last layer leaves the states (see HOut)
 };
 
 // Whether the decode step's attention kernel finishes the QKV projection
@@ -515,8 +516,6 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
   const PromptRow *map = c.prefill ? m->at<PromptRow>(L.prow) : nullptr;
   const dbt_layer_weights &W = m->layers[l];
   const int d = cf.d_model, fs = L.fs;
-  const int xrow0 = c.rows.p0 * c.rows.Bp;
-  const int M = c.rows.np * c.rows.Bp;
   const size_t es = esize(cf);
   float *P = m->at<float>(L.P), *S = m->at<float>(L.S);
   const size_t rq = (size_t)l * L.Bp_max;
@@ -677,6 +676,7 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
   cb.ret = Retain{c.retain ? ret_m : nullptr, map};
   cb.gG = cm ? W.g_shared_copy : nullptr;
   cb.S = S;
+  if (l + 1 == cf.n_layers) cb.ho = c.ho;
   cb.g_next = g_next;
   cb.eps = cf.rms_eps;
   cb.Xn = m->p(L.Xn);
@@ -935,7 +935,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
   else if (cf.vocab > 0 && c.last_norm) g_next = m->w.final_norm;
   HIPCHK(launch_down_finish(P, stride, S_d, d, d, c.mode, c.rows, W.c, ret_m,
                             Retain{c.retain ? ret_m : nullptr, map}, S, g_next, cf.rms_eps,
-                            cf.dtype, Xn, d, st));
+                            cf.dtype, Xn, d, st, l + 1 == cf.n_layers ? c.ho : HOut{}));
   return DBT_OK;
 }
 
@@ -957,26 +957,82 @@ dbt_status load_inputs(dbt_model *m, dbt_kv *kv, const dbt_step_in *in, const in
   return DBT_OK;
 }
 
+// Where a call leaves its logits and states.  An output array takes them
+// straight from the kernel that computes them when it is 16-byte aligned;
+// otherwise (or with no array) they go to the workspace, and the array is
+// filled by a copy at the end of the call.
+struct Sinks {
+  const float *z[4];  // logits of path j, row b at z[j] + b*V
+  bool copy_z1, copy_z2, copy_h1, copy_h2;
+  HOut ho;
+};
+
+bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+  return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
+// direct1 / direct2: whether the primary's / the branches' outputs may leave
+// the call early (every later read of the call is of other memory).
+Sinks make_sinks(const dbt_model *m, int B, int Bp, const dbt_step_out *out, bool direct1, bool direct2) {
+  const dbt_config &cf = m->cfg;
+  const int nb = n_branches(cf);
+  const size_t V = cf.vocab, zrow = (size_t)B * V * 4, hrow = (size_t)B * cf.d_model * 4;
+  Sinks k{};
+  for (int j = 0; j <= nb; ++j) k.z[j] = m->at<float>(m->L.logits) + (size_t)j * Bp * V;
+  if (!out) return k;
+  auto fits = [](const void *p) { return p && (uintptr_t)p % 16 == 0; };
+  const bool zapart = !overlap(out->logits1, zrow, out->logits2, zrow * nb);
+  const bool hapart = !overlap(out->h1_out, hrow, out->h2_out, hrow * nb);
+  k.copy_z1 = V > 0 && out->logits1;
+  k.copy_z2 = V > 0 && out->logits2;
+  k.copy_h1 = out->h1_out != nullptr;
+  k.copy_h2 = out->h2_out != nullptr;
+  k.ho.B = B;
+  if (k.copy_z1 && direct1 && zapart && fits(out->logits1)) {
+    k.z[0] = out->logits1;
+    k.copy_z1 = false;
+  }
+  if (k.copy_z2 && direct2 && zapart && fits(out->logits2)) {
+    for (int j = 0; j < nb; ++j) k.z[1 + j] = out->logits2 + (size_t)j * B * V;
+    k.copy_z2 = false;
+  }
+  if (k.copy_h1 && direct1 && hapart && fits(out->h1_out)) {
+    k.ho.h1 = out->h1_out;
+    k.copy_h1 = false;
+  }
+  if (k.copy_h2 && direct2 && hapart && fits(out->h2_out)) {
+    k.ho.h2 = out->h2_out;
+    k.copy_h2 = false;
+  }
+  return k;
+}
+
 // Final norm is already in Xn (applied by the last layer); output matrix for the active rows.
-dbt_status lm_head(dbt_model *m, Rows rows, hipStream_t st) {
+dbt_status lm_head(dbt_model *m, Rows rows, const Sinks &k, hipStream_t st) {
   const dbt_config &cf = m->cfg;
   const Layout &L = m->L;
   const int xrow0 = rows.p0 * rows.Bp;
   WSegs lm{{m->w.lm_head, nullptr, nullptr}, {cf.vocab, 0, 0}};
+  YRows yr{};
+  for (int j = 0; j < rows.np; ++j) yr.p[j] = const_cast<float *>(k.z[rows.p0 + j]);
+  yr.Bp = rows.Bp;
+  yr.B = rows.B;
   Timed tm(m, DBT_STAGE_LMHEAD, st);
   const bool fused = gemm_stats_tiles(cf.vocab, L.g_lm, cf.dtype) > 0;
   HIPCHK(launch_gemm(lm, cf.vocab, cf.d_model, cf.dtype, m->p(L.Xn) + (size_t)xrow0 * cf.d_model * esize(cf),
-                     cf.d_model, rows.np * rows.Bp, m->at<float>(L.logits) + (size_t)xrow0 * cf.vocab, cf.vocab,
-                     0, L.g_lm, st, fused ? m->at<float>(L.mstats) + (size_t)xrow0 * L.nstat * 3 : nullptr));
+                     cf.d_model, rows.np * rows.Bp, nullptr, cf.vocab, 0, L.g_lm, st,
+                     fused ? m->at<float>(L.mstats) + (size_t)xrow0 * L.nstat * 3 : nullptr, &yr));
   return DBT_OK;
 }
 
-dbt_status readout(dbt_model *m, int B, int Bp, bool branch, dbt_step_out *out, hipStream_t st) {
+// Mixture readout from the logits at k, and the copies of those the
+// projection did not write in place.
+dbt_status readout(dbt_model *m, int B, int Bp, bool branch, dbt_step_out *out, const Sinks &k, hipStream_t st) {
   const dbt_config &cf = m->cfg;
   const Layout &L = m->L;
   if (cf.vocab <= 0) return DBT_OK;
   MixArgs mx{};
-  mx.logits = m->at<float>(L.logits);
+  for (int j = 0; j < 4; ++j) mx.z[j] = k.z[j];
   mx.V = cf.vocab;
   const int nb = n_branches(cf);
   mx.rows = Rows{B, Bp, 0, branch ? 1 + nb : 1};
@@ -991,18 +1047,17 @@ dbt_status readout(dbt_model *m, int B, int Bp, bool branch, dbt_step_out *out, 
     Timed tm(m, DBT_STAGE_MIX, st);
     HIPCHK(launch_mixture(mx, st));
   }
-  if (out && out->logits1)
-    HIPCHK(hipMemcpyAsync(out->logits1, m->at<float>(L.logits), (size_t)B * cf.vocab * 4, hipMemcpyDeviceToDevice, st));
-  if (out && out->logits2 && branch)
+  if (k.copy_z1)
+    HIPCHK(hipMemcpyAsync(out->logits1, k.z[0], (size_t)B * cf.vocab * 4, hipMemcpyDeviceToDevice, st));
+  if (k.copy_z2 && branch)
     for (int j = 0; j < nb; ++j)
-      HIPCHK(hipMemcpyAsync(out->logits2 + (size_t)j * B * cf.vocab, m->at<float>(L.logits) + (size_t)(1 + j) * Bp * cf.vocab,
-                            (size_t)B * cf.vocab * 4, hipMemcpyDeviceToDevice, st));
+      HIPCHK(hipMemcpyAsync(out->logits2 + (size_t)j * B * cf.vocab, k.z[1 + j], (size_t)B * cf.vocab * 4,
+                            hipMemcpyDeviceToDevice, st));
   return DBT_OK;
 }
 
 // Final residual states of the branches: [n_branches][B][d].
 dbt_status copy_branch_rows(dbt_model *m, float *dst, int B, int Bp, hipStream_t st) {
-  if (!dst) return DBT_OK;
   const int d = m->cfg.d_model;
   for (int j = 0; j < n_branches(m->cfg); ++j)
     HIPCHK(hipMemcpyAsync(dst + (size_t)j * B * d, m->at<float>(m->L.S) + (size_t)(1 + j) * Bp * d, (size_t)B * d * 4,
@@ -1059,10 +1114,11 @@ dbt_status copy_rows(float *dst, const float *src, int B, int d, hipStream_t st)
 }
 
 // Branch-only pass over all layers (ungrouped pass 2 and the boundary).
-dbt_status branch_pass(dbt_model *m, dbt_kv *kv, int B, int Bp, hipStream_t st, const dbt_step_out *out = nullptr,
-                       const HIn *hin = nullptr) {
+dbt_status branch_pass(dbt_model *m, dbt_kv *kv, int B, int Bp, const Sinks &k, hipStream_t st,
+                       const dbt_step_out *out = nullptr, const HIn *hin = nullptr) {
   LayerCall lc{};
   lc.out = out;
+  lc.ho = k.ho;
   lc.hin = hin;
   const int nb = n_branches(m->cfg);
   lc.rows = Rows{B, Bp, 1, nb};
@@ -1075,7 +1131,7 @@ dbt_status branch_pass(dbt_model *m, dbt_kv *kv, int B, int Bp, hipStream_t st, 
     dbt_status s = run_layer(m, kv, l, lc, st);
     if (s) return s;
   }
-  if (m->cfg.vocab > 0) return lm_head(m, lc.rows, st);
+  if (m->cfg.vocab > 0) return lm_head(m, lc.rows, k, st);
   return DBT_OK;
 }
 
@@ -1111,14 +1167,17 @@ dbt_status decode_step_impl(dbt_model *m, dbt_kv *kv, const dbt_step_in *in, int
   lc.rows_layout = (1 + nb) * Bp;
   lc.last_norm = true;
   lc.out = out;
+  // (the last layer is the first to write an output, after every read of the inputs)
+  const Sinks k = make_sinks(m, B, Bp, out, true, on);
+  lc.ho = k.ho;
   for (int l = 0; l < cf.n_layers; ++l)
     if ((s = run_layer(m, kv, l, lc, st))) return s;
-  if (cf.vocab > 0 && (s = lm_head(m, rows, st))) return s;
+  if (cf.vocab > 0 && (s = lm_head(m, rows, k, st))) return s;
   for (int b = 0; b < B; ++b) kv->len[b] += 1;
   if (out) {
-    if ((s = readout(m, B, Bp, on, out, st))) return s;
-    if ((s = copy_rows(out->h1_out, m->at<float>(m->L.S), B, cf.d_model, st))) return s;
-    if (on && (s = copy_branch_rows(m, out->h2_out, B, Bp, st))) return s;
+    if ((s = readout(m, B, Bp, on, out, k, st))) return s;
+    if (k.copy_h1 && (s = copy_rows(out->h1_out, m->at<float>(m->L.S), B, cf.d_model, st))) return s;
+    if (on && k.copy_h2 && (s = copy_branch_rows(m, out->h2_out, B, Bp, st))) return s;
   }
   return DBT_OK;
 }
@@ -1323,18 +1382,41 @@ dbt_status dbt_decode_step_ungrouped(dbt_model *m, dbt_kv *kv, const dbt_step_in
   lc.rows_layout = (1 + n_branches(cf)) * Bp;
   lc.last_norm = true;
   lc.out = out;
+  // (the second pass reads inputs: the primary's outputs are copied at the end)
+  const Sinks k = make_sinks(m, B, Bp, out, false, true);
   for (int l = 0; l < cf.n_layers; ++l)
     if ((s = run_layer(m, kv, l, lc, st))) return s;
-  if (cf.vocab > 0 && (s = lm_head(m, prim, st))) return s;
+  if (cf.vocab > 0 && (s = lm_head(m, prim, k, st))) return s;
   // pass 2: every branch layer
   const Rows br{B, Bp, 1, n_branches(cf)};
   if (!fold && (s = load_inputs(m, kv, in, in->tokens, br, st))) return s;
-  if ((s = branch_pass(m, kv, B, Bp, st, out, fold ? &hin : nullptr))) return s;
+  if ((s = branch_pass(m, kv, B, Bp, k, st, out, fold ? &hin : nullptr))) return s;
   for (int b = 0; b < B; ++b) kv->len[b] += 1;
   if (out) {
-    if ((s = readout(m, B, Bp, true, out, st))) return s;
-    if ((s = copy_rows(out->h1_out, m->at<float>(m->L.S), B, cf.d_model, st))) return s;
-    if ((s = copy_branch_rows(m, out->h2_out, B, Bp, st))) return s;
+    if ((s = readout(m, B, Bp, true, out, k, st))) return s;
+    if (k.copy_h1 && (s = copy_rows(out->h1_out, m->at<float>(m->L.S), B, cf.d_model, st))) return s;
+    if (k.copy_h2 && (s = copy_branch_rows(m, out->h2_out, B, Bp, st))) return s;
+  }
+  return DBT_OK;
+}
+
+// The boundary after a prefill whose primary logits and states are at k.
+static dbt_status boundary_impl(dbt_model *m, dbt_kv *kv, int B, dbt_step_out *out, const Sinks &k, hipStream_t st) {
+  dbt_status s;
+  const dbt_config &cf = m->cfg;
+  const Layout &L = m->L;
+  const int Bp = round16(B);
+  std::vector<int> pos(B);
+  for (int b = 0; b < B; ++b) pos[b] = kv->len[b] - 1;
+  if ((s = flush(kv, pos.data(), B, st))) return s;
+  const Rows br{B, Bp, 1, n_branches(cf)};
+  HIPCHK(launch_embed(m->at<int>(L.btok), cf.vocab, m->w.emb1, m->w.emb2, m->w.emb_norm, m->layers[0].attn_norm, cf.rms_eps,
+                      cf.d_model, cf.dtype, br, m->at<float>(L.S), m->p(L.Xn), cf.d_model, st));
+  if ((s = branch_pass(m, kv, B, Bp, k, st))) return s;
+  m->bnd_kv = nullptr;
+  if (out) {
+    if ((s = readout(m, B, Bp, true, out, k, st))) return s;
+    if (k.copy_h2 && (s = copy_branch_rows(m, out->h2_out, B, Bp, st))) return s;
   }
   return DBT_OK;
 }
@@ -1370,6 +1452,7 @@ dbt_status dbt_prefill(dbt_model *m, dbt_kv *kv, const int32_t *tokens, const in
   const Layout &L = m->L;
   const int d = cf.d_model;
   const int Bp = round16(batch);
+  const Sinks k = make_sinks(m, batch, Bp, out, run_boundary != 0, true);
   // Packed passes over consecutive prompts: as few as the rows of the prompt
   // buffers allow, of about equal size.
   const Layout &Lp = m->Lp;
@@ -1405,22 +1488,22 @@ dbt_status dbt_prefill(dbt_model *m, dbt_kv *kv, const int32_t *tokens, const in
     lc.last_norm = false;
     for (int l = 0; l < cf.n_layers; ++l)
       if ((s = run_layer(m, kv, l, lc, st))) return s;
-    HIPCHK(launch_prompt_last(pk, m->at<float>(Lp.S), tokens + off, d, m->at<float>(L.slast), m->at<int>(L.btok), st));
+    HIPCHK(launch_prompt_last(pk, m->at<float>(Lp.S), tokens + off, d, m->at<float>(L.slast), k.ho.h1,
+                              m->at<int>(L.btok), st));
     off += T;
   }
-  // primary logits at each prompt's final position
+  // primary logits at each prompt's final position (kept in the workspace
+  // for a boundary call of its own)
   if (cf.vocab > 0) {
     HIPCHK(launch_rmsnorm_rows(m->at<float>(L.slast), m->w.final_norm, cf.rms_eps, d, cf.dtype, Rows{batch, 0, 0, 1},
                                m->p(L.Xn), d, st));
-    if ((s = lm_head(m, Rows{batch, Bp, 0, 1}, st))) return s;
+    if ((s = lm_head(m, Rows{batch, Bp, 0, 1}, k, st))) return s;
   }
-  if (out) {
-    if ((s = copy_rows(out->h1_out, m->at<float>(L.slast), batch, d, st))) return s;
-  }
+  if (k.copy_h1 && (s = copy_rows(out->h1_out, m->at<float>(L.slast), batch, d, st))) return s;
   m->bnd_kv = kv;
   m->bnd_batch = batch;
-  if (run_boundary) return dbt_boundary(m, kv, batch, out, stream);
-  if (out && (s = readout(m, batch, Bp, false, out, st))) return s;
+  if (run_boundary) return boundary_impl(m, kv, batch, out, k, st);
+  if (out && (s = readout(m, batch, Bp, false, out, k, st))) return s;
   return DBT_OK;
 }
 
@@ -1430,23 +1513,8 @@ dbt_status dbt_boundary(dbt_model *m, dbt_kv *kv, int32_t batch, dbt_step_out *o
   if (m->bnd_kv != kv || batch != m->bnd_batch)
     return fail(DBT_ERR_STATE, "boundary must directly follow dbt_prefill on the same cache and batch");
   hipStream_t st = (hipStream_t)stream;
-  const dbt_config &cf = m->cfg;
-  const Layout &L = m->L;
-  const int B = batch, Bp = round16(B);
   if ((s = ensure_device(m, st))) return s;
-  std::vector<int> pos(B);
-  for (int b = 0; b < B; ++b) pos[b] = kv->len[b] - 1;
-  if ((s = flush(kv, pos.data(), B, st))) return s;
-  const Rows br{B, Bp, 1, n_branches(cf)};
-  HIPCHK(launch_embed(m->at<int>(L.btok), cf.vocab, m->w.emb1, m->w.emb2, m->w.emb_norm, m->layers[0].attn_norm, cf.rms_eps,
-                      cf.d_model, cf.dtype, br, m->at<float>(L.S), m->p(L.Xn), cf.d_model, st));
-  if ((s = branch_pass(m, kv, B, Bp, st))) return s;
-  m->bnd_kv = nullptr;
-  if (out) {
-    if ((s = readout(m, B, Bp, true, out, st))) return s;
-    if ((s = copy_branch_rows(m, out->h2_out, B, Bp, st))) return s;
-  }
-  return DBT_OK;
+  return boundary_impl(m, kv, batch, out, make_sinks(m, batch, round16(batch), out, false, true), st);
 }
 
 dbt_status dbt_stage_timing(dbt_model *m, int32_t stage, int32_t enable) {

@@ -64,10 +64,13 @@ __global__ __launch_bounds__(256) void k_prompt_plan(Pack pk, int tp, PromptRow 
   ((int4 *)tiles)[rank] = make_int4(pk.off[s], j * tp, pk.off[s + 1] - pk.off[s], pk.seq0 + s);
 }
 
-__global__ void k_prompt_last(Pack pk, const float *S, const int *tokens, int d, float *slast, int *btok) {
+__global__ void k_prompt_last(Pack pk, const float *S, const int *tokens, int d, float *slast, float *hout, int *btok) {
   const int i = blockIdx.x, row = pk.off[i + 1] - 1, seq = pk.seq0 + i;
-  for (int j = threadIdx.x; j < d / 4; j += blockDim.x)
-    ((float4 *)(slast + (size_t)seq * d))[j] = ((const float4 *)(S + (size_t)row * d))[j];
+  for (int j = threadIdx.x; j < d / 4; j += blockDim.x) {
+    const float4 v = ((const float4 *)(S + (size_t)row * d))[j];
+    ((float4 *)(slast + (size_t)seq * d))[j] = v;
+    if (hout) ((float4 *)(hout + (size_t)seq * d))[j] = v;
+  }
   if (threadIdx.x == 0) btok[seq] = tokens[row];
 }
 
@@ -414,7 +417,8 @@ __global__ void k_swiglu_finish(const float *part, long long stride, int S, int 
 template <typename T, int R, bool ONE = false>
 __global__ void k_down_finish(const float *part, long long stride, int S, int ldp, int d, int mode,
                               Rows rows, const float *cvec, const float *M1_in, Retain ret,
-                              float *Sres, const float *g_next, float eps, T *Xn, int ldx) {
+                              float *Sres, const float *g_next, float eps, T *Xn, int ldx,
+                              HOut ho) {
   __shared__ float red[16];
   // one workgroup per (sequence, path); a branch row sums the primary's
   // slabs itself (the same additions, so the same M1 bits) for its coupling
@@ -426,6 +430,7 @@ __global__ void k_down_finish(const float *part, long long stride, int S, int ld
   const int kept_row = path == 0 ? ret.row(b) : -1;
   const bool keep = kept_row >= 0;
   float4 *kept = keep ? (float4 *)(ret.ptr + (size_t)kept_row * d) : nullptr;
+  float4 *sout = ho.row(path, b, d, s);
   float4 v[R], gv[R];
 #pragma unroll
   for (int k = 0; k < R; ++k) {
@@ -465,7 +470,7 @@ __global__ void k_down_finish(const float *part, long long stride, int S, int ld
       const float4 t = make_float4(m2.x + c.x * m1.x, m2.y + c.y * m1.y, m2.z + c.z * m1.z, m2.w + c.w * m1.w);
       v[k] = add4(x, t);
     }
-    s[i] = v[k];
+    sout[i] = v[k];
   }
   if (!g_next) return;
   if constexpr (R <= 2)
@@ -538,7 +543,7 @@ __global__ void k_mix_stats(MixArgs m) {
   const int row = phys_row(m.rows, path, b);
   const int nch = m.nstat;
   const int lo = c * m.chunk, hi = min(m.V, lo + m.chunk);
-  const float *z = m.logits + (size_t)row * m.V;
+  const float *z = m.z[path] + (size_t)b * m.V;
   // each thread keeps its values in registers between the two passes
   constexpr int PER = 16;
   float v[PER];
@@ -609,7 +614,7 @@ __global__ __launch_bounds__(256) void k_mix_select(MixArgs m) {
 #pragma unroll
   for (int j = 0; j < NP; ++j) {
     st[j] = m.stats + (size_t)(j * m.rows.Bp + b) * m.nstat * 3;
-    z[j] = m.logits + (size_t)(j * m.rows.Bp + b) * m.V;
+    z[j] = m.z[j] + (size_t)b * m.V;
   }
   // 1. lse and sum p^2: each thread merges its tiles t + 256k online, then
   //    the workgroup merges the threads (fixed tree); the maxima of the last
@@ -805,9 +810,9 @@ hipError_t launch_prompt_plan(const Pack &pk, int tp, PromptRow *rows, PromptTil
   return hipGetLastError();
 }
 
-hipError_t launch_prompt_last(const Pack &pk, const float *S, const int *tokens, int d, float *slast, int *btok,
-                              hipStream_t st) {
-  hipLaunchKernelGGL(k_prompt_last, dim3(pk.n), dim3(256), 0, st, pk, S, tokens, d, slast, btok);
+hipError_t launch_prompt_last(const Pack &pk, const float *S, const int *tokens, int d, float *slast, float *hout,
+                              int *btok, hipStream_t st) {
+  hipLaunchKernelGGL(k_prompt_last, dim3(pk.n), dim3(256), 0, st, pk, S, tokens, d, slast, hout, btok);
   return hipGetLastError();
 }
 
@@ -935,17 +940,18 @@ hipError_t launch_swiglu_finish(const float *part, long long stride, int S, int 
 
 hipError_t launch_down_finish(const float *part, long long stride, int S, int ldp, int d, int mode,
                               Rows rows, const float *cvec, const float *M1_in, Retain ret, float *Sres,
-                              const float *g_next, float eps, int dtype, void *Xn, int ldx, hipStream_t st) {
+                              const float *g_next, float eps, int dtype, void *Xn, int ldx, hipStream_t st,
+                              const HOut &ho) {
   dim3 grid(rows.B, rows.np);
   if (dtype == 1 && S == 1) {
     DBT_ROW_LAUNCH_ONE(k_down_finish, uint16_t, d, grid, dim3(row_threads(d)), 0, st, part, stride, S, ldp, d, mode,
-                       rows, cvec, M1_in, ret, Sres, g_next, eps, (uint16_t *)Xn, ldx)
+                       rows, cvec, M1_in, ret, Sres, g_next, eps, (uint16_t *)Xn, ldx, ho)
   } else if (dtype == 1) {
     DBT_ROW_LAUNCH(k_down_finish, uint16_t, d, grid, dim3(row_threads(d)), 0, st, part, stride, S, ldp, d, mode, rows,
-                   cvec, M1_in, ret, Sres, g_next, eps, (uint16_t *)Xn, ldx)
+                   cvec, M1_in, ret, Sres, g_next, eps, (uint16_t *)Xn, ldx, ho)
   } else {
     DBT_ROW_LAUNCH(k_down_finish, float, d, grid, dim3(row_threads(d)), 0, st, part, stride, S, ldp, d, mode, rows,
-                   cvec, M1_in, ret, Sres, g_next, eps, (float *)Xn, ldx)
+                   cvec, M1_in, ret, Sres, g_next, eps, (float *)Xn, ldx, ho)
   }
   return hipGetLastError();
 }
@@ -981,7 +987,8 @@ hipError_t launch_mixture(const MixArgs &m, hipStream_t st) {
   // float4 units when rows are 16-byte aligned and units stay inside tiles;
   // the primary alone keeps scalar loads (its scan reads about one tile, and
   // the wider loop's code costs more than it saves there)
-  const bool v4 = m.rows.np > 1 && m.V % 4 == 0 && m.tile_w % 4 == 0;
+  bool v4 = m.rows.np > 1 && m.V % 4 == 0 && m.tile_w % 4 == 0;
+  for (int j = 0; j < m.rows.np; ++j) v4 = v4 && (uintptr_t)m.z[j] % 16 == 0;
   switch (m.rows.np * 2 + (v4 ? 1 : 0)) {
     case 2: hipLaunchKernelGGL((k_mix_select<1, 1>), grid, block, 0, st, m); break;
     case 4: hipLaunchKernelGGL((k_mix_select<2, 1>), grid, block, 0, st, m); break;

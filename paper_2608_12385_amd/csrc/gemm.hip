@@ -85,7 +85,7 @@ template <int MB, int RB, int PD, int NW, bool GLU = false, int XA = 2, bool XF 
 __global__ __launch_bounds__(NW * 64) void k_gemm_bf16(WSegs segs, int K, const uint16_t *__restrict__ X, int ldx,
                                                        int M, float *__restrict__ Y, int ldy,
                                                        long long y_split_stride, float *__restrict__ row_stats,
-                                                       GluEpi ep, XArg<XF> xa) {
+                                                       GluEpi ep, XArg<XF> xa, YRows yr) {
   constexpr int XR = 16 * MB;
   constexpr int PIECES = XR * (kChunk / 8);  // 16-byte pieces of one activation chunk
   constexpr int PPT = (PIECES + NW * 64 - 1) / (NW * 64);
@@ -437,6 +437,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_bf16(WSegs segs, int K, const 
   // rows x 64 bytes; the tile goes through LDS first (rows padded by four
   // floats, so the 16 rows of one accumulator write fall in distinct banks).
   float *Ys = Y + (long long)split * y_split_stride;
+  const bool mapped = yr.Bp != 0;  // rows go to the arrays of YRows (no split)
   if constexpr (RB >= 2) {
     // per wave: 16 rows x RB*16 columns at a time, in its own LDS region
     constexpr int WC = RB * 16, PITCH = WC + 4, LPR = WC / 4;  // columns, pitch, lanes per row
@@ -452,7 +453,10 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_bf16(WSegs segs, int K, const 
         const int row = j * (64 / LPR) + lane / LPR, col = (lane % LPR) * 4;
         const int m = m0 + cb * 16 + row;
         const floatx4 v = *(const floatx4 *)&ost[row * PITCH + col];
-        if (m < M && rvalid[col >> 4]) *(floatx4 *)(Ys + (size_t)m * ldy + ny + col) = v;
+        bool live = true;
+        float *y = Ys + (size_t)m * ldy;
+        if (mapped) y = yr.row(m, ldy, live);
+        if (m < M && live && rvalid[col >> 4]) *(floatx4 *)(y + ny + col) = v;
       }
       wave_lds_fence();
     }
@@ -469,8 +473,11 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_bf16(WSegs segs, int K, const 
     for (int e = t; e < XR * TPR; e += NW * 64) {
       const int row = e / TPR, col = (e % TPR) * 4;
       const int m = m0 + row;
-      if (m < M && nloc + col < segrows)
-        *(floatx4 *)(Ys + (size_t)m * ldy + nt0 + col) = *(const floatx4 *)&ost[row * PITCH + col];
+      bool live = true;
+      float *y = Ys + (size_t)m * ldy;
+      if (mapped) y = yr.row(m, ldy, live);
+      if (m < M && live && nloc + col < segrows)
+        *(floatx4 *)(y + nt0 + col) = *(const floatx4 *)&ost[row * PITCH + col];
     }
   }
 }
@@ -496,7 +503,8 @@ constexpr int kWavesF32 = 8;
 
 template <int MB>
 __global__ __launch_bounds__(64 * kWavesF32) void k_gemm_f32(WSegs segs, int N, int K, const float *__restrict__ X,
-                                                             int ldx, int M, float *__restrict__ Y, int ldy) {
+                                                             int ldx, int M, float *__restrict__ Y, int ldy,
+                                                             YRows yr) {
   constexpr int XR = 16 * MB, PITCH = 20;  // floats per staged output row (16-byte rows, four-bank steps)
   __shared__ float red[kWavesF32][XR][PITCH];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -573,7 +581,10 @@ __global__ __launch_bounds__(64 * kWavesF32) void k_gemm_f32(WSegs segs, int N, 
     float s = 0.f;
 #pragma unroll
     for (int w = 0; w < kWavesF32; ++w) s += red[w][m][n];
-    if (m0 + m < M && n0 + n < N) Y[(size_t)(m0 + m) * ldy + n0 + n] = s;
+    bool live = true;
+    float *y = Y + (size_t)(m0 + m) * ldy;
+    if (yr.Bp != 0) y = yr.row(m0 + m, ldy, live);
+    if (m0 + m < M && live && n0 + n < N) y[n0 + n] = s;
   }
 }
 
@@ -628,25 +639,25 @@ GemmConfig gemm_config(int n_full, int K, int dtype, int seg_gran, int max_rows)
 namespace {
 template <int MB>
 void launch_mb(const GemmConfig &g, dim3 grid, hipStream_t st, const WSegs &segs, int K, const uint16_t *X, int ldx,
-               int M, float *Y, int ldy, long long yss, float *rs) {
+               int M, float *Y, int ldy, long long yss, float *rs, const YRows &yr) {
   const GluEpi none{};
   if (g.NW == 16)
-    hipLaunchKernelGGL((k_gemm_bf16<MB, 2, 1, 16>), grid, dim3(1024), 0, st, segs, K, X, ldx, M, Y, ldy, yss, rs, none, NoX{});
+    hipLaunchKernelGGL((k_gemm_bf16<MB, 2, 1, 16>), grid, dim3(1024), 0, st, segs, K, X, ldx, M, Y, ldy, yss, rs, none, NoX{}, yr);
   else if (g.NW == 8 && g.RB == 2)
-    hipLaunchKernelGGL((k_gemm_bf16<MB, 2, 1, 8>), grid, dim3(512), 0, st, segs, K, X, ldx, M, Y, ldy, yss, rs, none, NoX{});
+    hipLaunchKernelGGL((k_gemm_bf16<MB, 2, 1, 8>), grid, dim3(512), 0, st, segs, K, X, ldx, M, Y, ldy, yss, rs, none, NoX{}, yr);
   else if (g.NW == 8)
-    hipLaunchKernelGGL((k_gemm_bf16<MB, 1, 1, 8>), grid, dim3(512), 0, st, segs, K, X, ldx, M, Y, ldy, yss, rs, none, NoX{});
+    hipLaunchKernelGGL((k_gemm_bf16<MB, 1, 1, 8>), grid, dim3(512), 0, st, segs, K, X, ldx, M, Y, ldy, yss, rs, none, NoX{}, yr);
   else if (g.RB == 2)
-    hipLaunchKernelGGL((k_gemm_bf16<MB, 2, 2, 4>), grid, dim3(256), 0, st, segs, K, X, ldx, M, Y, ldy, yss, rs, none, NoX{});
+    hipLaunchKernelGGL((k_gemm_bf16<MB, 2, 2, 4>), grid, dim3(256), 0, st, segs, K, X, ldx, M, Y, ldy, yss, rs, none, NoX{}, yr);
   else
-    hipLaunchKernelGGL((k_gemm_bf16<MB, 1, 2, 4>), grid, dim3(256), 0, st, segs, K, X, ldx, M, Y, ldy, yss, rs, none, NoX{});
+    hipLaunchKernelGGL((k_gemm_bf16<MB, 1, 2, 4>), grid, dim3(256), 0, st, segs, K, X, ldx, M, Y, ldy, yss, rs, none, NoX{}, yr);
 }
 
 template <int MB>
 void launch_glu_mb(dim3 grid, hipStream_t st, const WSegs &segs, int K, const uint16_t *X, int ldx, int M,
                    const GluEpi &ep) {
   hipLaunchKernelGGL((k_gemm_bf16<MB, 1, 2, 8, true>), grid, dim3(512), 0, st, segs, K, X, ldx, M, nullptr, 0, 0LL,
-                     nullptr, ep, NoX{});
+                     nullptr, ep, NoX{}, YRows{});
 }
 
 template <int MB>
@@ -655,13 +666,13 @@ void launch_xnorm_mb(const GemmConfig &g, dim3 grid, hipStream_t st, const WSegs
   const GluEpi none{};
   if (g.NW == 8)
     hipLaunchKernelGGL((k_gemm_bf16<MB, 1, 1, 8, false, 2, true>), grid, dim3(512), 0, st, segs, K, nullptr, 0, M, Y,
-                       ldy, yss, nullptr, none, xn);
+                       ldy, yss, nullptr, none, xn, YRows{});
   else if (g.RB == 2)
     hipLaunchKernelGGL((k_gemm_bf16<MB, 2, 2, 4, false, 2, true>), grid, dim3(256), 0, st, segs, K, nullptr, 0, M, Y,
-                       ldy, yss, nullptr, none, xn);
+                       ldy, yss, nullptr, none, xn, YRows{});
   else
     hipLaunchKernelGGL((k_gemm_bf16<MB, 1, 2, 4, false, 2, true>), grid, dim3(256), 0, st, segs, K, nullptr, 0, M, Y,
-                       ldy, yss, nullptr, none, xn);
+                       ldy, yss, nullptr, none, xn, YRows{});
 }
 }  // namespace
 
@@ -735,8 +746,11 @@ hipError_t launch_gemm_xnorm(const WSegs &segs, int N, int K, const XNorm &xn, i
 }
 
 hipError_t launch_gemm(const WSegs &segs, int N, int K, int dtype, const void *X, int ldx, int M, float *Y,
-                       int ldy, long long y_split_stride, const GemmConfig &g, hipStream_t st, float *row_stats) {
+                       int ldy, long long y_split_stride, const GemmConfig &g, hipStream_t st, float *row_stats,
+                       const YRows *yrows) {
   if (M <= 0 || N <= 0) return hipSuccess;
+  if (yrows && (g.S != 1 || yrows->Bp < 16 || yrows->Bp % 16 || (M - 1) / yrows->Bp > 3)) return hipErrorInvalidValue;
+  const YRows yr = yrows ? *yrows : YRows{};
   if (dtype == 1) {
     const int mb_total = (M + 15) / 16;
     const int MB = mb_total >= 8 ? 8 : mb_total;
@@ -744,14 +758,14 @@ hipError_t launch_gemm(const WSegs &segs, int N, int K, int dtype, const void *X
     const uint16_t *Xb = (const uint16_t *)X;
     float *rs = g.S == 1 ? row_stats : nullptr;
     switch (MB) {
-      case 1: launch_mb<1>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs); break;
-      case 2: launch_mb<2>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs); break;
-      case 3: launch_mb<3>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs); break;
-      case 4: launch_mb<4>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs); break;
-      case 5: launch_mb<5>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs); break;
-      case 6: launch_mb<6>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs); break;
-      case 7: launch_mb<7>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs); break;
-      default: launch_mb<8>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs); break;
+      case 1: launch_mb<1>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs, yr); break;
+      case 2: launch_mb<2>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs, yr); break;
+      case 3: launch_mb<3>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs, yr); break;
+      case 4: launch_mb<4>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs, yr); break;
+      case 5: launch_mb<5>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs, yr); break;
+      case 6: launch_mb<6>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs, yr); break;
+      case 7: launch_mb<7>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs, yr); break;
+      default: launch_mb<8>(g, grid, st, segs, K, Xb, ldx, M, Y, ldy, y_split_stride, rs, yr); break;
     }
   } else {
     // as many activation rows per workgroup as still leave a workgroup for
@@ -762,9 +776,9 @@ hipError_t launch_gemm(const WSegs &segs, int N, int K, int dtype, const void *X
     const dim3 grid(nt, (mt + MB - 1) / MB), block(64 * kWavesF32);
     const float *Xf = (const float *)X;
     switch (MB) {
-      case 1: hipLaunchKernelGGL(k_gemm_f32<1>, grid, block, 0, st, segs, N, K, Xf, ldx, M, Y, ldy); break;
-      case 2: hipLaunchKernelGGL(k_gemm_f32<2>, grid, block, 0, st, segs, N, K, Xf, ldx, M, Y, ldy); break;
-      default: hipLaunchKernelGGL(k_gemm_f32<4>, grid, block, 0, st, segs, N, K, Xf, ldx, M, Y, ldy); break;
+      case 1: hipLaunchKernelGGL(k_gemm_f32<1>, grid, block, 0, st, segs, N, K, Xf, ldx, M, Y, ldy, yr); break;
+      case 2: hipLaunchKernelGGL(k_gemm_f32<2>, grid, block, 0, st, segs, N, K, Xf, ldx, M, Y, ldy, yr); break;
+      default: hipLaunchKernelGGL(k_gemm_f32<4>, grid, block, 0, st, segs, N, K, Xf, ldx, M, Y, ldy, yr); break;
     }
   }
   return hipGetLastError();

@@ -46,10 +46,10 @@ struct Pack {
 // Fills the row map of the pass and its attention tiles of tp positions,
 // longest first; returns their number through *ntiles.
 hipError_t launch_prompt_plan(const Pack &pk, int tp, PromptRow *rows, PromptTile *tiles, int *ntiles, hipStream_t st);
-// After the last layer: each prompt's final residual row to slast[seq], its
-// final token to btok[seq].
-hipError_t launch_prompt_last(const Pack &pk, const float *S, const int *tokens, int d, float *slast, int *btok,
-                              hipStream_t st);
+// After the last layer: each prompt's final residual row to slast[seq] (and
+// hout[seq] unless NULL), its final token to btok[seq].
+hipError_t launch_prompt_last(const Pack &pk, const float *S, const int *tokens, int d, float *slast, float *hout,
+                              int *btok, hipStream_t st);
 
 // Retention of primary intermediates for a later branch evaluation: row b of
 // the call is kept at retained row b, or, in a pass over prompts, at
@@ -97,9 +97,36 @@ struct GluEpi {
 bool gemm_glu_ok(int f, int M, int np, int dtype);
 hipError_t launch_gemm_glu(const uint16_t *w_gate, const uint16_t *w_up, int f, int K, const void *X, int ldx, int M,
                            const GluEpi &ep, hipStream_t st);
+// Where the rows of an unsplit projection go: row m of the call is row m % Bp
+// of p[m / Bp] (Bp a multiple of 16), rows past B are not stored.  The output
+// matrix writes its logits straight to the caller's arrays this way, one per
+// path, instead of to padded rows that are copied afterwards.  Bp = 0: not used.
+struct YRows {
+  float *p[4];
+  int Bp, B;
+#ifdef __HIPCC__
+  __device__ __forceinline__ float *row(int m, int ld, bool &live) const {
+    float *q = p[0];
+    if (m >= Bp) {
+      q = p[1];
+      m -= Bp;
+      if (m >= Bp) {
+        q = p[2];
+        m -= Bp;
+        if (m >= Bp) {
+          q = p[3];
+          m -= Bp;
+        }
+      }
+    }
+    live = m < B;
+    return q + (size_t)m * ld;
+  }
+#endif
+};
 hipError_t launch_gemm(const WSegs &segs, int N, int K, int dtype, const void *X, int ldx, int M,
                        float *Y, int ldy, long long y_split_stride, const GemmConfig &g, hipStream_t st,
-                       float *row_stats = nullptr);
+                       float *row_stats = nullptr, const YRows *yrows = nullptr);
 // Tiles per row of the statistics the output projection writes when given
 // row_stats (0: this shape does not produce them).
 int gemm_stats_tiles(int N, const GemmConfig &g, int dtype);
@@ -236,10 +263,24 @@ hipError_t launch_swiglu_finish(const float *part, long long split_stride, int S
                                 int mode, Rows rows, const float *bvec, const float *H1_in,
                                 Retain ret, int dtype, void *Xh, int ldh, hipStream_t st);
 
+// The last layer's states go straight to the caller's arrays (an entry that is
+// NULL: to Sres as in every other layer).
+struct HOut {
+  float *h1;  // [B][d]
+  float *h2;  // [n_b][B][d]
+  int B;
+#ifdef __HIPCC__
+  // row (path, b), or `s` where the path's array is not given
+  __device__ __forceinline__ float4 *row(int path, int b, int d, float4 *s) const {
+    if (path == 0) return h1 ? (float4 *)(h1 + (size_t)b * d) : s;
+    return h2 ? (float4 *)(h2 + ((size_t)(path - 1) * B + b) * d) : s;
+  }
+#endif
+};
 hipError_t launch_down_finish(const float *part, long long split_stride, int S, int ldp, int d,
                               int mode, Rows rows, const float *cvec, const float *M1_in,
                               Retain ret, float *Sres, const float *g_next, float eps, int dtype,
-                              void *Xn, int ldx, hipStream_t st);
+                              void *Xn, int ldx, hipStream_t st, const HOut &ho = HOut{});
 
 // ---- attention ----
 struct AttnArgs {
@@ -297,7 +338,7 @@ hipError_t launch_kv_fill(KVRef kv, int seq, int start, int count, const void *k
 
 // ---- mixture readout (Sec. 4.2) ----
 struct MixArgs {
-  const float *logits;  // [(1 + n_b) Bp][V]
+  const float *z[4];    // logits of path j: row b at z[j] + b*V
   int V;
   Rows rows;            // np = 1 + n_b with the branches on (n_b <= 3), 1 (primary) otherwise
   int chunk;            // vocabulary entries per statistics chunk when the projection wrote none
@@ -364,6 +405,7 @@ struct MoeCombine {
   Retain ret;          // compute-matched: keeps G1
   const float *gG;     // compute-matched variant (App. B.3): branch M2 = R2 + gG * G1; NULL otherwise
   float *S;
+  HOut ho;
   const float *g_next;
   float eps;
   void *Xn;

@@ -478,6 +478,7 @@ __global__ void k_moe_combine(MoeCombine a) {
   __syncthreads();
   float4 *s1 = (float4 *)(a.S + (size_t)r1 * d);
   float4 *s2 = (float4 *)(a.S + (size_t)r2 * d);
+  float4 *o1 = a.ho.row(0, b, d, s1), *o2 = a.ho.row(1, b, d, s2);
   const int kept_row = a.ret.row(b);
   const bool keep = kept_row >= 0;
   float4 *kept = keep ? (float4 *)(a.ret.ptr + (size_t)kept_row * d) : nullptr;
@@ -516,7 +517,7 @@ __global__ void k_moe_combine(MoeCombine a) {
       g1 = shared(r1, i);
       m1 = make_float4(r.x + g1.x, r.y + g1.y, r.z + g1.z, r.w + g1.w);
       const float4 s = s1[i];
-      s1[i] = make_float4(s.x + m1.x, s.y + m1.y, s.z + m1.z, s.w + m1.w);
+      o1[i] = make_float4(s.x + m1.x, s.y + m1.y, s.z + m1.z, s.w + m1.w);
       if (keep) kept[i] = cm ? g1 : m1;
     } else {
       m1 = g1 = ((const float4 *)(a.M1_in + (size_t)b * d))[i];
@@ -526,12 +527,12 @@ __global__ void k_moe_combine(MoeCombine a) {
       const float4 s = s2[i];
       if (cm) {  // M2 = R2 + g_G * G1
         const float4 gg = ((const float4 *)a.gG)[i];
-        s2[i] = make_float4(s.x + (r.x + gg.x * g1.x), s.y + (r.y + gg.y * g1.y), s.z + (r.z + gg.z * g1.z),
+        o2[i] = make_float4(s.x + (r.x + gg.x * g1.x), s.y + (r.y + gg.y * g1.y), s.z + (r.z + gg.z * g1.z),
                             s.w + (r.w + gg.w * g1.w));
       } else {   // M2 = R2 + shared expert of the branch + c * M1
         const float4 g2 = shared(r2, i);
         const float4 c = ((const float4 *)a.c)[i];
-        s2[i] = make_float4(s.x + ((r.x + g2.x) + c.x * m1.x), s.y + ((r.y + g2.y) + c.y * m1.y),
+        o2[i] = make_float4(s.x + ((r.x + g2.x) + c.x * m1.x), s.y + ((r.y + g2.y) + c.y * m1.y),
                             s.z + ((r.z + g2.z) + c.z * m1.z), s.w + ((r.w + g2.w) + c.w * m1.w));
       }
     }
@@ -540,7 +541,7 @@ __global__ void k_moe_combine(MoeCombine a) {
   __syncthreads();
   for (int p = 0; p < 2; ++p) {
     if ((p == 0 && !prim) || (p == 1 && !br)) continue;
-    const float *x = (const float *)(p == 0 ? s1 : s2);
+    const float *x = (const float *)(p == 0 ? o1 : o2);
     T *out = (T *)a.Xn + (size_t)(p == 0 ? r1 : r2) * a.ldx;
     float ss = 0.f;
     for (int i = threadIdx.x; i < d; i += blockDim.x) ss += x[i] * x[i];

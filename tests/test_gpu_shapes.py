@@ -123,3 +123,51 @@ def test_f32_several_prompt_passes(lens):
     shape = synth.ModelShape(n_layers=1, d_model=32, n_q_heads=2, n_kv_heads=1, head_dim=16, d_ff=40, vocab=64,
                              dtype="f32", has_embeddings=True, std=0.2, coupling_std=0.5)
     prompts_and_steps(shape, lens, F32_TOL, steps=1)
+
+
+# outputs in place and through the workspace (arrays off 16-byte boundaries,
+# overlapping, absent) hold the same bits, and nothing past them is written
+@pytest.mark.parametrize("dtype,vocab", [("bf16", 448), ("bf16", 65536 + 64), ("f32", 33)])
+@pytest.mark.parametrize("grouped", [True, False])
+def test_step_outputs_in_place_and_copied(dtype, vocab, grouped):
+    from paper_2608_12385_amd import binding
+    nb, B, d = 2, 3, 256
+    shape = synth.ModelShape(n_layers=1, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=256, vocab=vocab,
+                             dtype=dtype, has_embeddings=False, n_branches=nb, std=0.05, coupling_std=0.5)
+    sess = make_session(shape, synth.make_weights(shape), max_batch=5, max_pos=40)
+    for b in range(B):
+        sess.reserve_fill(b, *[[x[1] if x[1] is not None else x[0]] for x in synth.make_kv(shape, 0, b, 20 + b)])
+    h = torch.from_numpy(np.ascontiguousarray(synth.make_hidden(shape, B, paths=1 + nb))).cuda()
+    sizes = dict(logits1=B * vocab, logits2=nb * B * vocab, h1_out=B * d, h2_out=nb * B * d, alpha=B)
+
+    def step(off, skip=(), inplace=False):
+        buf = {n: torch.full((s + 64,), 7.0, device="cuda") for n, s in sizes.items() if n not in skip}
+        ptr = {n: t.data_ptr() + 4 * off for n, t in buf.items()}
+        h1, h2 = h[0].clone(), h[1:].clone()
+        if inplace:
+            ptr["h1_out"], ptr["h2_out"] = h1.data_ptr(), h2.data_ptr()
+        tok = torch.zeros(B, dtype=torch.int32, device="cuda")
+        out = binding.dbt_step_out(next_token=tok.data_ptr(), **ptr)
+        sin = sess.step_in(B, None, h1, h2)
+        if grouped:
+            binding.dbt_decode_step(sess.model, sess.kv, sin, 1, out, sess.stream)
+        else:
+            binding.dbt_decode_step_ungrouped(sess.model, sess.kv, sin, out, sess.stream)
+        torch.cuda.synchronize()
+        for b in range(B):
+            binding.dbt_kv_truncate(sess.kv, b, 20 + b)
+        got = {n: t[off:off + sizes[n]].clone() for n, t in buf.items()}
+        for n, t in buf.items():
+            if not (inplace and n in ("h1_out", "h2_out")):
+                assert (t[:off] == 7.0).all() and (t[off + sizes[n]:] == 7.0).all(), n
+        if inplace:
+            got["h1_out"], got["h2_out"] = h1.flatten(), h2.flatten()
+        got["next"] = tok
+        return got
+
+    want = step(0)
+    for other in (step(1), step(4), step(0, skip=("logits2", "h1_out")), step(3, skip=("logits1", "logits2")),
+                  step(0, inplace=True)):
+        for n, t in other.items():
+            assert torch.equal(t, want[n]), n
+    sess.close()
