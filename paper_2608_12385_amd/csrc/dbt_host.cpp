@@ -142,9 +142,10 @@ int prompt_splits(const GemmConfig &g, int M) { return std::max(1, g.S / ((M + 1
 // rows can need: plain outputs, or the slabs of a short pass.  fused: the
 // tiled kernel's epilogue writes no fp32 output.
 size_t prompt_part(const GemmConfig &g, int N, int K, int dtype, int rows, bool fused) {
-  const bool tiled = dtype == DBT_BF16 && (long long)N * K < (1LL << 32) && (long long)rows * K < (1LL << 32);
+  const bool tiled = dtype == DBT_BF16 && (long long)N * K < (1LL << 31) && (long long)rows * K < (1LL << 31);
   const size_t slabs = dtype == DBT_BF16 ? (size_t)std::max(g.S, 2) * std::min(rows, 128) * N : 0;
-  return std::max(slabs, tiled && fused ? (size_t)0 : (size_t)rows * N);
+  const size_t plain = (size_t)rows * N + (dtype == DBT_BF16 ? kTileSlabs : 0);
+  return std::max(slabs, tiled && fused ? (size_t)0 : plain);
 }
 
 // The workspace of a model: the state, the buffers of a call over stacked
@@ -704,8 +705,9 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
   };
   // A projection of the active rows: the 256-row tiled kernel over a whole
   // prompt, the weight-streaming kernel otherwise.
+  // S: its reduction splits.
   auto project = [&](const WSegs &segs, int N, int K, const char *X, int ldx, int rows_M, float *Y, int ldy,
-                     long long y_stride, const GemmConfig &g) -> hipError_t {
+                     long long y_stride, const GemmConfig &g, int &S) -> hipError_t {
     TileGemm tg{};
     for (int i = 0; i < 3; ++i) {
       tg.w[i] = (const uint16_t *)segs.w[i];
@@ -718,11 +720,17 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
     tg.M = rows_M;
     tg.Y = Y;
     tg.ldy = ldy;
-    if (c.prefill && cf.dtype == DBT_BF16 && gemm_tile_args_ok(tg, false)) return launch_gemm_tile(tg, false, st);
+    S = g.S;
+    if (c.prefill && cf.dtype == DBT_BF16 && gemm_tile_args_ok(tg, false)) {
+      tg.splits = S = gemm_tile_splits(N, K, rows_M);
+      tg.y_stride = y_stride;
+      return launch_gemm_tile(tg, false, st);
+    }
     return launch_gemm(segs, N, K, cf.dtype, X, ldx, rows_M, Y, ldy, y_stride, g, st);
   };
   const GemmConfig g_qkv = cfg(L.g_qkv), g_o = cfg(L.g_o), g_gu = cfg(L.g_gu), g_d = cfg(L.g_d);
-  const int S_qkv = g_qkv.S, S_o = g_o.S, S_gu = g_gu.S, S_d = g_d.S;
+  const int S_gu = g_gu.S;
+  int S_qkv = g_qkv.S, S_o = 1, S_d = 1;
   KVRef kvl = kv_layer(kv, l);
   const size_t rq = (size_t)l * L.Bp_max;
   float *ret_q = m->at<float>(L.ret_q) + rq * dq;
@@ -804,7 +812,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
     HIPCHK(launch_gemm_xnorm(qkv, nq, d, xn, aM, P + (size_t)axrow0 * nq, nq, stride, g_qkv, st));
   } else {
     Timed tm(m, DBT_STAGE_QKV, st);
-    HIPCHK(project(qkv, nq, d, Xn + (size_t)axrow0 * d * es, d, aM, P + (size_t)axrow0 * nq, nq, stride, g_qkv));
+    HIPCHK(project(qkv, nq, d, Xn + (size_t)axrow0 * d * es, d, aM, P + (size_t)axrow0 * nq, nq, stride, g_qkv, S_qkv));
   }
   QKVFinish qf{};
   qf.part = P;
@@ -878,7 +886,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
   stride = (long long)c.rows_layout * d;
   {
     Timed tm(m, DBT_STAGE_WO, st);
-    HIPCHK(project(wo, d, dq, O + (size_t)axrow0 * dq * es, dq, aM, P + (size_t)axrow0 * d, d, stride, g_o));
+    HIPCHK(project(wo, d, dq, O + (size_t)axrow0 * dq * es, dq, aM, P + (size_t)axrow0 * d, d, stride, g_o, S_o));
   }
   const GatedCopy gca = cm ? GatedCopy{W.g_attn_copy, ret_a, Retain{c.retain ? ret_a : nullptr, map}}
                            : GatedCopy{};
@@ -928,7 +936,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
   stride = (long long)c.rows_layout * d;
   {
     Timed tm(m, DBT_STAGE_DOWN, st);
-    HIPCHK(project(wd, d, f, Xh + (size_t)xrow0 * f * es, f, M, P + (size_t)xrow0 * d, d, stride, g_d));
+    HIPCHK(project(wd, d, f, Xh + (size_t)xrow0 * f * es, f, M, P + (size_t)xrow0 * d, d, stride, g_d, S_d));
   }
   const float *g_next = nullptr;
   if (l + 1 < cf.n_layers) g_next = m->layers[l + 1].attn_norm;

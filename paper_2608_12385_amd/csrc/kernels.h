@@ -132,7 +132,7 @@ hipError_t launch_gemm(const WSegs &segs, int N, int K, int dtype, const void *X
 int gemm_stats_tiles(int N, const GemmConfig &g, int dtype);
 int gemm_tile_rows(const GemmConfig &g);  // weight rows (output columns) per workgroup
 
-// Projection of a whole prompt (M >= 256 rows, K a multiple of 64, N a
+// Projection of a whole prompt (M >= 256 rows, K a multiple of 128, N a
 // multiple of 16, bf16): 256-row tiles on the matrix cores.  Plain: Y (fp32,
 // [M][ldy]) = X W^T with W the stacked segments w[0..2] (rows[0..2] rows).
 // GLU: w[0] = gate, w[1] = up (N = f rows each); writes H (bf16, [M][ldh]) =
@@ -149,6 +149,8 @@ struct TileGemm {
   int ldx, M;
   float *Y;
   int ldy;
+  int splits;          // plain: reduction splits, slab s at Y + s*y_stride (0 reads as 1)
+  long long y_stride;
   uint16_t *H;
   int ldh;
   Retain ret;
@@ -158,11 +160,15 @@ struct TileGemm {
   const PromptRow *prompt;
 };
 bool gemm_tile_ok(int N, int K, int M, int dtype);
-// Prompt rows from which launch_gemm_tile is used (its tile height).
+// Prompt rows from which launch_gemm_tile is used.
 constexpr int kTileRows = 256;
+// Reduction splits launch_gemm_tile should run a plain projection with; every
+// slab together has at most kTileSlabs elements more than one.
+int gemm_tile_splits(int N, int K, int M);
+constexpr int kTileSlabs = 256 * 256 * 256;
 // Everything launch_gemm_tile requires of g (the shape test above, segment
 // sizes multiples of 8 summing to N, row strides multiples of 8, element
-// offsets within 32 bits); callers fall back to launch_gemm otherwise.
+// byte offsets within 32 bits); callers fall back to launch_gemm otherwise.
 bool gemm_tile_args_ok(const TileGemm &g, bool glu);
 hipError_t launch_gemm_tile(const TileGemm &g, bool glu, hipStream_t st);
 

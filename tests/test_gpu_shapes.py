@@ -171,3 +171,18 @@ def test_step_outputs_in_place_and_copied(dtype, vocab, grouped):
         for n, t in other.items():
             assert torch.equal(t, want[n]), n
     sess.close()
+
+
+# the tiled projections of 256 rows and more: one, three and five 128-element
+# reduction steps, a partial last row tile, an odd number of heads, splits of
+# unequal length; and a width whose gate/up tiles are the largest ones
+@pytest.mark.parametrize("d,nq,nkv,f,lens", [
+    (128, 1, 1, 640, [260, 1]),
+    (384, 3, 1, 1664, [257]),
+    (1152, 6, 2, 1408, [300, 90]),
+    (2048, 16, 4, 5632, [400, 601]),
+])
+def test_bf16_tiled_projections(d, nq, nkv, f, lens):
+    shape = synth.ModelShape(n_layers=1, d_model=d, n_q_heads=nq, n_kv_heads=nkv, head_dim=128, d_ff=f, vocab=512,
+                             dtype="bf16", has_embeddings=True, std=0.03, coupling_std=0.5)
+    prompts_and_steps(shape, lens, BF16_TOL, steps=1)
