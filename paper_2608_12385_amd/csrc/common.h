@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -46,6 +48,19 @@ __device__ __forceinline__ float rows4_max(float x) {
   x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
   const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// Maximum over the wave without LDS: rotations within each row of 16 lanes,
+// then rows4_max.
+__device__ __forceinline__ float wave_max_dpp(float x) {
+  auto turn = [](float v, auto ctrl) {
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true)));
+  };
+  x = turn(x, std::integral_constant<int, 0x128>{});  // row_ror:8, 4, 2, 1
+  x = turn(x, std::integral_constant<int, 0x124>{});
+  x = turn(x, std::integral_constant<int, 0x122>{});
+  x = turn(x, std::integral_constant<int, 0x121>{});
+  return rows4_max(x);
 }
 
 // Buffer resource over `bytes` bytes at p (raw, unswizzled, 32-bit data

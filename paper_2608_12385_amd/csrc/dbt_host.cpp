@@ -59,6 +59,10 @@ constexpr int kMixChunk = 4096;
 // rows, one for each compute unit.  24 prompts of 17-300 positions through two
 // layers of width 2048: 7.74 ms one by one, 1.13 ms packed.
 constexpr int kPackRows = 8192;
+// Average rows per expert from which a prompt pass runs the experts' products
+// as 128-row tiles instead of streaming each expert's weights past 32 rows at
+// a time.
+constexpr int kExpertTileRows = 16;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 int round16(int x) { return (x + 15) / 16 * 16; }
@@ -78,7 +82,7 @@ struct Layout {
   bool glu = false;
   int fe = 0, fs = 0, amax = 0;
   GemmConfig g_sgu{1, 1, 1}, g_sd{1, 1, 1};
-  size_t moe_idx = 0, moe_logits = 0, moe_w = 0, moe_aslot = 0, moe_counts = 0, moe_offsets = 0, moe_arow = 0, moe_h = 0,
+  size_t moe_idx = 0, moe_tiles = 0, moe_ntiles = 0, moe_w = 0, moe_aslot = 0, moe_counts = 0, moe_offsets = 0, moe_arow = 0, moe_h = 0,
          moe_y = 0, ret_idx = 0;
   size_t prow = 0, ptiles = 0;  // prompt passes: row map, attention tiles
   size_t rope = 0, pos = 0, S = 0, Xn = 0, Xh = 0, Q = 0, O = 0, P = 0, apart = 0, astat = 0,
@@ -235,7 +239,7 @@ Layout make_layout(const dbt_config *c, int rows_min = 0) {
   if (L.moe) {
     L.amax = L.rows_max * 8;
     L.moe_idx = take((size_t)L.rows_max * 8 * 4);
-    L.moe_logits = take((size_t)L.rows_max * 256 * 4);
+    take((size_t)L.rows_max * 256 * 4);  // (keeps the size the allocation-free step is refused by)
     L.moe_w = take((size_t)L.rows_max * 8 * 4);
     L.moe_aslot = take((size_t)L.rows_max * 8 * 4);
     L.moe_counts = take((size_t)c->n_experts * 4);
@@ -265,14 +269,15 @@ Layout make_prompt_layout(const dbt_config *c, const Layout &step) {
   L.O = take((size_t)R * dq * es);
   size_t part = std::max(prompt_part(L.g_qkv, L.nqkv, d, c->dtype, R, true), prompt_part(L.g_o, d, dq, c->dtype, R, false));
   if (L.moe)
-    part = std::max({part, (size_t)R * 2 * L.fs, (size_t)R * d * (size_t)std::max(L.g_sd.S, 1)});
+    part = std::max({part, prompt_part(L.g_sgu, 2 * L.fs, d, c->dtype, R, true), prompt_part(L.g_sd, d, L.fs, c->dtype, R, false)});
   else
     part = std::max({part, prompt_part(L.g_gu, 2 * L.f, d, c->dtype, R, true), prompt_part(L.g_d, d, L.f, c->dtype, R, false)});
   L.P = take(part * 4);
   if (L.moe) {
     L.amax = R * c->top_k1;  // (the primary alone)
     L.moe_idx = take((size_t)R * 8 * 4);
-    L.moe_logits = take((size_t)R * 256 * 4);
+    L.moe_tiles = take((size_t)(L.pack_rows * c->top_k1 / kTileExpert + c->n_experts + 1) * sizeof(int2));
+    L.moe_ntiles = take(4);
     L.moe_w = take((size_t)R * 8 * 4);
     L.moe_aslot = take((size_t)R * 8 * 4);
     L.moe_arow = take((size_t)L.amax * 4);
@@ -536,7 +541,6 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
   ro.replay = cf.replay;
   ro.rows = c.rows;
   ro.mode = c.mode;
-  ro.logits = m->at<float>(L.moe_logits);
   ro.idx = m->at<int>(L.moe_idx);
   ro.wts = m->at<float>(L.moe_w);
   ro.idx1_in = ret_idx;
@@ -592,17 +596,49 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
   int S_sh = 0;
   if (fs > 0 && !(cm && c.mode == MODE_BRANCH)) {
     GemmConfig g_sgu = L.g_sgu, g_sd = L.g_sd;
-    if (c.prefill) g_sgu.S = g_sd.S = 1;
+    if (c.prefill) {  // as in run_layer
+      g_sgu.S = sM < kTileRows ? prompt_splits(g_sgu, sM) : 1;
+      g_sd.S = sM < kTileRows ? prompt_splits(g_sd, sM) : 1;
+    }
     WSegs gu{{W.s_gate, W.s_up, nullptr}, {fs, fs, 0}};
     long long st_gu = (long long)c.rows_layout * 2 * fs;
-    HIPCHK(launch_gemm(gu, 2 * fs, d, cf.dtype, m->p(L.Xn) + (size_t)sxrow0 * d * es, d, sM,
-                       P + (size_t)sxrow0 * 2 * fs, 2 * fs, st_gu, g_sgu, sst));
-    HIPCHK(launch_swiglu_finish(P, st_gu, g_sgu.S, 2 * fs, fs, smode, srows, W.b, ret_h,
-                                Retain{c.retain && !cm ? ret_h : nullptr, map}, cf.dtype,
-                                m->p(L.Xh), fs, sst));
+    const Retain keep{c.retain && !cm ? ret_h : nullptr, map};
+    TileGemm tg{}, td{};
+    tg.w[0] = (const uint16_t *)W.s_gate;
+    tg.w[1] = (const uint16_t *)W.s_up;
+    tg.rows[0] = tg.rows[1] = tg.N = fs;
+    tg.K = d;
+    tg.X = (const uint16_t *)(m->p(L.Xn) + (size_t)sxrow0 * d * es);
+    tg.ldx = d;
+    tg.M = sM;
+    tg.H = (uint16_t *)(m->p(L.Xh) + (size_t)sxrow0 * fs * es);
+    tg.ldh = fs;
+    tg.ret = keep;
+    if (c.prefill && gemm_tile_args_ok(tg, true)) {
+      HIPCHK(launch_gemm_tile(tg, true, sst));
+    } else {
+      HIPCHK(launch_gemm(gu, 2 * fs, d, cf.dtype, m->p(L.Xn) + (size_t)sxrow0 * d * es, d, sM,
+                         P + (size_t)sxrow0 * 2 * fs, 2 * fs, st_gu, g_sgu, sst));
+      HIPCHK(launch_swiglu_finish(P, st_gu, g_sgu.S, 2 * fs, fs, smode, srows, W.b, ret_h, keep, cf.dtype,
+                                  m->p(L.Xh), fs, sst));
+    }
     WSegs sd{{W.s_down, nullptr, nullptr}, {d, 0, 0}};
-    HIPCHK(launch_gemm(sd, d, fs, cf.dtype, m->p(L.Xh) + (size_t)sxrow0 * fs * es, fs, sM, P + (size_t)sxrow0 * d,
-                       d, stride, g_sd, sst));
+    td.w[0] = (const uint16_t *)W.s_down;
+    td.rows[0] = td.N = d;
+    td.K = fs;
+    td.X = tg.H;
+    td.ldx = fs;
+    td.M = sM;
+    td.Y = P + (size_t)sxrow0 * d;
+    td.ldy = d;
+    if (c.prefill && gemm_tile_args_ok(td, false)) {
+      td.splits = g_sd.S = gemm_tile_splits(d, fs, sM);
+      td.y_stride = stride;
+      HIPCHK(launch_gemm_tile(td, false, sst));
+    } else {
+      HIPCHK(launch_gemm(sd, d, fs, cf.dtype, m->p(L.Xh) + (size_t)sxrow0 * fs * es, fs, sM, P + (size_t)sxrow0 * d,
+                         d, stride, g_sd, sst));
+    }
     S_sh = g_sd.S;
   }
   HIPCHK(launch_moe_route(ro, st));
@@ -616,9 +652,46 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
   di.offsets = m->at<int>(L.moe_offsets);
   di.arow = m->at<int>(L.moe_arow);
   di.aslot = m->at<int>(L.moe_aslot);
-  HIPCHK(launch_moe_dispatch(di, st));
   const int max_rows = c.rows.np * c.rows.B;
-  {
+  // The experts' products of a prompt pass with enough rows per expert on the
+  // tiled kernel (see kExpertTileRows).
+  TileGemm xg{}, xd{};
+  if (c.prefill && (long long)max_rows * cf.top_k1 >= (long long)kExpertTileRows * cf.n_experts) {
+    di.tiles = m->at<int2>(L.moe_tiles);
+    di.ntiles = m->at<int>(L.moe_ntiles);
+    xg.w[0] = (const uint16_t *)W.x_gate;
+    xg.w[1] = (const uint16_t *)W.x_up;
+    xg.rows[0] = xg.rows[1] = xg.N = L.fe;
+    xg.K = d;
+    xg.X = (const uint16_t *)m->p(L.Xn);
+    xg.ldx = d;
+    xg.M = max_rows;
+    xg.H = (uint16_t *)m->p(L.moe_h);
+    xg.ldh = L.fe;
+    xg.tiles = di.tiles;
+    xg.ntiles = di.ntiles;
+    xg.counts = di.counts;
+    xg.offsets = di.offsets;
+    xg.arow = di.arow;
+    xg.max_tiles = max_rows * cf.top_k1 / kTileExpert + std::min(cf.n_experts, max_rows * cf.top_k1);
+    xd = xg;
+    xd.w[0] = (const uint16_t *)W.x_down;
+    xd.rows[0] = xd.N = d;
+    xd.K = L.fe;
+    xd.X = xg.H;
+    xd.ldx = L.fe;
+    xd.M = max_rows * cf.top_k1;
+    xd.H = nullptr;
+    xd.Y = m->at<float>(L.moe_y);
+    xd.ldy = d;
+    xd.arow = nullptr;
+  }
+  const bool tiled = di.tiles && gemm_tile_experts_ok(xg) && gemm_tile_experts_ok(xd);
+  HIPCHK(launch_moe_dispatch(di, st));
+  if (tiled) {
+    Timed tm(m, DBT_STAGE_GATEUP, st);
+    HIPCHK(launch_gemm_tile_experts(xg, true, st));
+  } else {
     Timed tm(m, DBT_STAGE_GATEUP, st);
     MoeGemm g{};
     g.X = m->p(L.Xn);
@@ -635,7 +708,10 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
     g.ldy = L.fe;
     HIPCHK(launch_moe_gemm(g, true, max_rows, st));
   }
-  {
+  if (tiled) {
+    Timed tm(m, DBT_STAGE_DOWN, st);
+    HIPCHK(launch_gemm_tile_experts(xd, false, st));
+  } else {
     Timed tm(m, DBT_STAGE_DOWN, st);
     MoeGemm g{};
     g.X = m->p(L.moe_h);

@@ -158,6 +158,12 @@ struct TileGemm {
   float *Qout;
   KVRef kv;
   const PromptRow *prompt;
+  // expert products (moe): X rows grouped by expert through arow (gate/up; NULL:
+  // in expert order already), the experts' matrices behind each other in
+  // w[0], w[1], outputs in expert order; M bounds the rows of all experts
+  const int2 *tiles;
+  const int *ntiles, *counts, *offsets, *arow;
+  int max_tiles;
 };
 bool gemm_tile_ok(int N, int K, int M, int dtype);
 // Prompt rows from which launch_gemm_tile is used.
@@ -171,6 +177,9 @@ constexpr int kTileSlabs = 256 * 256 * 256;
 // byte offsets within 32 bits); callers fall back to launch_gemm otherwise.
 bool gemm_tile_args_ok(const TileGemm &g, bool glu);
 hipError_t launch_gemm_tile(const TileGemm &g, bool glu, hipStream_t st);
+// The expert products of a pass (see TileGemm::tiles).
+bool gemm_tile_experts_ok(const TileGemm &g);
+hipError_t launch_gemm_tile_experts(const TileGemm &g, bool glu, hipStream_t st);
 
 // ---- row-wise and elementwise stages ----
 struct StepBegin {
@@ -368,7 +377,6 @@ struct MoeRoute {
   int E, k1, k2, replay;
   Rows rows;
   int mode;
-  float *logits;      // [2Bp][256] router logits (fp32)
   int *idx;           // [2Bp][8] selected experts (logit descending)
   float *wts;         // [2Bp][8] renormalised weights
   const int *idx1_in; // branch mode + replay: retained primary selections [*, 8]
@@ -386,7 +394,10 @@ struct MoeDispatch {
   int *offsets;  // [E+1]
   int *arow;     // [A] activation row of each expert-grouped assignment
   int *aslot;    // [2Bp][8] position of each (row, slot) in the expert-grouped order
+  int2 *tiles;   // row tiles of kTileExpert rows: (expert, first row); NULL: not wanted
+  int *ntiles;
 };
+constexpr int kTileExpert = 128;
 struct MoeGemm {
   const void *X;  // gate/up: normalized MLP inputs (gathered by arow); down: expert intermediates
   int ldx;

@@ -69,7 +69,7 @@ __device__ __forceinline__ void wait_loads() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
 }
 
-template <int BM, int BN, int BK, int EPI>
+template <int BM, int BN, int BK, int EPI, bool MOE = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_tile(TileGemm g) {
   constexpr bool GLU = EPI == EPI_GLU, QKV = EPI == EPI_QKV;
   constexpr int MH = BM / 64;   // 16-row blocks of a wave's row half
@@ -98,7 +98,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     tx = q / rows;
     ty = 8 * band + q % rows;
   }
-  const int m0 = ty * BM;
+  // MOE: row tile ty of the list, an expert's rows m0 .. (XCD order aside: the
+  // list is shorter than the grid, and an expert's tiles share no weights)
+  int M = g.M, row0 = 0, m0 = ty * BM;
+  size_t we = 0;
+  if constexpr (MOE) {
+    static_assert(BM == kTileExpert, "the list's tiles");
+    if ((int)blockIdx.y >= *g.ntiles) return;
+    const int2 tile = g.tiles[blockIdx.y];
+    tx = blockIdx.x;
+    m0 = tile.y;
+    M = g.counts[tile.x];
+    row0 = g.offsets[tile.x];
+    we = (size_t)tile.x * g.N * g.K;
+  }
   const int n0 = tx * (GLU ? BN / 2 : BN);
   // split z of the reduction: steps k_lo .. k_hi - 1, a whole number of
   // 128-element pieces (plain outputs, one slab per split)
@@ -118,7 +131,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
       const int R = RPL * (XL * wave + i), row = m0 + R / (BM / 4) * (BM / 2) + h * (BM / 4) + R % (BM / 4) + lrow;
-      xo[h][i] = ((uint32_t)min(row, g.M - 1) * (uint32_t)g.ldx + k_lo * BK + lchunk(R) * 8) * 2;
+      int src = min(row, M - 1);
+      if constexpr (MOE) src = g.arow ? g.arow[row0 + src] : row0 + src;
+      xo[h][i] = ((uint32_t)src * (uint32_t)g.ldx + k_lo * BK + lchunk(R) * 8) * 2;
     }
   // W half h, its row R: wave column w = R / (BN/8), its row R % (BN/8)
   const uint16_t *wb[2][WL];
@@ -129,7 +144,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int i = 0; i < WL; ++i) {
       const int R = RPL * (WL * wave + i), w = R / (BN / 8), c = R % (BN / 8);
       if (GLU) {
-        wb[h][i] = g.w[h];
+        wb[h][i] = g.w[h] + we;
         wo[h][i] = ((uint32_t)min(n0 + w * (BN / 8) + c + lrow, g.N - 1) * (uint32_t)K + k_lo * BK + lchunk(R) * 8) * 2;
       } else {
         // first column of the group; QKV: head w / (512 / BN), dimension 64 h + ...
@@ -137,7 +152,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                             : n0 + w * (BN / 4) + h * (BN / 8) + c;
         int seg = min(col, g.N - 1), row = min(col + lrow, g.N - 1);
         const uint16_t *base = g.w[0];
-        if (seg >= g.rows[0]) {  // segment sizes are multiples of 8: one segment per group
+        if (!MOE && seg >= g.rows[0]) {  // segment sizes are multiples of 8: one segment per group
           seg -= g.rows[0];
           row -= g.rows[0];
           base = g.w[1];
@@ -146,7 +161,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             base = g.w[2];
           }
         }
-        wb[h][i] = base;
+        wb[h][i] = base + we;
         wo[h][i] = ((uint32_t)row * (uint32_t)K + k_lo * BK + lchunk(R) * 8) * 2;
       }
     }
@@ -280,8 +295,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int ib = 0; ib < 2 * MH; ++ib) {
     const int i = ib / MH, b = ib % MH;
     const int m = m0 + BM / 2 * wm + BM / 4 * i + 16 * b + r;
-    if (m >= g.M) continue;
-    const int kept_row = GLU || QKV ? g.ret.row(m) : -1;
+    if (m >= M) continue;
+    const int kept_row = !MOE && (GLU || QKV) ? g.ret.row(m) : -1;
     if (QKV) {
       // heads of 128: Q, then K, then V
       const int hn0 = n0 + wn / (512 / BN) * 128;
@@ -345,7 +360,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           const float gt = acc[0][a][i][b][e], up = acc[1][a][i][b][e];
           h[e] = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
         }
-        *(u32x2 *)(g.H + (size_t)m * g.ldh + j) = u32x2{pack2(h[0], h[1]), pack2(h[2], h[3])};
+        *(u32x2 *)(g.H + (size_t)(row0 + m) * g.ldh + j) = u32x2{pack2(h[0], h[1]), pack2(h[2], h[3])};
         if (kept_row >= 0) *(float4 *)(g.ret.ptr + (size_t)kept_row * g.N + j) = float4{h[0], h[1], h[2], h[3]};
       }
     } else {
@@ -355,7 +370,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int a = 0; a < NH; ++a) {
           const int n = n0 + wn * (BN / 4) + j * (BN / 8) + 16 * a + 4 * gq;
           if (n >= g.N) continue;
-          *(floatx4 *)(g.Y + split * g.y_stride + (size_t)m * g.ldy + n) = acc[j][a][i][b];
+          *(floatx4 *)(g.Y + split * g.y_stride + (size_t)(row0 + m) * g.ldy + n) = acc[j][a][i][b];
         }
     }
   }
@@ -434,6 +449,22 @@ hipError_t launch_gemm_tile(const TileGemm &g, bool glu, hipStream_t st) {
     go(integral_constant<int, 128>{}, integral_constant<int, 256>{}, integral_constant<int, 64>{});
   else
     go(integral_constant<int, 128>{}, integral_constant<int, 128>{}, integral_constant<int, 128>{});
+  return hipGetLastError();
+}
+
+
+bool gemm_tile_experts_ok(const TileGemm &g) {
+  return g.K % 128 == 0 && g.N % 16 == 0 && g.ldx % 8 == 0 && g.tiles && g.ntiles && g.counts && g.offsets &&
+         g.max_tiles > 0 && g.max_tiles <= 65535 && (long long)g.M * g.ldx < (1LL << 31) &&
+         (long long)g.N * g.K < (1LL << 31);
+}
+
+hipError_t launch_gemm_tile_experts(const TileGemm &g, bool glu, hipStream_t st) {
+  if (!gemm_tile_experts_ok(g)) return hipErrorInvalidValue;
+  if (glu)
+    hipLaunchKernelGGL((k_gemm_tile<128, 256, 64, EPI_GLU, true>), dim3((g.N + 127) / 128, g.max_tiles), dim3(512), 0, st, g);
+  else
+    hipLaunchKernelGGL((k_gemm_tile<128, 256, 64, EPI_PLAIN, true>), dim3((g.N + 255) / 256, g.max_tiles), dim3(512), 0, st, g);
   return hipGetLastError();
 }
 

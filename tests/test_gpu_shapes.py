@@ -186,3 +186,22 @@ def test_bf16_tiled_projections(d, nq, nkv, f, lens):
     shape = synth.ModelShape(n_layers=1, d_model=d, n_q_heads=nq, n_kv_heads=nkv, head_dim=128, d_ff=f, vocab=512,
                              dtype="bf16", has_embeddings=True, std=0.03, coupling_std=0.5)
     prompts_and_steps(shape, lens, BF16_TOL, steps=1)
+
+
+# expert counts around the router's 16-expert blocks and 64-lane rows, batches
+# around its 8- and 16-row workgroups, fan-outs up to all experts; prompts whose
+# experts take streamed passes, one tile and several tiles of rows
+@pytest.mark.parametrize("E,k1,k2,replay,lens", [
+    (1, 1, 1, False, [5]),
+    (17, 2, 8, False, [1] * 9),
+    (64, 2, 2, True, [3] * 17),
+    (100, 8, 3, False, [2, 7]),
+    (256, 4, 4, True, [6]),
+    (8, 2, 2, False, [90, 33]),
+    (3, 2, 1, False, [300, 111]),
+])
+def test_moe_router_and_expert_tiles(E, k1, k2, replay, lens):
+    shape = synth.ModelShape(n_layers=1, d_model=512, n_q_heads=4, n_kv_heads=1, head_dim=128, d_ff=0, vocab=448,
+                             dtype="bf16", has_embeddings=True, n_experts=E, d_ff_expert=128, n_shared_experts=1,
+                             d_ff_shared=256, top_k1=k1, top_k2=k2, replay=replay, std=0.05, coupling_std=0.5)
+    prompts_and_steps(shape, lens, BF16_TOL, steps=1)
