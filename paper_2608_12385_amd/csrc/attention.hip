@@ -495,7 +495,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
         l += sl[w][qr] * f;
       }
     }
-    if constexpr (SINGLE) {
+    if (SINGLE || npages <= a.pages_per_split) {  // no other split: nothing to merge
       const int path = a.rows.p0 + qr / G, head = g * G + qr % G;
       ((uint16_t *)a.O)[(size_t)(path * a.rows.Bp + b) * a.ldo + head * DH + dh] = f2bf(o / l);
     } else {
@@ -557,6 +557,7 @@ __global__ void k_attn_combine(AttnArgs a, T *O, int ldo) {
   const int len = a.pos_arr[b] + 1;
   const int npages = (len + 15) >> 4;
   const int nsplit = (npages + a.pages_per_split - 1) / a.pages_per_split;  // as split_range
+  if (sizeof(T) == 2 && nsplit == 1) return;  // written by the attention kernel
   const int n_kv = a.kv.n_kv, DH = a.kv.d_h, Q4 = DH / 4;
   const int G = a.n_q / n_kv;
   const int nrows = a.rows.np * G;

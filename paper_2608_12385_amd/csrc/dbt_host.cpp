@@ -862,7 +862,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
   // appends the cache entry itself.
   int maxlen = 0;
   if (!c.prefill)
-    for (int b = 0; b < c.rows.B; ++b) maxlen = std::max(maxlen, kv->len[b] + 1);
+    for (int b = 0; b < c.rows.B; ++b) maxlen = std::max(maxlen, kv->len[b] + 1);  // (the boundary: one too many)
   bool attn_single = false;
   const bool finish_in_attn = !c.prefill && attn_finishes_qkv(m, c.rows.B, maxlen, &attn_single);
   const bool xin = l == 0 && c.hin && c.hin->h1;
@@ -954,7 +954,8 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
       Timed tm(m, DBT_STAGE_ATTN, st);
       HIPCHK(launch_attn_decode(aa, st));
     }
-    if (!aa.single) HIPCHK(launch_attn_combine(aa, O, dq, st));
+    // (a sequence of one split is written by the kernel itself)
+    if (!aa.single && (maxlen + kPage - 1) / kPage > L.split_target) HIPCHK(launch_attn_combine(aa, O, dq, st));
   }
 
   // 3. output projection + residual + MLP norm

@@ -654,8 +654,14 @@ void launch_mb(const GemmConfig &g, dim3 grid, hipStream_t st, const WSegs &segs
 }
 
 template <int MB>
-void launch_glu_mb(dim3 grid, hipStream_t st, const WSegs &segs, int K, const uint16_t *X, int ldx, int M,
+void launch_glu_mb(int NW, dim3 grid, hipStream_t st, const WSegs &segs, int K, const uint16_t *X, int ldx, int M,
                    const GluEpi &ep) {
+  if (NW == 4) {
+    if constexpr (MB <= 4)
+      hipLaunchKernelGGL((k_gemm_bf16<MB, 1, 4, 4, true, 4>), grid, dim3(256), 0, st, segs, K, X, ldx, M, nullptr, 0,
+                         0LL, nullptr, ep, NoX{}, YRows{});
+    return;
+  }
   hipLaunchKernelGGL((k_gemm_bf16<MB, 1, 2, 8, true>), grid, dim3(512), 0, st, segs, K, X, ldx, M, nullptr, 0, 0LL,
                      nullptr, ep, NoX{}, YRows{});
 }
@@ -697,9 +703,14 @@ int gemm_stats_tiles(int N, const GemmConfig &g, int dtype) {
 
 // Tiles of 64 gate + 64 up rows (eight waves of 8 + 8); enough of them to
 // fill the chip, and a branch row's primary partner in the same activation
-// tile (M <= 128).
+// tile (M <= 128).  Narrower MLPs of 128 to 256 tiles of 32 + 32 rows take those
+// (four waves, one workgroup per compute unit, four chunks in flight) up to 64
+// stacked rows: 5632 units of width 2048 at 32 rows 13.2 us (14.6 with two chunks
+// in flight), against 13.0 us for the split projection and 4.4 us for a SwiGLU
+// kernel after it; at 128 rows they lose (27-32 against 25 us).
 bool gemm_glu_ok(int f, int M, int np, int dtype) {
-  return dtype == 1 && f % 64 == 0 && f / 64 >= 192 && (np == 1 || M <= 128);
+  if (dtype != 1) return false;
+  return (f % 64 == 0 && f / 64 >= 192 && (np == 1 || M <= 128)) || (f % 32 == 0 && f / 32 >= 128 && f / 32 <= 256 && M <= 64);
 }
 
 hipError_t launch_gemm_glu(const uint16_t *w_gate, const uint16_t *w_up, int f, int K, const void *X, int ldx, int M,
@@ -708,18 +719,18 @@ hipError_t launch_gemm_glu(const uint16_t *w_gate, const uint16_t *w_up, int f, 
   if (!gemm_glu_ok(f, M, ep.rows.np, 1)) return hipErrorInvalidValue;
   const WSegs segs{{w_gate, w_up, nullptr}, {f, f, 0}};
   const int mb_total = (M + 15) / 16;
-  const int MB = mb_total >= 8 ? 8 : mb_total;
-  dim3 grid(f / 64, 1, (mb_total + MB - 1) / MB);
+  const int MB = mb_total >= 8 ? 8 : mb_total, NW = f / 64 >= 192 ? 8 : 4;
+  dim3 grid(f / (8 * NW), 1, (mb_total + MB - 1) / MB);
   const uint16_t *Xb = (const uint16_t *)X;
   switch (MB) {
-    case 1: launch_glu_mb<1>(grid, st, segs, K, Xb, ldx, M, ep); break;
-    case 2: launch_glu_mb<2>(grid, st, segs, K, Xb, ldx, M, ep); break;
-    case 3: launch_glu_mb<3>(grid, st, segs, K, Xb, ldx, M, ep); break;
-    case 4: launch_glu_mb<4>(grid, st, segs, K, Xb, ldx, M, ep); break;
-    case 5: launch_glu_mb<5>(grid, st, segs, K, Xb, ldx, M, ep); break;
-    case 6: launch_glu_mb<6>(grid, st, segs, K, Xb, ldx, M, ep); break;
-    case 7: launch_glu_mb<7>(grid, st, segs, K, Xb, ldx, M, ep); break;
-    default: launch_glu_mb<8>(grid, st, segs, K, Xb, ldx, M, ep); break;
+    case 1: launch_glu_mb<1>(NW, grid, st, segs, K, Xb, ldx, M, ep); break;
+    case 2: launch_glu_mb<2>(NW, grid, st, segs, K, Xb, ldx, M, ep); break;
+    case 3: launch_glu_mb<3>(NW, grid, st, segs, K, Xb, ldx, M, ep); break;
+    case 4: launch_glu_mb<4>(NW, grid, st, segs, K, Xb, ldx, M, ep); break;
+    case 5: launch_glu_mb<5>(NW, grid, st, segs, K, Xb, ldx, M, ep); break;
+    case 6: launch_glu_mb<6>(NW, grid, st, segs, K, Xb, ldx, M, ep); break;
+    case 7: launch_glu_mb<7>(NW, grid, st, segs, K, Xb, ldx, M, ep); break;
+    default: launch_glu_mb<8>(NW, grid, st, segs, K, Xb, ldx, M, ep); break;
   }
   return hipGetLastError();
 }
