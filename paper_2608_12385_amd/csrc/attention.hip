@@ -52,18 +52,14 @@ __device__ __forceinline__ float row_scale(const QKVFinish &f, int R) {
 }
 
 // Requires d_h == 128 and np*G <= 16.
-// <4, false>: one split of the sequence per workgroup of four waves (at most
-// 128 pages, two page ids per lane), partials merged by k_attn_combine.
-// <8, false>: the same with eight waves and splits of up to 1024 pages (page
-// ids staged in LDS), for long sequences: one round of longer workgroups.
-// <8, true> (a.single): the whole sequence in one workgroup of eight waves
-// (at most 1024 pages), the waves merged in LDS and the normalised rows
-// written to a.O directly.
-template <int NW, bool SINGLE>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_attn_decode_bf16(AttnArgs a) {
+// SINGLE (a.single): the whole sequence in one workgroup of eight waves (at
+// most 1024 pages), the waves merged in LDS and the normalised rows written to
+// a.O directly.  Otherwise one split of at most 1024 pages per workgroup,
+// partials merged by k_attn_combine.
+template <bool SINGLE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_attn_decode_bf16(AttnArgs a) {
   constexpr int DH = 128;
-  constexpr bool LDSIDS = NW == 8;  // page ids of the split staged in LDS (else two per lane)
-  static_assert(!SINGLE || LDSIDS, "the single-workgroup kernel has eight waves");
+  constexpr int NW = 8;
   const int split = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
   const int len = a.pos_arr[b] + 1;
   const int npages = (len + 15) >> 4;
@@ -77,49 +73,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int nrows = a.rows.np * G;
   const int dq = a.n_q * DH;
   const float scale = kLog2e / sqrtf((float)DH);
-  // page ids of the split: lane i holds pages pb + i and pb + 64 + i
   const int *ptab = a.kv.page_table + (size_t)b * a.kv.mpps;
-  __shared__ int pid_s[LDSIDS ? 1024 : 1];
-  int myid0 = 0, myid1 = 0;
+  __shared__ int pid_s[1024];  // page ids of the split
   u32x4 qf[4];
-  // Fused finish of the QKV projection (single mode, a.fused): the workgroup
-  // turns the projection's split-K slabs into its query rows (qs) and the
-  // primary's new cache entry of KV head g, with the slabs added in split
-  // order and the same rope_pair / couple as k_qkv_finish, so the bits equal
-  // the unfused path's.
+  // Finish of the QKV projection: the workgroup turns the projection's split-K
+  // slabs into its query rows (qs) and the primary's new cache entry of KV
+  // head g, with the slabs added in split order and the same rope_pair /
+  // couple as k_qkv_finish.
   constexpr int QLD = DH + 4;  // row pitch of qs (floats): rows start on different banks
   __shared__ float qs[16][QLD];
-  if constexpr (!LDSIDS) {
-    myid0 = (pb + lane < pe) ? ptab[pb + lane] : 0;
-    myid1 = (pb + 64 + lane < pe) ? ptab[pb + 64 + lane] : 0;
-  }
-  auto page_id = [&](int j) {
-    if constexpr (LDSIDS) return pid_s[j];
-    else return __shfl(j < 64 ? myid0 : myid1, j & 63, 64);
-  };
-
-  // Query operand: lane (query r, group gq) holds Q[r][s*32 + gq*8 .. +8].
-  // Rows past the group's queries read row 0 and are zeroed: all eight
-  // loads are issued at once (a load guarded per element compiles to a
-  // branch and a full wait each, 32 round trips before the first page).
-  if (!a.fused) {
-    const bool valid = r < nrows;
-    const int path = a.rows.p0 + (valid ? r / G : 0);
-    const int head = g * G + (valid ? r % G : 0);
-    const float *qp = a.Q + (size_t)(path * a.rows.Bp + b) * dq + head * DH + gq * 8;
-    float4 x[8];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      x[2 * s] = *(const float4 *)(qp + s * 32);
-      x[2 * s + 1] = *(const float4 *)(qp + s * 32 + 4);
-    }
-    const float z = valid ? 1.f : 0.f;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const float4 u = x[2 * s] * z, w = x[2 * s + 1] * z;
-      qf[s] = u32x4{pack2(u.x, u.y), pack2(u.z, u.w), pack2(w.x, w.y), pack2(w.z, w.w)};
-    }
-  }
+  auto page_id = [&](int j) { return pid_s[j]; };
 
   const uint16_t *kbase = (const uint16_t *)a.kv.k;
   const uint16_t *vbase = (const uint16_t *)a.kv.v;
@@ -270,7 +233,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   // the loads in front of the multiplies.
   u32x4 raw[16];
   {
-    // Fused finish (a.fused): thread t < 64 G finishes the rotary pair
+    // Thread t < 64 G finishes the rotary pair
     // (i, i + 64) of query head g G + t / 64 on every path of the call (every
     // split of a sequence computes its queries); threads 64 G .. 64 G + 191
     // of the workgroup that holds the sequence's last page append the
@@ -283,30 +246,28 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     const QKVFinish &f = a.fin;
     const int t = threadIdx.x, pos = len - 1, np = a.rows.np;
     const bool prim = f.mode != MODE_BRANCH;  // then path p0 = 0 is the primary
-    const bool appends = a.fused && prim && pe == npages;
+    const bool appends = prim && pe == npages;
     const int hh = t / (DH / 2), i = t % (DH / 2), u = t - G * (DH / 2);
     const int c0 = (g * G + hh) * DH + i, c1 = c0 + DH / 2;
     const int dkv = n_kv * DH;
     auto at = [&](int path, int col) { return (size_t)(path * a.rows.Bp + b) * f.ldp + col; };
     int ncol = 0;
     size_t idx[4] = {0, 0, 0, 0};
-    if (a.fused) {
-      if (u < 0) {
+    if (u < 0) {
 #pragma unroll
-        for (int pp = 0; pp < 2; ++pp)
-          if (pp < np) {
-            idx[2 * pp] = at(a.rows.p0 + pp, c0);
-            idx[2 * pp + 1] = at(a.rows.p0 + pp, c1);
-          }
-        ncol = 2 * min(np, 2);
-      } else if (appends && u < DH / 2) {
-        idx[0] = at(0, dq + g * DH + u);
-        idx[1] = at(0, dq + g * DH + u + DH / 2);
-        ncol = 2;
-      } else if (appends && u < DH / 2 + DH) {
-        idx[0] = at(0, dq + dkv + g * DH + u - DH / 2);
-        ncol = 1;
-      }
+      for (int pp = 0; pp < 2; ++pp)
+        if (pp < np) {
+          idx[2 * pp] = at(a.rows.p0 + pp, c0);
+          idx[2 * pp + 1] = at(a.rows.p0 + pp, c1);
+        }
+      ncol = 2 * min(np, 2);
+    } else if (appends && u < DH / 2) {
+      idx[0] = at(0, dq + g * DH + u);
+      idx[1] = at(0, dq + g * DH + u + DH / 2);
+      ncol = 2;
+    } else if (appends && u < DH / 2 + DH) {
+      idx[0] = at(0, dq + dkv + g * DH + u - DH / 2);
+      ncol = 1;
     }
     // slabs 0..7 of the thread's columns, as 32 unconditional loads (a loop
     // or a guarded load here would wait for every outstanding load before
@@ -342,7 +303,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       if (u < 0 && !prim) q1 = make_float2(f.Q1_in[(size_t)b * dq + c0], f.Q1_in[(size_t)b * dq + c1]);
       if (u >= 0) page = ptab[pos >> 4];
     }
-    const int pid0 = LDSIDS && t < pe - pb ? ptab[pb + t] : 0;
+    const int pid0 = t < pe - pb ? ptab[pb + t] : 0;
     const bool early = wave < npairs && (!appends || pb + 2 * wave + 1 < npages - 1);
     // issued by every wave (empty resources when not early: no traffic), so
     // that the waits below count the same loads on every path
@@ -433,14 +394,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
           ((uint16_t *)a.kv.v)[(((size_t)page2 * n_kv + g) * DH + u2 - DH / 2) * 16 + (pos & 15)] = f2bf(vv);
         }
       }
-    if constexpr (LDSIDS) {
-      if (threadIdx.x < pe - pb) pid_s[threadIdx.x] = pid0;
-      for (int i = threadIdx.x + NW * 64; i < pe - pb; i += NW * 64) pid_s[i] = ptab[pb + i];
-    }
-    if (LDSIDS || a.fused) __syncthreads();  // page ids and query rows in LDS, the appended entry written
+    if (threadIdx.x < pe - pb) pid_s[threadIdx.x] = pid0;
+    for (int i = threadIdx.x + NW * 64; i < pe - pb; i += NW * 64) pid_s[i] = ptab[pb + i];
+    __syncthreads();  // page ids and query rows in LDS, the appended entry written
     if (!early && wave < npairs) load_pair(wave, raw, false);
   }
-  if (a.fused) {
+  {
     // query operand from the rows staged above (rows past the group's are zero)
     const float z = r < nrows ? 1.f : 0.f;
     const int rq = r < nrows ? r : 0;
@@ -594,26 +553,21 @@ __global__ void k_attn_combine(AttnArgs a, T *O, int ldo) {
 }  // namespace
 
 hipError_t launch_attn_decode(const AttnArgs &a, hipStream_t st) {
-  // split lengths: the four-wave bf16 kernel holds two page ids per lane, the
-  // eight-wave one 1024 in LDS (the fp32 one reads them as it goes)
-  const int max_pps = a.dtype == 1 && !a.wide ? 128 : 1024;
-  if ((!a.single || a.dtype != 1) && (a.pages_per_split < 1 || a.pages_per_split > max_pps)) return hipErrorInvalidValue;
-  // the fused query finish: bf16 cache, decode positions (one per
-  // sequence), the same rows as the attention, every query head of a KV
-  // head in the first pass (G <= waves)
-  if (a.fused && !(a.dtype == 1 && a.fin.pos_arr == a.pos_arr && a.fin.d_h == 128 &&
-                   a.fin.n_q == a.n_q && a.fin.n_kv == a.kv.n_kv && a.fin.rows.p0 == a.rows.p0 &&
-                   a.fin.rows.np == a.rows.np && a.fin.rows.Bp == a.rows.Bp && a.fin.rows.B == a.rows.B &&
-                   a.rows.np >= 1 && (a.fin.mode == MODE_BRANCH) == (a.rows.p0 >= 1) &&
-                   a.n_q / a.kv.n_kv <= (a.single || a.wide ? 8 : 4)))
+  // (the bf16 kernel holds 1024 page ids in LDS, the fp32 one reads them as it goes)
+  if ((!a.single || a.dtype != 1) && (a.pages_per_split < 1 || a.pages_per_split > 1024)) return hipErrorInvalidValue;
+  // the query finish: decode positions (one per sequence), the same rows as
+  // the attention, every query head of a KV head in the first pass (G <= waves)
+  if (a.dtype == 1 && !(a.fin.pos_arr == a.pos_arr && a.fin.d_h == 128 &&
+                        a.fin.n_q == a.n_q && a.fin.n_kv == a.kv.n_kv && a.fin.rows.p0 == a.rows.p0 &&
+                        a.fin.rows.np == a.rows.np && a.fin.rows.Bp == a.rows.Bp && a.fin.rows.B == a.rows.B &&
+                        a.rows.np >= 1 && (a.fin.mode == MODE_BRANCH) == (a.rows.p0 >= 1) &&
+                        a.n_q / a.kv.n_kv <= 8))
     return hipErrorInvalidValue;
   dim3 grid(a.max_splits, a.kv.n_kv, a.rows.B);
   if (a.dtype == 1 && a.single)
-    hipLaunchKernelGGL((k_attn_decode_bf16<8, true>), dim3(1, a.kv.n_kv, a.rows.B), dim3(512), 0, st, a);
-  else if (a.dtype == 1 && a.wide)
-    hipLaunchKernelGGL((k_attn_decode_bf16<8, false>), grid, dim3(512), 0, st, a);
+    hipLaunchKernelGGL((k_attn_decode_bf16<true>), dim3(1, a.kv.n_kv, a.rows.B), dim3(512), 0, st, a);
   else if (a.dtype == 1)
-    hipLaunchKernelGGL((k_attn_decode_bf16<4, false>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_attn_decode_bf16<false>), grid, dim3(512), 0, st, a);
   else {
     const dim3 g1(a.single ? 1 : a.max_splits, a.kv.n_kv, a.rows.B), block(64 * kWavesF32Attn);
     if (a.single && a.ldo != a.n_q * a.kv.d_h) return hipErrorInvalidValue;

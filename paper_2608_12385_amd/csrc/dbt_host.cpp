@@ -44,14 +44,19 @@ dbt_status fail(dbt_status s, const char *fmt, ...) {
 
 constexpr int kPage = 16;
 // Decode attention reads a sequence of P pages in ceil(P / target) equal
-// splits; 86 pages (1376 positions) keeps the splits long enough to amortise a
-// workgroup's start, and e.g. 4097 positions (257 pages) in three equal splits.
-// A model with few (sequence, KV head) pairs (max_batch x n_kv below 256)
-// takes shorter splits, down to 16 pages, so that its longest caches fill
-// about 512 workgroups.  The target is fixed when the model is created, so a
-// row's result depends only on its own query and cache.
+// splits, one workgroup of eight waves each.  A model with few (sequence, KV
+// head) pairs (max_batch x n_kv below 256) takes the target that makes its
+// longest caches one round of workgroups, within 24 pages (two or three page
+// pairs for each wave; the workgroup's start costs as much) and the 1024 page
+// ids the kernel holds; one with more pairs, which reads whole sequences when
+// the batch fills the chip, 86 pages for its smaller calls.  The target is
+// fixed when the model is created, so a row's result depends only on its own
+// query and cache.  Against four-wave workgroups of 16 to 128 pages, about
+// twice as many: 16 sequences of 300-1500 positions with 4 KV heads 14.9 + 5.7
+// (merge) -> 13.0 + 4.3 us; 16 or 48 pages instead of 24: equal, 15.8 us; two
+// rounds instead of one: up to 12 % slower steps.
 // fp32 splits are 64 pages long.
-constexpr int kSplitTargetBf16 = 86, kSplitMinBf16 = 16, kSplitTargetF32 = 64, kSplitWideMin = 256;
+constexpr int kSplitTargetBf16 = 86, kSplitMinBf16 = 24, kSplitMaxBf16 = 1024, kSplitTargetF32 = 64;
 constexpr int kMixChunk = 4096;
 // Prompts are prefilled in packed passes of up to max(max_prompt, kPackRows)
 // rows, so that each weight is read once for many short prompts and the tiled
@@ -74,7 +79,6 @@ struct Layout {
   int Bp_max = 0, R_max = 0, rows_max = 0, pack_rows = 0, max_in = 0, nqkv = 0, f = 0;
   GemmConfig g_qkv{1, 1, 1}, g_o{1, 1, 1}, g_gu{1, 1, 1}, g_d{1, 1, 1}, g_lm{1, 1, 1};
   int split_target = 0, max_splits = 0, nch = 0, nstat = 0;
-  bool wide = false;  // attention splits in eight-wave workgroups (see the layout set-up)
   bool moe = false;
   // Decode gate/up on the fused SwiGLU kernel: fixed per model (from the
   // largest stacked call), so every call of a step sums each output element
@@ -181,17 +185,9 @@ Layout make_layout(const dbt_config *c, int rows_min = 0) {
   const int maxpages = (c->max_pos + kPage - 1) / kPage;
   if (c->dtype == DBT_BF16) {
     const int pairs = c->max_batch * c->n_kv_heads;
-    const int want = pairs >= 256 ? 1 : (512 + pairs - 1) / pairs;  // splits per pair
-    L.split_target = std::clamp((maxpages + want - 1) / want, kSplitMinBf16, kSplitTargetBf16);
-    // long caches and few (sequence, KV head) pairs: one round of eight-wave
-    // workgroups, each reading up to 1024 pages, instead of several rounds
-    // of four-wave ones (fewer prologues, partial stores and splits to merge)
-    const int want8 = (256 + pairs - 1) / pairs;
-    const int target8 = (maxpages + want8 - 1) / want8;
-    if (pairs < 256 && target8 >= kSplitWideMin) {
-      L.wide = true;
-      L.split_target = std::min(target8, 1024);
-    }
+    const int want = (256 + pairs - 1) / pairs;  // splits per pair
+    L.split_target = pairs >= 256 ? std::min(std::max(maxpages, kSplitMinBf16), kSplitTargetBf16)
+                                  : std::clamp((maxpages + want - 1) / want, kSplitMinBf16, kSplitMaxBf16);
   } else {
     L.split_target = kSplitTargetF32;
   }
@@ -500,7 +496,7 @@ bool attn_finishes_qkv(const dbt_model *m, int B, int maxlen, bool *single_out) 
   // fp32: no sequence needs a second split (no partials to merge)
   const bool single = cf.dtype == DBT_BF16 ? B * cf.n_kv_heads >= 256 && npages <= 1024 : npages <= m->L.split_target;
   if (single_out) *single_out = single;
-  return cf.dtype == DBT_BF16 && cf.head_dim == 128 && cf.n_q_heads / cf.n_kv_heads <= (single || m->L.wide ? 8 : 4);
+  return cf.dtype == DBT_BF16;
 }
 
 bool input_fold(const dbt_model *m, const dbt_kv *kv, int B) {
@@ -945,8 +941,6 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
     // (sequence, KV head) is read by one eight-wave workgroup and no partials
     // are merged.  The choice depends on the batch, never on the branch.
     aa.single = attn_single;
-    aa.wide = L.wide;
-    aa.fused = finish_in_attn;
     aa.fin = qf;
     aa.O = O;
     aa.ldo = dq;

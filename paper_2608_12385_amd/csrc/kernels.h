@@ -299,7 +299,7 @@ hipError_t launch_down_finish(const float *part, long long split_stride, int S, 
 
 // ---- attention ----
 struct AttnArgs {
-  const float *Q;  // [2Bp][n_q*d_h]
+  const float *Q;  // fp32: [2Bp][n_q*d_h]
   KVRef kv;
   const int *pos_arr;  // length of sequence b = pos_arr[b] + 1
   Rows rows;
@@ -315,13 +315,9 @@ struct AttnArgs {
   int single;
   void *O;
   int ldo;
-  // bf16, not single: splits of up to 1024 pages in workgroups of eight waves
-  // (else up to 128 pages in workgroups of four)
-  int wide;
-  // bf16 decode: the queries and the cache append are computed by the
-  // attention kernel itself from the QKV projection's split-K slabs (fin),
-  // exactly as k_qkv_finish would (one launch fewer); Q is then not read
-  int fused;
+  // bf16: the queries and the cache append are computed by the attention
+  // kernel itself from the QKV projection's split-K slabs, exactly as
+  // k_qkv_finish would (one launch fewer); Q is then not read
   QKVFinish fin;
 };
 hipError_t launch_attn_decode(const AttnArgs &a, hipStream_t st);
