@@ -66,8 +66,9 @@ constexpr int kMixChunk = 4096;
 constexpr int kPackRows = 8192;
 // Average rows per expert from which a prompt pass runs the experts' products
 // as 128-row tiles instead of streaming each expert's weights past 32 rows at
-// a time.
-constexpr int kExpertTileRows = 16;
+// a time.  64 experts of 1408, whole pass of one layer: 19 rows each 571 us
+// tiled and 537 streamed, 31 rows 614 and 682.
+constexpr int kExpertTileRows = 24;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 int round16(int x) { return (x + 15) / 16 * 16; }
@@ -1192,9 +1193,11 @@ dbt_status copy_rows(float *dst, const float *src, int B, int d, hipStream_t st)
   return DBT_OK;
 }
 
-// Branch-only pass over all layers (ungrouped pass 2 and the boundary).
+// Branch-only pass over all layers (ungrouped pass 2 and the boundary), then
+// the output matrix over the branch rows, or over every path's rows where the
+// primary's normed final rows wait in Xn (with_primary).
 dbt_status branch_pass(dbt_model *m, dbt_kv *kv, int B, int Bp, const Sinks &k, hipStream_t st,
-                       const dbt_step_out *out = nullptr, const HIn *hin = nullptr) {
+                       const dbt_step_out *out = nullptr, const HIn *hin = nullptr, bool with_primary = false) {
   LayerCall lc{};
   lc.out = out;
   lc.ho = k.ho;
@@ -1210,7 +1213,7 @@ dbt_status branch_pass(dbt_model *m, dbt_kv *kv, int B, int Bp, const Sinks &k, 
     dbt_status s = run_layer(m, kv, l, lc, st);
     if (s) return s;
   }
-  if (m->cfg.vocab > 0) return lm_head(m, lc.rows, k, st);
+  if (m->cfg.vocab > 0) return lm_head(m, with_primary ? Rows{B, Bp, 0, 1 + nb} : lc.rows, k, st);
   return DBT_OK;
 }
 
@@ -1479,8 +1482,11 @@ dbt_status dbt_decode_step_ungrouped(dbt_model *m, dbt_kv *kv, const dbt_step_in
   return DBT_OK;
 }
 
-// The boundary after a prefill whose primary logits and states are at k.
-static dbt_status boundary_impl(dbt_model *m, dbt_kv *kv, int B, dbt_step_out *out, const Sinks &k, hipStream_t st) {
+// The boundary after a prefill whose primary logits are at k, or, as part of
+// the prefill call (with_primary), still to be computed: the output matrix is
+// then read once for every path.
+static dbt_status boundary_impl(dbt_model *m, dbt_kv *kv, int B, dbt_step_out *out, const Sinks &k, bool with_primary,
+                                hipStream_t st) {
   dbt_status s;
   const dbt_config &cf = m->cfg;
   const Layout &L = m->L;
@@ -1491,7 +1497,7 @@ static dbt_status boundary_impl(dbt_model *m, dbt_kv *kv, int B, dbt_step_out *o
   const Rows br{B, Bp, 1, n_branches(cf)};
   HIPCHK(launch_embed(m->at<int>(L.btok), cf.vocab, m->w.emb1, m->w.emb2, m->w.emb_norm, m->layers[0].attn_norm, cf.rms_eps,
                       cf.d_model, cf.dtype, br, m->at<float>(L.S), m->p(L.Xn), cf.d_model, st));
-  if ((s = branch_pass(m, kv, B, Bp, k, st))) return s;
+  if ((s = branch_pass(m, kv, B, Bp, k, st, nullptr, nullptr, with_primary))) return s;
   m->bnd_kv = nullptr;
   if (out) {
     if ((s = readout(m, B, Bp, true, out, k, st))) return s;
@@ -1576,12 +1582,12 @@ dbt_status dbt_prefill(dbt_model *m, dbt_kv *kv, const int32_t *tokens, const in
   if (cf.vocab > 0) {
     HIPCHK(launch_rmsnorm_rows(m->at<float>(L.slast), m->w.final_norm, cf.rms_eps, d, cf.dtype, Rows{batch, 0, 0, 1},
                                m->p(L.Xn), d, st));
-    if ((s = lm_head(m, Rows{batch, Bp, 0, 1}, k, st))) return s;
+    if (!run_boundary && (s = lm_head(m, Rows{batch, Bp, 0, 1}, k, st))) return s;
   }
   if (k.copy_h1 && (s = copy_rows(out->h1_out, m->at<float>(L.slast), batch, d, st))) return s;
   m->bnd_kv = kv;
   m->bnd_batch = batch;
-  if (run_boundary) return boundary_impl(m, kv, batch, out, k, st);
+  if (run_boundary) return boundary_impl(m, kv, batch, out, k, true, st);
   if (out && (s = readout(m, batch, Bp, false, out, k, st))) return s;
   return DBT_OK;
 }
@@ -1593,7 +1599,7 @@ dbt_status dbt_boundary(dbt_model *m, dbt_kv *kv, int32_t batch, dbt_step_out *o
     return fail(DBT_ERR_STATE, "boundary must directly follow dbt_prefill on the same cache and batch");
   hipStream_t st = (hipStream_t)stream;
   if ((s = ensure_device(m, st))) return s;
-  return boundary_impl(m, kv, batch, out, make_sinks(m, batch, round16(batch), out, false, true), st);
+  return boundary_impl(m, kv, batch, out, make_sinks(m, batch, round16(batch), out, false, true), false, st);
 }
 
 dbt_status dbt_stage_timing(dbt_model *m, int32_t stage, int32_t enable) {
