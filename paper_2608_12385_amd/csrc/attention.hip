@@ -195,21 +195,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     // Lazy rescaling: a row's base m moves only when the pair's maximum
     // exceeds it by more than kLazyMargin (base 2), so the exponentials stay
     // <= 2^kLazyMargin and the running sums are rescaled a few times per row
-    // (every pair a wave takes holds a valid position, so m is finite after
-    // its first pair; the wave merge below works for any common base).
+    // (the wave merge below works for any common base).
     const bool grow = mt > m_run + kLazyMargin;
     const float m_new = grow ? mt : m_run;
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;  // no score above -inf yet
     float p[8];
     float ps = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      p[i] = __builtin_amdgcn_exp2f(sc[i] - m_new);
+      p[i] = __builtin_amdgcn_exp2f(sc[i] - m_use);
       ps += p[i];
     }
     // rescale the running sums only when some row's base moved (wave-uniform
     // test; a factor of exactly 1 for the other rows)
     if (__any(grow)) {
-      const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+      const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
       l_run *= corr;
 #pragma unroll
       for (int c = 0; c < 8; ++c) acc[c] = acc[c] * corr;
@@ -448,7 +448,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     float o = 0.f, l = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      if (sm[w][qr] != -INFINITY) {
+      // (a wave whose scores were all NaN has no maximum, but its sums are NaN
+      // and count; one without pages has sums of zero)
+      if (sm[w][qr] != -INFINITY || sl[w][qr] != 0.f) {
         const float f = exp2f(sm[w][qr] - mx);
         o += so[w][dh][qr] * f;
         l += sl[w][qr] * f;

@@ -23,6 +23,8 @@ struct F32Merge {
   float o[kWavesF32Attn][16 * NC][17];
   float m[kWavesF32Attn][16], l[kWavesF32Attn][16];
   // the sums of query row qr over all waves, relative to their maximum mx
+  // (a wave whose scores were all NaN has no maximum either, but its sums are
+  // NaN and count; one without keys has sums of zero)
   __device__ __forceinline__ void merged(int qr, int dh, float &os, float &ls, float &mx) const {
     mx = -INFINITY;
 #pragma unroll
@@ -30,7 +32,7 @@ struct F32Merge {
     os = ls = 0.f;
 #pragma unroll
     for (int w = 0; w < kWavesF32Attn; ++w)
-      if (m[w][qr] != -INFINITY) {
+      if (m[w][qr] != -INFINITY || l[w][qr] != 0.f) {
         const float f = exp2f(m[w][qr] - mx);
         os += o[w][dh][qr] * f;
         ls += l[w][qr] * f;
@@ -40,7 +42,7 @@ struct F32Merge {
 
 // qp: this lane's query row (row r = lane & 15; live = false: a stand-in whose
 // results are not used); it sees keys 0 .. seen - 1.  Pages [pb, pe) of ptab;
-// positions >= valid hold no key (stale slots).  Ends with a barrier.
+// positions >= valid hold no key (stale slots).   Ends with a barrier.
 template <int NC>
 __device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool live, int seen, int valid,
                                          const float *kbase, const float *vbase, const int *ptab, int pb, int pe,

@@ -1,0 +1,54 @@
+"""Keys that are not finite, on the GPU: a NaN key reaches the result of every
+row that sees it, however the pages are dealt to waves and splits."""
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_util import fill_cache, make_session, to_np
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def layer_shape(dtype, nq, nkv, dh):
+    return synth.ModelShape(n_layers=1, d_model=128, n_q_heads=nq, n_kv_heads=nkv, head_dim=dh, d_ff=128, vocab=0,
+                            dtype=dtype, has_embeddings=False, std=0.1, coupling_std=0.5)
+
+
+# one or two pages of NaN keys: the wave that reads them reads no other page
+# (fp32: a page per wave and turn; bf16: a pair of pages), reads them after or
+# before others, or in another split; half a pair; and (last) the workgroup of
+# a whole sequence
+@pytest.mark.parametrize("dtype,nkv,batch,length,bad", [
+    ("f32", 2, 3, 100, [2]),
+    ("f32", 2, 3, 300, [0]),
+    ("f32", 2, 3, 300, [15]),
+    ("f32", 2, 3, 1200, [70]),
+    ("f32", 2, 3, 112, [6]),
+    ("bf16", 2, 3, 100, [3]),
+    ("bf16", 2, 3, 100, [2, 3]),
+    ("bf16", 2, 3, 383, [8, 9]),
+    ("bf16", 2, 3, 700, [30, 31]),
+    ("bf16", 2, 3, 273, [17]),
+    ("bf16", 64, 4, 200, [4, 5]),
+])
+def test_nan_keys_reach_the_result(dtype, nkv, batch, length, bad):
+    shape = layer_shape(dtype, nkv, nkv, 128 if dtype == "bf16" else 32)
+    sess = make_session(shape, synth.make_weights(shape), max_batch=batch, max_pos=length + 4)
+    fill_cache(sess, None, shape, [length] * batch)
+    wt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    h = synth.make_hidden(shape, batch)
+    clean = {k: to_np(v).copy() for k, v in sess.decode(h1=h[0], h2=h[1]).items()}
+    from paper_2608_12385_amd import binding
+    for b in range(batch):
+        binding.dbt_kv_truncate(sess.kv, b, length)
+    pool = sess.k_pages.view(wt).view(1, -1, nkv, 16 * shape.head_dim)
+    for page in bad:
+        pool[0, binding.dbt_kv_pages(sess.kv, 1)[page]] = float("nan")
+    got = {k: to_np(v) for k, v in sess.decode(h1=h[0], h2=h[1]).items()}
+    for key in ("h1_out", "h2_out"):
+        assert bool(np.isnan(got[key][1]).all()), key
+        for b in range(batch):
+            if b != 1:
+                np.testing.assert_array_equal(got[key][b], clean[key][b], err_msg=key)
+    sess.close()
