@@ -79,6 +79,7 @@ __device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool
   if (j < pe) load(ptab[j]);
   for (; j < pe; j += kWavesF32Attn) {
     floatx4 s = {0.f, 0.f, 0.f, 0.f};
+    if (16 * NC > DH && 16 * (NC - 1) + 4 * gq >= DH) k[NC - 1] = floatx4{0.f, 0.f, 0.f, 0.f};  // (infinity * 0)
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll

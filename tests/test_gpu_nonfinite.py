@@ -1,10 +1,13 @@
-"""Keys that are not finite, on the GPU: a NaN key reaches the result of every
-row that sees it, however the pages are dealt to waves and splits."""
+"""Keys and values that are not finite, on the GPU: a NaN key reaches the
+result of every row that sees it, however the pages are dealt to waves and
+splits; a score of -inf is a probability of zero; rows before a position never
+see it."""
 import numpy as np
 import pytest
 
 import synth
-from tests.gpu_util import fill_cache, make_session, to_np
+from oracle import Oracle
+from tests.gpu_util import fill_cache, make_session, row_err, to_np
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -51,4 +54,43 @@ def test_nan_keys_reach_the_result(dtype, nkv, batch, length, bad):
         for b in range(batch):
             if b != 1:
                 np.testing.assert_array_equal(got[key][b], clean[key][b], err_msg=key)
+    sess.close()
+
+
+# a page of keys with an infinite first dimension: scores of +inf (not a
+# number after the softmax) or of -inf (no weight), as the sign of the query's
+# first dimension says; head sizes that are and are not whole 16-dimension
+# pieces, a wave that reads this page alone
+@pytest.mark.parametrize("dtype,dh,length", [("f32", 12, 100), ("f32", 16, 100), ("f32", 20, 300), ("f32", 100, 70),
+                                             ("bf16", 128, 150)])
+def test_infinite_keys(dtype, dh, length):
+    shape, B = layer_shape(dtype, 1, 1, dh), 12
+    W = synth.make_weights(shape)
+    sess, orc = make_session(shape, W, max_batch=B, max_pos=length + 4), Oracle(shape, W.values)
+    wt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    for b in range(B):
+        (k, kb), (v, vb) = synth.make_kv(shape, 0, b, length)
+        k = k.copy()
+        k[32:64, 0, 0] = np.inf  # pages 2 and 3
+        orc.kv_fill(b, length, [k], [v])
+        sess.reserve_fill(b, [kb if kb is not None else k], [vb if vb is not None else v])
+        from paper_2608_12385_amd import binding
+        pages = binding.dbt_kv_pages(sess.kv, b)
+        pool = sess.k_pages.view(wt).view(1, -1, 1, 16, dh)
+        pool[0, pages[2], 0, :, 0] = pool[0, pages[3], 0, :, 0] = float("inf")
+    h = synth.make_hidden(shape, B)
+    with np.errstate(all="ignore"):
+        outs = orc.decode_step(h1=h[0], h2=h[1])
+    t = sess.decode(h1=h[0], h2=h[1])
+    seen = set()
+    for key, ref in (("h1_out", "h1"), ("h2_out", "h2")):
+        want, got = np.stack([o[ref] for o in outs]), to_np(t[key])
+        for b in range(B):
+            finite = bool(np.isfinite(want[b]).all())
+            seen.add(finite)
+            if finite:
+                assert row_err(got[b:b + 1], want[b:b + 1]).max() <= (2e-2 if dtype == "bf16" else 1e-5), (key, b)
+            else:
+                assert bool(np.isnan(want[b]).any()) and bool(np.isnan(got[b]).all()), (key, b)
+    assert seen == {True, False}
     sess.close()
