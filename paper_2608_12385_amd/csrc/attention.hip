@@ -490,7 +490,7 @@ __global__ __launch_bounds__(64 * kWavesF32Attn) void k_attn_decode_f32(AttnArgs
   const int r = threadIdx.x & 15;
   __shared__ F32Merge<NC> mg;
   const float *qp = a.Q + row_of(r < nrows ? r : 0, 0);
-  attn_f32<NC>(mg, qp, r < nrows, len, len, (const float *)a.kv.k, (const float *)a.kv.v,
+  attn_f32<NC, false>(mg, qp, r < nrows, len, len, len, (const float *)a.kv.k, (const float *)a.kv.v,
                a.kv.page_table + (size_t)b * a.kv.mpps, pb, pe, n_kv, g, DH);
   const size_t obase = (((size_t)b * n_kv + g) * a.max_splits + split) * 16;
   for (int e = threadIdx.x; e < nrows * DH; e += 64 * kWavesF32Attn) {

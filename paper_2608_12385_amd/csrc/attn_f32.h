@@ -10,6 +10,10 @@
 // of the value sum O^T = V^T P^T when its j-th multiply takes key 4 gq + j of
 // every group: V pages are dimension-major, so lane (r, gq) reads the four keys
 // of dimension 16 c + r as one float4.  No operand passes through LDS.
+//
+// Keys and values may be infinite or not a number: a key that a row does not
+// see (after its position, stale, or of another row) leaves no trace in it,
+// and one that it sees does, whichever wave reads its page.
 #pragma once
 #include "common.h"
 
@@ -42,9 +46,10 @@ struct F32Merge {
 
 // qp: this lane's query row (row r = lane & 15; live = false: a stand-in whose
 // results are not used); it sees keys 0 .. seen - 1.  Pages [pb, pe) of ptab;
-// positions >= valid hold no key (stale slots).   Ends with a barrier.
-template <int NC>
-__device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool live, int seen, int valid,
+// positions >= valid hold no key (stale slots).  CAUSAL: rows see different
+// numbers of keys, the fewest `first`.  Ends with a barrier.
+template <int NC, bool CAUSAL>
+__device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool live, int seen, int first, int valid,
                                          const float *kbase, const float *vbase, const int *ptab, int pb, int pe,
                                          int n_kv, int g, int DH) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -115,11 +120,35 @@ __device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool
         for (int i = 0; i < 4; ++i)
           if (p0 + i >= valid) vc[c][i] = 0.f;
     }
+    bool apart = false;  // a value that some row of the tile must not see is not finite
+    if (CAUSAL && 16 * j + 16 > first) {
+      bool odd = false;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      acc[c] = acc[c] * corr;
+      for (int c = 0; c < NC; ++c)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[c][i], p[i], acc[c], 0, 0, 0);
+        for (int i = 0; i < 4; ++i) odd |= !(fabsf(vc[c][i]) < INFINITY);
+      apart = __any(odd);
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c] = acc[c] * corr;
+    if (!apart) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[c][i], p[i], acc[c], 0, 0, 0);
+    } else {  // row by row: its keys only, for a probability of zero does not hide such a value
+#pragma unroll 1
+      for (int row = 0; row < 16; ++row) {
+        const int see = __shfl(seen, row, 64);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          floatx4 o = acc[c];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            o = __builtin_amdgcn_mfma_f32_16x16x4f32(p0 + i < see ? vc[c][i] : 0.f, p[i], o, 0, 0, 0);
+          if (r == row) acc[c] = o;
+        }
+      }
     }
   }
   l_run += __shfl_xor(l_run, 16, 64);

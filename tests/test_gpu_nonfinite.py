@@ -94,3 +94,32 @@ def test_infinite_keys(dtype, dh, length):
                 assert bool(np.isnan(want[b]).any()) and bool(np.isnan(got[b]).all()), (key, b)
     assert seen == {True, False}
     sess.close()
+
+
+def test_prompt_rows_before_an_infinite_value():
+    """fp32 prompt whose token at position 5 has infinite values in layer 0:
+    the rows before it in the same page are those of the prompt without it."""
+    dh, d, L = 32, 64, 40
+    shape = synth.ModelShape(n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1, head_dim=dh, d_ff=96, vocab=32,
+                             dtype="f32", has_embeddings=True, std=0.2, coupling_std=0.5)
+    W = synth.make_weights(shape)
+    mark = 31
+    W.values["E1"][:, 0] = 0.0
+    W.values["E1"][mark, 0] = 4.0
+    W.values["L0.W_V"][:, 0] = 3e38  # times 4 / rms: infinite for the marked token, zero for every other
+    prompt = np.arange(L, dtype=np.int32) % 30
+    marked = prompt.copy()
+    marked[5] = mark
+    pages = []
+    for p in (prompt, marked):
+        sess = make_session(shape, W, max_batch=1, max_pos=L + 4, max_prompt=L)
+        sess.prefill([p], run_boundary=False)
+        from paper_2608_12385_amd import binding
+        first = binding.dbt_kv_pages(sess.kv, 0)[0]
+        k = sess.k_pages.view(torch.float32).view(2, -1, 16, dh)[1, first]
+        v = sess.v_pages.view(torch.float32).view(2, -1, dh, 16)[1, first].t()
+        pages.append((to_np(k).copy(), to_np(v).copy()))
+        sess.close()
+    for clean, got in zip(*pages):
+        assert bool(np.isfinite(clean).all()) and not bool(np.isfinite(got[5:]).any())
+        np.testing.assert_array_equal(got[:5], clean[:5])
