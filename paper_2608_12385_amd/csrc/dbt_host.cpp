@@ -1524,6 +1524,7 @@ dbt_status dbt_prefill(dbt_model *m, dbt_kv *kv, const int32_t *tokens, const in
   if (need > (int)kv->free_pages.size()) return fail(DBT_ERR_NO_PAGES, "need %d free pages, have %zu", need, kv->free_pages.size());
   hipStream_t st = (hipStream_t)stream;
   if ((s = ensure_device(m, st))) return s;  // before any state changes
+  m->bnd_kv = nullptr;  // (a boundary needs a prefill that went through)
   for (int b = 0; b < batch; ++b) {  // pages for every sequence first, in batch order
     const int np = (h_prompt_lens[b] + kPage - 1) / kPage;
     for (int i = 0; i < np; ++i) {
@@ -1585,10 +1586,10 @@ dbt_status dbt_prefill(dbt_model *m, dbt_kv *kv, const int32_t *tokens, const in
     if (!run_boundary && (s = lm_head(m, Rows{batch, Bp, 0, 1}, k, st))) return s;
   }
   if (k.copy_h1 && (s = copy_rows(out->h1_out, m->at<float>(L.slast), batch, d, st))) return s;
-  m->bnd_kv = kv;
-  m->bnd_batch = batch;
   if (run_boundary) return boundary_impl(m, kv, batch, out, k, true, st);
   if (out && (s = readout(m, batch, Bp, false, out, k, st))) return s;
+  m->bnd_kv = kv;
+  m->bnd_batch = batch;
   return DBT_OK;
 }
 

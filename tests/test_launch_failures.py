@@ -1,0 +1,115 @@
+"""Launches that fail, on the CPU: the library runs in a child process on a
+stand-in for the HIP runtime (fake_hip.c) that counts launches and fails the
+one it is told to.  What a failing call leaves behind must not be used."""
+import ctypes
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+pytestmark = pytest.mark.skipif(shutil.which("gcc") is None, reason="gcc not available")
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "fake_hip.c")],
+                   check=True)
+    return so
+
+
+def run_child(fake, name):
+    pre = " ".join(x for x in (fake, os.environ.get("LD_PRELOAD", "")) if x)
+    r = subprocess.run([sys.executable, __file__, name, fake], capture_output=True, text=True, cwd=ROOT, timeout=300,
+                       env=dict(os.environ, LD_PRELOAD=pre, PYTHONPATH=ROOT))
+    assert r.returncode == 0 and "done" in r.stdout, (r.stdout + r.stderr)[-3000:]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_no_boundary_after_a_failed_prefill(fake, dtype):
+    run_child(fake, "boundary_" + dtype)
+
+
+# ---------------------------------------------------------------------------
+# in the child
+# ---------------------------------------------------------------------------
+
+FAKE = 1 << 40  # placeholder device address, never dereferenced
+
+
+class Program:
+    def __init__(self, dtype="f32", max_batch=4, **kw):
+        from paper_2608_12385_amd import binding as B
+        self.B = B
+        size = dict(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=256, vocab=512)
+        if dtype == "f32":
+            size = dict(d_model=48, n_q_heads=4, n_kv_heads=2, head_dim=16, d_ff=96, vocab=64)
+        cfg = B.dbt_config(n_layers=2, dtype=B.DBT_BF16 if dtype == "bf16" else B.DBT_F32, has_embeddings=1,
+                           max_batch=max_batch, max_pos=256, max_prompt=64, rms_eps=1e-5, rope_theta=1e4,
+                           **dict(size, **kw))
+        self.layers = (B.dbt_layer_weights * cfg.n_layers)()
+        for l in range(cfg.n_layers):
+            for f, _ in B.dbt_layer_weights._fields_:
+                setattr(self.layers[l], f, FAKE)
+        w = B.dbt_weights(emb1=FAKE, emb2=FAKE, emb_norm=FAKE, final_norm=FAKE, lm_head=FAKE, h_layers=self.layers)
+        self.model = B.dbt_create(cfg, w, FAKE)
+        self.out = B.dbt_step_out(logits1=FAKE, logits2=FAKE, alpha=FAKE, next_token=FAKE, h1_out=FAKE, h2_out=FAKE)
+        self.mpps = 16
+
+    def cache(self, pages=64, nseq=4):
+        """A cache and its page table (host memory: the stand-in writes it)."""
+        table = (ctypes.c_int * (nseq * self.mpps))(*([-1] * (nseq * self.mpps)))
+        return self.B.dbt_kv_create(self.model, FAKE, FAKE, pages, ctypes.addressof(table), self.mpps), table
+
+    def status(self, fn, *a):
+        try:
+            fn(*a)
+        except self.B.DbtError as e:
+            return e.status
+        return 0
+
+
+def boundary(fk, dtype):
+    """A boundary is valid directly after a prefill without one that succeeded,
+    and never after one that failed: its logits, final states and kept rows
+    are not those of the prompts."""
+    p = Program(dtype)
+    B, lens = p.B, [5, 20, 3]
+
+    def prefill(kv, run):
+        return p.status(B.dbt_prefill, p.model, kv, FAKE, lens, 3, run, p.out, 0)
+
+    def fresh(kv):
+        for b in range(3):
+            B.dbt_kv_truncate(kv, b, 0)
+
+    (one, _t1), (two, _t2) = p.cache(), p.cache()
+    assert prefill(one, 0) == 0 and p.status(B.dbt_boundary, p.model, one, 3, p.out, 0) == 0
+    assert p.status(B.dbt_boundary, p.model, one, 3, p.out, 0) == 4
+    for run in (1, 0):
+        fresh(one)
+        fk.fake_reset(-1)
+        assert prefill(one, run) == 0
+        n = fk.fake_launches()
+        assert n > 10
+        for at in range(n):
+            fresh(one)
+            fresh(two)
+            fk.fake_reset(-1)
+            assert prefill(two, 0) == 0  # a boundary of the other cache is due, and lost with its rows
+            fk.fake_reset(at)
+            assert prefill(one, run) == 6, (run, at)
+            fk.fake_reset(-1)
+            for kv in (one, two):
+                assert p.status(B.dbt_boundary, p.model, kv, 3, p.out, 0) == 4, (run, at, kv == one)
+
+
+if __name__ == "__main__":
+    fk = ctypes.CDLL(sys.argv[2])
+    fk.fake_kernel.restype = ctypes.c_char_p
+    boundary(fk, sys.argv[1].split("_")[1])
+    print("done")
