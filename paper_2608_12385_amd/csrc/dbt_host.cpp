@@ -413,47 +413,55 @@ dbt_status flush(dbt_kv *kv, const int *h_pos, int npos, hipStream_t st, StepBeg
     fold->n_pos = fold->n_pt = 0;
     fold->b0 = 0;
   }
+  // The list itself is left as it is until everything is enqueued: after a
+  // failure the next call sends it again.
+  const std::vector<dbt_kv::Upd> &up = kv->pending;
+  auto run_end = [&](size_t i) {  // end of the run of consecutive pages from entry i
+    size_t e = i + 1;
+    while (e < up.size() && up[e].b == up[i].b && up[e].slot == up[i].slot + (int)(e - i) &&
+           up[e].page == up[i].page + (int)(e - i))
+      ++e;
+    return e;
+  };
   PageRuns pr;
   pr.n = 0;
-  size_t single = 0;  // single entries, moved to the front of the list
-  for (size_t i = 0; i < kv->pending.size();) {
-    const dbt_kv::Upd u = kv->pending[i];
-    size_t e = i + 1;
-    while (e < kv->pending.size() && kv->pending[e].b == u.b && kv->pending[e].slot == u.slot + (int)(e - i) &&
-           kv->pending[e].page == u.page + (int)(e - i))
-      ++e;
+  size_t singles = 0;
+  for (size_t i = 0, e; i < up.size(); i = e) {
+    e = run_end(i);
     if (e == i + 1) {
-      kv->pending[single++] = u;
-    } else {
-      pr.b[pr.n] = u.b;
-      pr.slot[pr.n] = u.slot;
-      pr.page[pr.n] = u.page;
-      pr.count[pr.n] = (int)(e - i);
-      if (++pr.n == kPageRuns) {
-        HIPCHK(launch_page_runs(pr, kv->page_table, kv->mpps, st));
-        pr.n = 0;
-      }
+      ++singles;
+      continue;
     }
-    i = e;
+    pr.b[pr.n] = up[i].b;
+    pr.slot[pr.n] = up[i].slot;
+    pr.page[pr.n] = up[i].page;
+    pr.count[pr.n] = (int)(e - i);
+    if (++pr.n == kPageRuns) {
+      HIPCHK(launch_page_runs(pr, kv->page_table, kv->mpps, st));
+      pr.n = 0;
+    }
   }
   HIPCHK(launch_page_runs(pr, kv->page_table, kv->mpps, st));
-  size_t ip = 0;
+  size_t ip = 0;  // entries looked at
   int ipos = 0;
-  while (ip < single || ipos < npos) {
+  while (singles > 0 || ipos < npos) {
     StepBegin sb;
     std::memset(&sb, 0, sizeof sb);
     sb.b0 = ipos;
     sb.n_pos = std::min(64, npos - ipos);
     for (int i = 0; i < sb.n_pos; ++i) sb.pos[i] = h_pos[ipos + i];
     ipos += sb.n_pos;
-    sb.n_pt = (int)std::min<size_t>(64, single - ip);
-    for (int i = 0; i < sb.n_pt; ++i) {
-      sb.pt_b[i] = kv->pending[ip + i].b;
-      sb.pt_slot[i] = kv->pending[ip + i].slot;
-      sb.pt_page[i] = kv->pending[ip + i].page;
+    while (sb.n_pt < 64 && singles > 0) {
+      const size_t e = run_end(ip);
+      if (e == ip + 1) {
+        sb.pt_b[sb.n_pt] = up[ip].b;
+        sb.pt_slot[sb.n_pt] = up[ip].slot;
+        sb.pt_page[sb.n_pt++] = up[ip].page;
+        --singles;
+      }
+      ip = e;
     }
-    ip += sb.n_pt;
-    if (fold && ip >= single && ipos >= npos) {
+    if (fold && singles == 0 && ipos >= npos) {
       *fold = sb;
       break;
     }

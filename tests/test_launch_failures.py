@@ -34,6 +34,10 @@ def test_no_boundary_after_a_failed_prefill(fake, dtype):
     run_child(fake, "boundary_" + dtype)
 
 
+def test_page_table_after_failed_launches(fake):
+    run_child(fake, "pages")
+
+
 # ---------------------------------------------------------------------------
 # in the child
 # ---------------------------------------------------------------------------
@@ -108,8 +112,42 @@ def boundary(fk, dtype):
                 assert p.status(B.dbt_boundary, p.model, kv, 3, p.out, 0) == 4, (run, at, kv == one)
 
 
+def pages(fk):
+    """Page-table entries that a failing launch kept back are written by the
+    next call: runs of consecutive pages and single entries, more of both than
+    one launch takes."""
+    nseq, mpps = 400, 16
+    for at in range(12):
+        p = Program("f32", max_batch=nseq)
+        B = p.B
+        kv, table = p.cache(nseq * 4, nseq)
+        for b in range(nseq):  # one, two and three pages
+            B.dbt_kv_reserve(kv, b, 16 * (1 + b % 3))
+        for b in range(0, nseq, 5):  # freed pages: later rows are runs and singles mixed
+            B.dbt_kv_truncate(kv, b, 0)
+        for b in range(0, nseq, 10):
+            B.dbt_kv_reserve(kv, b, 64)
+        fk.fake_reset(at)
+        first = p.status(B.dbt_kv_fill, kv, 0, 0, 0, 1, FAKE, FAKE, 0)
+        failed = at < fk.fake_launches()
+        assert first == (6 if failed else 0)
+        fk.fake_reset(-1)
+        if failed:
+            assert p.status(B.dbt_kv_fill, kv, 0, 0, 0, 1, FAKE, FAKE, 0) == 0
+        for b in range(nseq):
+            want = B.dbt_kv_pages(kv, b)
+            assert list(table[b * mpps:b * mpps + len(want)]) == want, (at, b)
+        if not failed:
+            assert at > 4, at  # several launches of each kind were tried
+            return
+    raise AssertionError("the flush never went through")
+
+
 if __name__ == "__main__":
     fk = ctypes.CDLL(sys.argv[2])
     fk.fake_kernel.restype = ctypes.c_char_p
-    boundary(fk, sys.argv[1].split("_")[1])
+    if sys.argv[1] == "pages":
+        pages(fk)
+    else:
+        boundary(fk, sys.argv[1].split("_")[1])
     print("done")
