@@ -1046,49 +1046,69 @@ dbt_status load_inputs(dbt_model *m, dbt_kv *kv, const dbt_step_in *in, const in
 }
 
 // Where a call leaves its logits and states.  An output array takes them
-// straight from the kernel that computes them when it is 16-byte aligned;
-// otherwise (or with no array) they go to the workspace, and the array is
-// filled by a copy at the end of the call.
+// straight from the kernel that computes them when it is 16-byte aligned and
+// shares no memory with another output; otherwise (or with no array) they go to
+// the workspace, and the array is filled by a copy at the end of the call
+// (arrays that overlap then hold what the last copy leaves: the readout's
+// outputs, logits1, logits2, h1_out, h2_out in this order).
 struct Sinks {
   const float *z[4];  // logits of path j, row b at z[j] + b*V
   bool copy_z1, copy_z2, copy_h1, copy_h2;
   HOut ho;
 };
 
-bool overlap(const void *a, size_t na, const void *b, size_t nb) {
-  return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+struct Span {
+  const void *p;
+  size_t bytes;
+};
+
+bool overlap(const Span &a, const Span &b) {
+  return a.p && b.p && (uintptr_t)a.p < (uintptr_t)b.p + b.bytes && (uintptr_t)b.p < (uintptr_t)a.p + a.bytes;
 }
 
 // direct1 / direct2: whether the primary's / the branches' outputs may leave
-// the call early (every later read of the call is of other memory).
-Sinks make_sinks(const dbt_model *m, int B, int Bp, const dbt_step_out *out, bool direct1, bool direct2) {
+// the call early (every later read of the call is of other memory).  late: an
+// input that is still read when the first states leave.
+Sinks make_sinks(const dbt_model *m, int B, int Bp, const dbt_step_out *out, bool direct1, bool direct2,
+                 const Span &late = Span{}) {
   const dbt_config &cf = m->cfg;
   const int nb = n_branches(cf);
   const size_t V = cf.vocab, zrow = (size_t)B * V * 4, hrow = (size_t)B * cf.d_model * 4;
   Sinks k{};
   for (int j = 0; j <= nb; ++j) k.z[j] = m->at<float>(m->L.logits) + (size_t)j * Bp * V;
   if (!out) return k;
-  auto fits = [](const void *p) { return p && (uintptr_t)p % 16 == 0; };
-  const bool zapart = !overlap(out->logits1, zrow, out->logits2, zrow * nb);
-  const bool hapart = !overlap(out->h1_out, hrow, out->h2_out, hrow * nb);
+  const size_t rows = (size_t)cf.n_layers * B * 4, k1 = rows * cf.top_k1, k2 = rows * (cf.replay ? cf.top_k1 : cf.top_k2),
+               re = rows * cf.n_experts;
+  const Span all[] = {{out->logits1, zrow}, {out->logits2, zrow * nb}, {out->h1_out, hrow}, {out->h2_out, hrow * nb},
+                      {out->alpha, (size_t)B * 4}, {out->next_token, (size_t)B * 4}, {out->route_idx1, k1},
+                      {out->route_idx2, k2}, {out->route_w1, k1}, {out->route_w2, k2}, {out->route_logits1, re},
+                      {out->route_logits2, re}, late};
+  auto fits = [&](const void *p) {  // one of the first four
+    if (!p || (uintptr_t)p % 16) return false;
+    for (const Span &a : all)
+      if (a.p == p)
+        for (const Span &b : all)
+          if (&a != &b && overlap(a, b)) return false;
+    return true;
+  };
   k.copy_z1 = V > 0 && out->logits1;
   k.copy_z2 = V > 0 && out->logits2;
   k.copy_h1 = out->h1_out != nullptr;
   k.copy_h2 = out->h2_out != nullptr;
   k.ho.B = B;
-  if (k.copy_z1 && direct1 && zapart && fits(out->logits1)) {
+  if (k.copy_z1 && direct1 && fits(out->logits1)) {
     k.z[0] = out->logits1;
     k.copy_z1 = false;
   }
-  if (k.copy_z2 && direct2 && zapart && fits(out->logits2)) {
+  if (k.copy_z2 && direct2 && fits(out->logits2)) {
     for (int j = 0; j < nb; ++j) k.z[1 + j] = out->logits2 + (size_t)j * B * V;
     k.copy_z2 = false;
   }
-  if (k.copy_h1 && direct1 && hapart && fits(out->h1_out)) {
+  if (k.copy_h1 && direct1 && fits(out->h1_out)) {
     k.ho.h1 = out->h1_out;
     k.copy_h1 = false;
   }
-  if (k.copy_h2 && direct2 && hapart && fits(out->h2_out)) {
+  if (k.copy_h2 && direct2 && fits(out->h2_out)) {
     k.ho.h2 = out->h2_out;
     k.copy_h2 = false;
   }
@@ -1546,12 +1566,12 @@ dbt_status dbt_prefill(dbt_model *m, dbt_kv *kv, const int32_t *tokens, const in
   const Layout &L = m->L;
   const int d = cf.d_model;
   const int Bp = round16(batch);
-  const Sinks k = make_sinks(m, batch, Bp, out, run_boundary != 0, true);
+  size_t off = 0, left = 0;
+  for (int b = 0; b < batch; ++b) left += h_prompt_lens[b];
+  const Sinks k = make_sinks(m, batch, Bp, out, run_boundary != 0, true, Span{tokens, left * sizeof(int)});
   // Packed passes over consecutive prompts: as few as the rows of the prompt
   // buffers allow, of about equal size.
   const Layout &Lp = m->Lp;
-  size_t off = 0, left = 0;
-  for (int b = 0; b < batch; ++b) left += h_prompt_lens[b];
   for (int b = 0; b < batch;) {
     const size_t passes = (left + Lp.pack_rows - 1) / Lp.pack_rows, share = (left + passes - 1) / passes;
     Pack pk;
