@@ -1570,26 +1570,28 @@ dbt_status dbt_prefill(dbt_model *m, dbt_kv *kv, const int32_t *tokens, const in
   for (int b = 0; b < batch; ++b) left += h_prompt_lens[b];
   const Sinks k = make_sinks(m, batch, Bp, out, run_boundary != 0, true, Span{tokens, left * sizeof(int)});
   // Packed passes over consecutive prompts: as few as the rows of the prompt
-  // buffers allow, of about equal size.
+  // buffers allow, of about equal size.  A prompt's own length chooses its
+  // attention kernel, so prompts of different kernels take passes of their own.
   const Layout &Lp = m->Lp;
+  auto shares = [&](int len) { return prompt_shares_pages(cf.n_q_heads, cf.n_kv_heads, len, cf.dtype); };
   for (int b = 0; b < batch;) {
     const size_t passes = (left + Lp.pack_rows - 1) / Lp.pack_rows, share = (left + passes - 1) / passes;
     Pack pk;
     pk.n = 0;
     pk.seq0 = b;
     pk.off[0] = 0;
-    int T = 0, longest = 0;
-    while (b < batch && pk.n < kPackSeqs && (pk.n == 0 || ((size_t)T < share && T + h_prompt_lens[b] <= Lp.pack_rows))) {
+    LayerCall lc{};
+    int T = 0;
+    while (b < batch && pk.n < kPackSeqs &&
+           (pk.n == 0 || ((size_t)T < share && T + h_prompt_lens[b] <= Lp.pack_rows && shares(h_prompt_lens[b]) == lc.tiles.shared))) {
+      lc.tiles.shared = shares(h_prompt_lens[b]);
       T += h_prompt_lens[b];
-      longest = std::max(longest, h_prompt_lens[b]);
       pk.off[++pk.n] = T;
       ++b;
     }
     left -= T;
     const Rows rows{T, T, 0, 1};
-    LayerCall lc{};
-    lc.tiles.tp = prompt_tile_positions(cf.n_q_heads, cf.n_kv_heads, longest, cf.dtype);
-    lc.tiles.long_prompt = prompt_is_long(longest);
+    lc.tiles.tp = prompt_tile_positions(cf.n_q_heads, cf.n_kv_heads, lc.tiles.shared);
     lc.tiles.tiles = m->at<PromptTile>(Lp.ptiles);
     HIPCHK(launch_prompt_plan(pk, lc.tiles.tp, m->at<PromptRow>(Lp.prow), m->at<PromptTile>(Lp.ptiles), &lc.tiles.ntiles, st));
     HIPCHK(launch_embed(tokens + off, cf.vocab, m->w.emb1, m->w.emb2, m->w.emb_norm, m->layers[0].attn_norm, cf.rms_eps, d,

@@ -334,13 +334,14 @@ struct PromptAttn {
   int ldo;
   const PromptTile *tiles;
   int ntiles;
-  int tp;           // positions per tile: prompt_tile_positions of the pass
-  int long_prompt;  // a prompt has more pages than the kernel that shares K/V holds ids for
+  bool shared;      // prompt_shares_pages of every prompt of the pass
+  int tp;           // positions per tile: prompt_tile_positions
 };
-// Query positions per workgroup for prompts of at most max_len positions
-// (n_q / n_kv query heads per KV head).
-int prompt_tile_positions(int n_q, int n_kv, int max_len, int dtype);
-bool prompt_is_long(int max_len);  // for PromptAttn::long_prompt
+// Whether a prompt of len positions (n_q / n_kv query heads per KV head) runs
+// the kernel whose sixteen waves share each page through LDS.
+bool prompt_shares_pages(int n_q, int n_kv, int len, int dtype);
+// Query positions per workgroup of the prompt kernels.
+int prompt_tile_positions(int n_q, int n_kv, bool shared);
 hipError_t launch_attn_prefill(const PromptAttn &a, hipStream_t st);
 
 // ---- cache fill ----

@@ -426,39 +426,35 @@ __global__ __launch_bounds__(64 * kWavesF32Attn) void k_attn_prefill_f32(PromptA
 
 }  // namespace
 
-// K/V shared by 16 waves through LDS when G divides 16 and the page ids of
-// the longest prompt fit: 256 query rows per workgroup; else 16 positions.
-bool prompt_is_long(int max_len) { return (max_len + 15) / 16 > kPrefillMaxPages; }
-
-int prompt_tile_positions(int n_q, int n_kv, int max_len, int dtype) {
-  const int G = n_q / n_kv;
-  return dtype == 1 && 16 % G == 0 && !prompt_is_long(max_len) ? 256 / G : 16;
+// K/V shared by 16 waves through LDS (256 query rows per workgroup) when G
+// divides 16 and the page ids of the prompt fit; else 16 positions.
+bool prompt_shares_pages(int n_q, int n_kv, int len, int dtype) {
+  return dtype == 1 && 16 % (n_q / n_kv) == 0 && (len + 15) / 16 <= kPrefillMaxPages;
 }
+
+int prompt_tile_positions(int n_q, int n_kv, bool shared) { return shared ? 256 / (n_q / n_kv) : 16; }
 
 hipError_t launch_attn_prefill(const PromptAttn &a, hipStream_t st) {
   const int G = a.n_q / a.kv.n_kv;
-  if (a.ntiles < 1 || !a.tiles) return hipErrorInvalidValue;
+  if (a.ntiles < 1 || !a.tiles || a.tp != prompt_tile_positions(a.n_q, a.kv.n_kv, a.shared)) return hipErrorInvalidValue;
   if (a.dtype == 1) {
     if (a.kv.d_h != 128 || G < 1 || G > 16 || a.ldq % 4) return hipErrorInvalidValue;
     const dim3 grid(a.ntiles, a.kv.n_kv);
-    // (G = 16: tiles of 16 positions fit both kernels; its longest prompts
-    // are told apart by the page ids)
-    if (a.tp == 256 / G && 16 % G == 0 && !a.long_prompt) {
+    if (a.shared) {
       switch (G) {
         case 1: hipLaunchKernelGGL(k_attn_prefill_wide<1>, grid, dim3(1024), 0, st, a); break;
         case 2: hipLaunchKernelGGL(k_attn_prefill_wide<2>, grid, dim3(1024), 0, st, a); break;
         case 4: hipLaunchKernelGGL(k_attn_prefill_wide<4>, grid, dim3(1024), 0, st, a); break;
         case 8: hipLaunchKernelGGL(k_attn_prefill_wide<8>, grid, dim3(1024), 0, st, a); break;
-        default: hipLaunchKernelGGL(k_attn_prefill_wide<16>, grid, dim3(1024), 0, st, a);
+        case 16: hipLaunchKernelGGL(k_attn_prefill_wide<16>, grid, dim3(1024), 0, st, a); break;
+        default: return hipErrorInvalidValue;
       }
-    } else if (a.tp == 16) {
-      hipLaunchKernelGGL(k_attn_prefill_bf16, grid, dim3(64 * G), 0, st, a);
     } else {
-      return hipErrorInvalidValue;
+      hipLaunchKernelGGL(k_attn_prefill_bf16, grid, dim3(64 * G), 0, st, a);
     }
     return hipGetLastError();
   }
-  if (a.tp != 16) return hipErrorInvalidValue;
+  if (a.shared) return hipErrorInvalidValue;
   const dim3 grid(a.ntiles, a.n_q), block(64 * kWavesF32Attn);
   switch ((a.kv.d_h + 15) / 16) {
     case 1: hipLaunchKernelGGL(k_attn_prefill_f32<1>, grid, block, 0, st, a); break;

@@ -1,6 +1,7 @@
-"""Launches that fail, on the CPU: the library runs in a child process on a
-stand-in for the HIP runtime (fake_hip.c) that counts launches and fails the
-one it is told to.  What a failing call leaves behind must not be used."""
+"""The library's launches, on the CPU: it runs in a child process on a stand-in
+for the HIP runtime (fake_hip.c) that names and counts launches and fails the
+one it is told to.  What a failing call leaves behind must not be used, and a
+prompt's length alone chooses its attention kernel."""
 import ctypes
 import os
 import shutil
@@ -38,6 +39,10 @@ def test_page_table_after_failed_launches(fake):
     run_child(fake, "pages")
 
 
+def test_prompt_attention_by_the_prompts_own_length(fake):
+    run_child(fake, "attention")
+
+
 # ---------------------------------------------------------------------------
 # in the child
 # ---------------------------------------------------------------------------
@@ -52,9 +57,9 @@ class Program:
         size = dict(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=256, vocab=512)
         if dtype == "f32":
             size = dict(d_model=48, n_q_heads=4, n_kv_heads=2, head_dim=16, d_ff=96, vocab=64)
-        cfg = B.dbt_config(n_layers=2, dtype=B.DBT_BF16 if dtype == "bf16" else B.DBT_F32, has_embeddings=1,
-                           max_batch=max_batch, max_pos=256, max_prompt=64, rms_eps=1e-5, rope_theta=1e4,
-                           **dict(size, **kw))
+        cfg = B.dbt_config(dtype=B.DBT_BF16 if dtype == "bf16" else B.DBT_F32, has_embeddings=1, max_batch=max_batch,
+                           rms_eps=1e-5, rope_theta=1e4,
+                           **dict(dict(size, n_layers=2, max_pos=256, max_prompt=64), **kw))
         self.layers = (B.dbt_layer_weights * cfg.n_layers)()
         for l in range(cfg.n_layers):
             for f, _ in B.dbt_layer_weights._fields_:
@@ -62,7 +67,7 @@ class Program:
         w = B.dbt_weights(emb1=FAKE, emb2=FAKE, emb_norm=FAKE, final_norm=FAKE, lm_head=FAKE, h_layers=self.layers)
         self.model = B.dbt_create(cfg, w, FAKE)
         self.out = B.dbt_step_out(logits1=FAKE, logits2=FAKE, alpha=FAKE, next_token=FAKE, h1_out=FAKE, h2_out=FAKE)
-        self.mpps = 16
+        self.mpps = (cfg.max_pos + 15) // 16
 
     def cache(self, pages=64, nseq=4):
         """A cache and its page table (host memory: the stand-in writes it)."""
@@ -143,11 +148,28 @@ def pages(fk):
     raise AssertionError("the flush never went through")
 
 
+def attention(fk):
+    """Prompts of more pages than the page-sharing kernel holds ids for (1024)
+    among shorter ones: each runs the kernel it runs alone."""
+    for heads, short_kernel in ((4, "wide"), (3, "bf16")):  # (3 heads per KV head never share pages)
+        p = Program("bf16", n_q_heads=heads, n_kv_heads=1, n_layers=1, max_pos=20000, max_prompt=20000)
+        kv, _table = p.cache(8000)
+        for lens, want in (([50, 7], [short_kernel]), ([16384], [short_kernel]), ([16385], ["bf16"]),
+                           ([50, 16385, 60, 70], [short_kernel, "bf16", short_kernel])):
+            if short_kernel == "bf16":
+                want = ["bf16"] * (1 if sum(lens) <= 20000 else 2)
+            for b in range(4):
+                p.B.dbt_kv_truncate(kv, b, 0)
+            fk.fake_reset(-1)
+            p.B.dbt_prefill(p.model, kv, FAKE, lens, len(lens), 0, p.out, 0)
+            names = [fk.fake_kernel(i).decode() for i in range(fk.fake_launches())]
+            got = ["wide" if "prefill_wide" in n else "bf16" for n in names if "k_attn_prefill" in n]
+            assert got == want, (heads, lens, got)
+
+
 if __name__ == "__main__":
     fk = ctypes.CDLL(sys.argv[2])
     fk.fake_kernel.restype = ctypes.c_char_p
-    if sys.argv[1] == "pages":
-        pages(fk)
-    else:
-        boundary(fk, sys.argv[1].split("_")[1])
+    what, _, arg = sys.argv[1].partition("_")
+    dict(boundary=boundary, pages=pages, attention=attention)[what](*([fk, arg] if arg else [fk]))
     print("done")
