@@ -87,7 +87,7 @@ struct Layout {
   bool glu = false;
   int fe = 0, fs = 0, amax = 0;
   GemmConfig g_sgu{1, 1, 1}, g_sd{1, 1, 1};
-  size_t moe_idx = 0, moe_tiles = 0, moe_ntiles = 0, moe_w = 0, moe_aslot = 0, moe_counts = 0, moe_offsets = 0, moe_arow = 0, moe_h = 0,
+  size_t moe_idx = 0, moe_logits = 0, moe_tiles = 0, moe_ntiles = 0, moe_w = 0, moe_aslot = 0, moe_counts = 0, moe_offsets = 0, moe_arow = 0, moe_h = 0,
          moe_y = 0, ret_idx = 0;
   size_t prow = 0, ptiles = 0;  // prompt passes: row map, attention tiles
   size_t rope = 0, pos = 0, S = 0, Xn = 0, Xh = 0, Q = 0, O = 0, P = 0, apart = 0, astat = 0,
@@ -236,7 +236,7 @@ Layout make_layout(const dbt_config *c, int rows_min = 0) {
   if (L.moe) {
     L.amax = L.rows_max * 8;
     L.moe_idx = take((size_t)L.rows_max * 8 * 4);
-    take((size_t)L.rows_max * 256 * 4);  // (keeps the size the allocation-free step is refused by)
+    L.moe_logits = take((size_t)L.rows_max * 256 * 4);
     L.moe_w = take((size_t)L.rows_max * 8 * 4);
     L.moe_aslot = take((size_t)L.rows_max * 8 * 4);
     L.moe_counts = take((size_t)c->n_experts * 4);
@@ -275,6 +275,7 @@ Layout make_prompt_layout(const dbt_config *c, const Layout &step) {
     L.moe_idx = take((size_t)R * 8 * 4);
     L.moe_tiles = take((size_t)(L.pack_rows * c->top_k1 / kTileExpert + c->n_experts + 1) * sizeof(int2));
     L.moe_ntiles = take(4);
+    if (c->n_experts > 128) L.moe_logits = take((size_t)R * 256 * 4);
     L.moe_w = take((size_t)R * 8 * 4);
     L.moe_aslot = take((size_t)R * 8 * 4);
     L.moe_arow = take((size_t)L.amax * 4);
@@ -546,6 +547,7 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
   ro.replay = cf.replay;
   ro.rows = c.rows;
   ro.mode = c.mode;
+  ro.logits = m->at<float>(L.moe_logits);
   ro.idx = m->at<int>(L.moe_idx);
   ro.wts = m->at<float>(L.moe_w);
   ro.idx1_in = ret_idx;

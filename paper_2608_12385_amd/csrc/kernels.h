@@ -374,6 +374,7 @@ struct MoeRoute {
   int E, k1, k2, replay;
   Rows rows;
   int mode;
+  float *logits;      // [2Bp][256] router logits, for more than 128 experts
   int *idx;           // [2Bp][8] selected experts (logit descending)
   float *wts;         // [2Bp][8] renormalised weights
   const int *idx1_in; // branch mode + replay: retained primary selections [*, 8]

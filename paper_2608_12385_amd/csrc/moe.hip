@@ -2,8 +2,8 @@
 // Sec. 4.3 Eq. (19); independent primary/branch fan-outs k1, k2, Sec. 5
 // Eq. (22)).
 //
-// 1. k_moe_route: the router logits of each sequence's primary and branch rows
-//    from the fp32 MLP input (RMSNorm of S_bar), top-k (logit descending, ties
+// 1. k_moe_route (above 128 experts followed by k_moe_select): the router
+//    logits of each sequence's primary and branch rows from the fp32 MLP input (RMSNorm of S_bar), top-k (logit descending, ties
 //    to the lower index) and the renormalised softmax weights of the selected
 //    experts.
 // 2. k_moe_dispatch: per expert, the list of (path, sequence, slot)
@@ -47,16 +47,89 @@ __device__ __forceinline__ int prow(const Rows &r, int path, int b) { return pat
 // runs its code once, from a cold instruction cache, so loops stay rolled and
 // more waves rather than unrolled pieces shorten the chain of loads (eight
 // waves with four pieces each in flight: 20 us).
+// Above 128 experts a workgroup would read a router of 0.5 to 1 MB by itself:
+// blockIdx.y is then a group of 64 experts, the logits go to memory and
+// k_moe_select follows (LOGITS).  Whole step with 256 experts and width 2048, one
+// kernel against two: one sequence 115.2 and 94.4 us, eight 141.3 and 121.1,
+// 64 sequences 229.4 and 206.2; at 128 experts one kernel (two before: 106.9
+// against 95.9 us for one sequence).
 constexpr int route_waves(int EB) { return EB <= 4 ? 16 : 8; }
+constexpr int kRouteOne = 128, kRouteGroup = 64;
 
-template <int EB>
+// Top-k of row (path p, sequence b) by one wave (logit descending, ties to the
+// lower index) by repeated wave argmax, and the softmax over all experts
+// gathered at the selection and renormalised = exp(r_e - max_sel) / sum over
+// the selection.  Lane j holds selection j; sel0: the primary's, which a
+// replaying branch of the same call (both) takes.
+template <int VQ>
+__device__ __forceinline__ void route_select(const MoeRoute &a, const float *lg, int p, int b, bool both, int &sel0) {
+  const int E = a.E, lane = threadIdx.x & 63, k = p == 0 ? a.k1 : a.k2;
+  int sel = 0;
+  float val = -INFINITY;
+  if (p == 1 && a.replay) {
+    // the branch reuses the primary's experts
+    sel = lane >= k ? 0 : both ? sel0 : a.idx1_in[(size_t)b * 8 + lane];
+    val = lane >= k ? -INFINITY : lg[sel];
+  } else {
+    float v[VQ];
+    bool open[VQ];  // not selected yet
+#pragma unroll
+    for (int q = 0; q < VQ; ++q) {
+      open[q] = lane + 64 * q < E;
+      v[q] = open[q] ? lg[lane + 64 * q] : -INFINITY;
+    }
+#pragma unroll 1
+    for (int j = 0; j < k; ++j) {
+      float best = -INFINITY;
+#pragma unroll
+      for (int q = 0; q < VQ; ++q) best = open[q] ? fmaxf(best, v[q]) : best;
+      best = wave_max_dpp(best);
+      int e = -1;
+#pragma unroll
+      for (int q = 0; q < VQ; ++q) {
+        const unsigned long long m = __ballot(open[q] && v[q] == best);
+        if (e < 0 && m) e = 64 * q + __ffsll(m) - 1;
+      }
+      if (e < 0)  // no number among what is left: the lowest of it
+#pragma unroll
+        for (int q = 0; q < VQ; ++q) {
+          const unsigned long long m = __ballot(open[q]);
+          if (e < 0 && m) e = 64 * q + __ffsll(m) - 1;
+        }
+#pragma unroll
+      for (int q = 0; q < VQ; ++q) open[q] = open[q] && lane + 64 * q != e;
+      if (lane == j) {
+        sel = e;
+        val = best;
+      }
+    }
+  }
+  sel0 = sel;
+  const float mx = wave_max_dpp(lane < k ? val : -INFINITY), w = lane < k ? expf(val - mx) : 0.f;
+  float den = 0.f;
+#pragma unroll 1
+  for (int j = 0; j < k; ++j) den += __shfl(w, j, 64);
+  if (lane < k) {
+    const size_t row = (size_t)prow(a.rows, p, b);
+    int *oi = p == 0 ? a.out_idx1 : a.out_idx2;
+    float *ow = p == 0 ? a.out_w1 : a.out_w2;
+    const int kept = p != 0 || !a.ret_idx ? -1 : a.ret_map ? a.ret_map[b].keep : b;
+    a.idx[row * 8 + lane] = sel;
+    a.wts[row * 8 + lane] = w / den;
+    if (oi) oi[(size_t)b * k + lane] = sel;
+    if (ow) ow[(size_t)b * k + lane] = w / den;
+    if (kept >= 0) a.ret_idx[(size_t)kept * 8 + lane] = sel;
+  }
+}
+
+template <int EB, bool LOGITS = false>
 __global__ __launch_bounds__(64 * route_waves(EB)) void k_moe_route(MoeRoute a) {
   constexpr int PITCH = 16 * EB + 4, kRouteWaves = route_waves(EB);
   __shared__ float red[kRouteWaves][16][PITCH];
   __shared__ float ssr[kRouteWaves][16];
   const bool prim = a.mode != MODE_BRANCH, br = a.mode != MODE_PRIMARY;
   const bool both = prim && br;
-  const int E = a.E, d = a.d;
+  const int E = a.E, d = a.d, e0 = LOGITS ? (int)blockIdx.y * 16 * EB : 0;  // experts e0 ..
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, r = lane & 15, gq = lane >> 4;
   // row i of the workgroup: sequence and path
   const int per = both ? 8 : 16, b0 = blockIdx.x * per;
@@ -65,7 +138,7 @@ __global__ __launch_bounds__(64 * route_waves(EB)) void k_moe_route(MoeRoute a) 
   const float *xr = a.Sbar + (size_t)prow(a.rows, path_of(r), min(seq_of(r), a.rows.B - 1)) * d + 8 * gq;
   const uint16_t *wr[EB];
 #pragma unroll
-  for (int q = 0; q < EB; ++q) wr[q] = (const uint16_t *)a.Wr + (size_t)min(16 * q + r, E - 1) * d + 8 * gq;
+  for (int q = 0; q < EB; ++q) wr[q] = (const uint16_t *)a.Wr + (size_t)min(e0 + 16 * q + r, E - 1) * d + 8 * gq;
   floatx4 acc[EB];
 #pragma unroll
   for (int q = 0; q < EB; ++q) acc[q] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -133,16 +206,14 @@ __global__ __launch_bounds__(64 * route_waves(EB)) void k_moe_route(MoeRoute a) 
     red[0][i][x] = v;  // (read and written by this thread alone)
     const int b = seq_of(i);
     float *og = path_of(i) == 0 ? a.out_lg1 : a.out_lg2;
-    if (og && x < E && b < a.rows.B) og[(size_t)b * E + x] = v;
+    if (e0 + x < E && b < a.rows.B) {
+      if (og) og[(size_t)b * E + e0 + x] = v;
+      if (LOGITS) a.logits[(size_t)prow(a.rows, path_of(i), b) * 256 + e0 + x] = v;
+    }
   }
+  if constexpr (LOGITS) return;
   __syncthreads();
-  // top-k (logit descending, ties to the lower index) by repeated wave argmax,
-  // and the softmax over all experts gathered at the selection and
-  // renormalised = exp(r_e - max_sel) / sum over the selection.  Lane j holds
-  // selection j.
-  constexpr int VQ = (EB + 3) / 4;
-  int sel = 0, sel0 = 0;
-  float val = -INFINITY;
+  int sel0 = 0;
   // (a wave takes both rows of a sequence where the branch replays)
   const bool two = kRouteWaves == 8 || (both && a.replay);
   if (two && wave >= 8) return;
@@ -150,63 +221,19 @@ __global__ __launch_bounds__(64 * route_waves(EB)) void k_moe_route(MoeRoute a) 
   for (int h = 0; h < (two ? 2 : 1); ++h) {
     const int i = !two ? wave : both ? wave + 8 * h : 2 * wave + h, p = path_of(i), b = seq_of(i);
     if (b >= a.rows.B) break;  // (uniform; later rows are past the end too)
-    const int k = p == 0 ? a.k1 : a.k2;
-    const float *lg = red[0][i];
-    if (p == 1 && a.replay) {
-      // the branch reuses the primary's experts
-      sel = lane >= k ? 0 : both ? sel0 : a.idx1_in[(size_t)b * 8 + lane];
-      val = lane >= k ? -INFINITY : lg[sel];
-    } else {
-      float v[VQ];
-      bool open[VQ];  // not selected yet
-#pragma unroll
-      for (int q = 0; q < VQ; ++q) {
-        open[q] = lane + 64 * q < E;
-        v[q] = open[q] ? lg[lane + 64 * q] : -INFINITY;
-      }
-#pragma unroll 1
-      for (int j = 0; j < k; ++j) {
-        float best = -INFINITY;
-#pragma unroll
-        for (int q = 0; q < VQ; ++q) best = open[q] ? fmaxf(best, v[q]) : best;
-        best = wave_max_dpp(best);
-        int e = -1;
-#pragma unroll
-        for (int q = 0; q < VQ; ++q) {
-          const unsigned long long m = __ballot(open[q] && v[q] == best);
-          if (e < 0 && m) e = 64 * q + __ffsll(m) - 1;
-        }
-        if (e < 0)  // no number among what is left: the lowest of it
-#pragma unroll
-          for (int q = 0; q < VQ; ++q) {
-            const unsigned long long m = __ballot(open[q]);
-            if (e < 0 && m) e = 64 * q + __ffsll(m) - 1;
-          }
-#pragma unroll
-        for (int q = 0; q < VQ; ++q) open[q] = open[q] && lane + 64 * q != e;
-        if (lane == j) {
-          sel = e;
-          val = best;
-        }
-      }
-    }
-    sel0 = sel;
-    const float mx = wave_max_dpp(lane < k ? val : -INFINITY), w = lane < k ? expf(val - mx) : 0.f;
-    float den = 0.f;
-#pragma unroll 1
-    for (int j = 0; j < k; ++j) den += __shfl(w, j, 64);
-    if (lane < k) {
-      const size_t row = (size_t)prow(a.rows, p, b);
-      int *oi = p == 0 ? a.out_idx1 : a.out_idx2;
-      float *ow = p == 0 ? a.out_w1 : a.out_w2;
-      const int kept = p != 0 || !a.ret_idx ? -1 : a.ret_map ? a.ret_map[b].keep : b;
-      a.idx[row * 8 + lane] = sel;
-      a.wts[row * 8 + lane] = w / den;
-      if (oi) oi[(size_t)b * k + lane] = sel;
-      if (ow) ow[(size_t)b * k + lane] = w / den;
-      if (kept >= 0) a.ret_idx[(size_t)kept * 8 + lane] = sel;
-    }
+    route_select<(EB + 3) / 4>(a, red[0][i], p, b, both, sel0);
   }
+}
+
+// The selection over logits in memory: a wave per sequence, its paths in turn.
+template <int VQ>
+__global__ __launch_bounds__(64) void k_moe_select(MoeRoute a) {
+  const bool prim = a.mode != MODE_BRANCH, br = a.mode != MODE_PRIMARY;
+  const int b = blockIdx.x;
+  int sel0 = 0;
+#pragma unroll 1
+  for (int p = prim ? 0 : 1; p < (br ? 2 : 1); ++p)
+    route_select<VQ>(a, a.logits + (size_t)prow(a.rows, p, b) * 256, p, b, prim && br, sel0);
 }
 
 // Expert-grouped order as a stable counting sort of the assignments
@@ -622,11 +649,15 @@ hipError_t launch_moe_route(const MoeRoute &a, hipStream_t st) {
   const int per = a.mode == MODE_GROUPED ? 8 : 16;
   const int eb = (a.E + 15) / 16;
   const dim3 grid((a.rows.B + per - 1) / per), block(64 * route_waves(eb));
-  if (eb <= 1) hipLaunchKernelGGL(k_moe_route<1>, grid, block, 0, st, a);
+  if (a.E > kRouteOne) {
+    if (!a.logits) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_moe_route<kRouteGroup / 16, true>), dim3(grid.x, (a.E + kRouteGroup - 1) / kRouteGroup),
+                       dim3(64 * route_waves(kRouteGroup / 16)), 0, st, a);
+    hipLaunchKernelGGL(k_moe_select<4>, dim3(a.rows.B), dim3(64), 0, st, a);
+  } else if (eb <= 1) hipLaunchKernelGGL(k_moe_route<1>, grid, block, 0, st, a);
   else if (eb <= 2) hipLaunchKernelGGL(k_moe_route<2>, grid, block, 0, st, a);
   else if (eb <= 4) hipLaunchKernelGGL(k_moe_route<4>, grid, block, 0, st, a);
-  else if (eb <= 8) hipLaunchKernelGGL(k_moe_route<8>, grid, block, 0, st, a);
-  else hipLaunchKernelGGL(k_moe_route<16>, grid, block, 0, st, a);
+  else hipLaunchKernelGGL(k_moe_route<8>, grid, block, 0, st, a);
   return hipGetLastError();
 }
 

@@ -11,12 +11,14 @@ static const void *host_fn[kMaxKernels];
 static const char *dev_name[kMaxKernels];
 static int n_kernels, n_log, fail_at = -1, last_error;
 static int log_id[kMaxLog];
+static uint32_t log_grid[kMaxLog];
 
 void fake_reset(int at) {
   fail_at = at;
   n_log = last_error = 0;
 }
 int fake_launches(void) { return n_log; }
+uint32_t fake_groups(int i) { return log_grid[i]; } /* workgroups of launch i */
 const char *fake_kernel(int i) { return log_id[i] < 0 ? "" : dev_name[log_id[i]]; }
 
 void **__hipRegisterFatBinary(const void *data) {
@@ -55,12 +57,15 @@ struct page_runs { int n, b[128], slot[128], page[128], count[128]; };
 struct step_begin { int n_pos, b0, pos[64], n_pt, pt_b[64], pt_slot[64], pt_page[64]; };
 
 int hipLaunchKernel(const void *fn, dims g, dims b, void **args, size_t shared, void *st) {
-  (void)g, (void)b, (void)shared, (void)st;
+  (void)b, (void)shared, (void)st;
   int id = -1;
   for (int i = 0; i < n_kernels; ++i)
     if (host_fn[i] == fn) id = i;
   const int at = n_log;
-  if (n_log < kMaxLog) log_id[n_log++] = id;
+  if (n_log < kMaxLog) {
+    log_grid[n_log] = g.x * g.y * g.z;
+    log_id[n_log++] = id;
+  }
   if (at == fail_at) return last_error = 719; /* hipErrorLaunchFailure */
   if (id >= 0 && strstr(dev_name[id], "k_page_runs")) {
     const struct page_runs *r = args[0];

@@ -205,3 +205,18 @@ def test_moe_router_and_expert_tiles(E, k1, k2, replay, lens):
                              dtype="bf16", has_embeddings=True, n_experts=E, d_ff_expert=128, n_shared_experts=1,
                              d_ff_shared=256, top_k1=k1, top_k2=k2, replay=replay, std=0.05, coupling_std=0.5)
     prompts_and_steps(shape, lens, BF16_TOL, steps=1)
+
+
+# routers of more than 128 experts: groups of 64 experts (one of a single
+# expert, a partial one, four whole), the selection as a kernel of its own;
+# steps, prompts and the boundary, fan-outs up to eight, a replayed branch.
+# (Fan-outs at which the oracle's last chosen logit leads the next one by at
+# least 0.2 % of the largest, about what the rounding of the states to bf16
+# moves it by: with k2 = 8, 129 experts leave a lead of 0.02 % in one row.)
+@pytest.mark.parametrize("E,k1,k2,replay,lens", [
+    (129, 3, 4, False, [1] * 9),
+    (200, 8, 3, False, [2, 40]),
+    (256, 3, 3, True, [3] * 17),
+])
+def test_moe_router_groups(E, k1, k2, replay, lens):
+    test_moe_router_and_expert_tiles(E, k1, k2, replay, lens)

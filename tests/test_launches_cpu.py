@@ -43,6 +43,10 @@ def test_prompt_attention_by_the_prompts_own_length(fake):
     run_child(fake, "attention")
 
 
+def test_large_routers_are_read_by_several_workgroups(fake):
+    run_child(fake, "router")
+
+
 # ---------------------------------------------------------------------------
 # in the child
 # ---------------------------------------------------------------------------
@@ -167,9 +171,24 @@ def attention(fk):
             assert got == want, (heads, lens, got)
 
 
+def router(fk):
+    """One sequence and 256 experts: the router matrix is 1 MB at width 2048,
+    and one workgroup reads 0.25 MB of it at most, as with 64 experts."""
+    for E, groups in ((64, 1), (128, 1), (129, 3), (256, 4)):
+        p = Program("bf16", n_layers=1, d_model=2048, d_ff=0, n_experts=E, d_ff_expert=128, d_ff_shared=128, top_k1=2,
+                    top_k2=4)
+        kv, _table = p.cache()
+        fk.fake_reset(-1)
+        p.B.dbt_decode_step(p.model, kv, p.B.dbt_step_in(tokens=FAKE, batch=1), 1, p.out, 0)
+        names = [fk.fake_kernel(i).decode() for i in range(fk.fake_launches())]
+        got = [fk.fake_groups(i) for i, n in enumerate(names) if "k_moe_route" in n]
+        assert got == [groups], (E, got)
+        assert sum("k_moe_select" in n for n in names) == (E > 128), E
+
+
 if __name__ == "__main__":
     fk = ctypes.CDLL(sys.argv[2])
     fk.fake_kernel.restype = ctypes.c_char_p
     what, _, arg = sys.argv[1].partition("_")
-    dict(boundary=boundary, pages=pages, attention=attention)[what](*([fk, arg] if arg else [fk]))
+    dict(boundary=boundary, pages=pages, attention=attention, router=router)[what](*([fk, arg] if arg else [fk]))
     print("done")
