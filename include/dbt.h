@@ -255,8 +255,8 @@ dbt_status dbt_decode_step_ungrouped(dbt_model *m, dbt_kv *kv, const dbt_step_in
  * dbt_decode_step's bit for bit.  The array holds DBT_STATIC_SCRATCH_BYTES
  * on every GPU the library runs on, from load until the process ends; a
  * model whose step buffers need more (large vocabularies with many
- * sequences, or models sized for long prompts) gets DBT_ERR_UNSUPPORTED
- * before anything changes.  Every call on one GPU shares that GPU's array:
+ * sequences) gets DBT_ERR_UNSUPPORTED before anything changes; prompts have
+ * buffers of their own, so max_prompt does not count.  Every call on one GPU shares that GPU's array:
  * calls that overlap on one GPU (other streams, threads or models) race.
  * The model still needs its workspace for the state kept between calls. */
 #define DBT_STATIC_SCRATCH_BYTES ((size_t)64 << 20)

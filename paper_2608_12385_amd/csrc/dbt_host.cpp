@@ -77,7 +77,7 @@ int n_branches(const dbt_config &c) { return c.n_branches > 1 ? c.n_branches : 1
 
 // Offsets (bytes) of every workspace buffer.
 struct Layout {
-  int Bp_max = 0, R_max = 0, rows_max = 0, pack_rows = 0, max_in = 0, nqkv = 0, f = 0;
+  int Bp_max = 0, R_max = 0, pack_rows = 0, max_in = 0, nqkv = 0, f = 0;
   GemmConfig g_qkv{1, 1, 1}, g_o{1, 1, 1}, g_gu{1, 1, 1}, g_d{1, 1, 1}, g_lm{1, 1, 1};
   int split_target = 0, max_splits = 0, nch = 0, nstat = 0;
   bool moe = false;
@@ -90,6 +90,7 @@ struct Layout {
   size_t moe_idx = 0, moe_logits = 0, moe_tiles = 0, moe_ntiles = 0, moe_w = 0, moe_aslot = 0, moe_counts = 0, moe_offsets = 0, moe_arow = 0, moe_h = 0,
          moe_y = 0, ret_idx = 0;
   size_t prow = 0, ptiles = 0;  // prompt passes: row map, attention tiles
+  size_t part = 0;  // floats at P
   size_t rope = 0, pos = 0, S = 0, Xn = 0, Xh = 0, Q = 0, O = 0, P = 0, apart = 0, astat = 0,
          logits = 0, mstats = 0, xss = 0, ret_q = 0, ret_h = 0, ret_m = 0, ret_a = 0, btok = 0, slast = 0,
          // [0, state_total): state; [state_total, step_total): step buffers; [step_total, total): prompt passes
@@ -148,19 +149,21 @@ dbt_status check_config(const dbt_config *c) {
 int prompt_splits(const GemmConfig &g, int M) { return std::max(1, g.S / ((M + 127) / 128)); }
 
 // fp32 output elements a projection N x K of a prompt pass of up to `rows`
-// rows can need: plain outputs, or the slabs of a short pass.  fused: the
-// tiled kernel's epilogue writes no fp32 output.
+// rows can need: plain outputs, the slabs of a short pass, or those of a tiled
+// one (at least 1024 elements of the reduction each; kTileSlabs bounds all of
+// them together).  fused: the tiled kernel's epilogue writes no fp32 output.
 size_t prompt_part(const GemmConfig &g, int N, int K, int dtype, int rows, bool fused) {
-  const bool tiled = dtype == DBT_BF16 && (long long)N * K < (1LL << 31) && (long long)rows * K < (1LL << 31);
-  const size_t slabs = dtype == DBT_BF16 ? (size_t)std::max(g.S, 2) * std::min(rows, 128) * N : 0;
-  const size_t plain = (size_t)rows * N + (dtype == DBT_BF16 ? kTileSlabs : 0);
-  return std::max(slabs, tiled && fused ? (size_t)0 : plain);
+  const size_t one = (size_t)rows * N;
+  if (dtype != DBT_BF16) return one;
+  const size_t slabs = (size_t)std::max(g.S, 2) * std::min(rows, 128) * N;
+  if (rows < kTileRows) return std::max(slabs, one);
+  if (fused && (long long)N * K < (1LL << 31) && (long long)rows * K < (1LL << 31)) return slabs;
+  return std::max({slabs, one, K >= 2048 ? std::min<size_t>(kTileSlabs, one * std::min(4, K / 1024)) : 0});
 }
 
 // The workspace of a model: the state, the buffers of a call over stacked
-// sequences (rows_min: at least that many rows in each), and the buffers of
-// the packed prompt passes.
-Layout make_layout(const dbt_config *c, int rows_min = 0) {
+// sequences, and the buffers of the packed prompt passes.
+Layout make_layout(const dbt_config *c) {
   Layout L;
   const int d = c->d_model, dq = c->n_q_heads * c->head_dim, dkv = c->n_kv_heads * c->head_dim;
   L.moe = c->n_experts > 0;
@@ -169,7 +172,6 @@ Layout make_layout(const dbt_config *c, int rows_min = 0) {
   L.f = L.moe ? std::max(L.fs, 128) : c->d_ff;
   L.Bp_max = round16(c->max_batch);
   L.R_max = (1 + n_branches(*c)) * L.Bp_max;
-  L.rows_max = std::max(L.R_max, rows_min);
   L.max_in = std::max(std::max(d, dq), L.f);
   L.nqkv = dq + 2 * dkv;
   L.g_qkv = gemm_config(L.nqkv, d, c->dtype, std::gcd(dq, dkv), L.R_max);
@@ -200,7 +202,7 @@ Layout make_layout(const dbt_config *c, int rows_min = 0) {
   size_t part = std::max({(size_t)L.g_qkv.S * L.R_max * L.nqkv, (size_t)L.g_o.S * L.R_max * d,
                           (size_t)L.g_gu.S * L.R_max * 2 * L.f, (size_t)L.g_d.S * L.R_max * d});
   if (L.moe) part = std::max({part, (size_t)L.g_sgu.S * L.R_max * 2 * L.f, (size_t)L.g_sd.S * L.R_max * d});
-  part = std::max(part, (size_t)rows_min * std::max({L.nqkv, d, 2 * L.f}));
+  L.part = part;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += align256(bytes); return at; };
   // State kept between calls: the RoPE table, positions, the primary
@@ -220,11 +222,11 @@ Layout make_layout(const dbt_config *c, int rows_min = 0) {
   // results are never used), so any memory of this size can hold them.
   o = align256(o);
   L.state_total = o;
-  L.S = take((size_t)L.rows_max * d * 4);
-  L.Xn = take((size_t)L.rows_max * L.max_in * 4);
-  L.Xh = take((size_t)L.rows_max * L.f * 4);
-  L.Q = take((size_t)L.rows_max * dq * 4);
-  L.O = take((size_t)L.rows_max * dq * 4);
+  L.S = take((size_t)L.R_max * d * 4);
+  L.Xn = take((size_t)L.R_max * L.max_in * 4);
+  L.Xh = take((size_t)L.R_max * L.f * 4);
+  L.Q = take((size_t)L.R_max * dq * 4);
+  L.O = take((size_t)L.R_max * dq * 4);
   L.P = take(part * 4);
   L.apart = take((size_t)c->max_batch * c->n_kv_heads * L.max_splits * 16 * c->head_dim * 4);
   L.astat = take((size_t)c->max_batch * c->n_kv_heads * L.max_splits * 16 * 2 * 4);
@@ -234,11 +236,11 @@ Layout make_layout(const dbt_config *c, int rows_min = 0) {
   L.mstats = take((size_t)L.R_max * L.nstat * 3 * 4);
   L.xss = take((size_t)std::max(L.g_qkv.S, 1) * L.R_max * 4);
   if (L.moe) {
-    L.amax = L.rows_max * 8;
-    L.moe_idx = take((size_t)L.rows_max * 8 * 4);
-    L.moe_logits = take((size_t)L.rows_max * 256 * 4);
-    L.moe_w = take((size_t)L.rows_max * 8 * 4);
-    L.moe_aslot = take((size_t)L.rows_max * 8 * 4);
+    L.amax = L.R_max * 8;
+    L.moe_idx = take((size_t)L.R_max * 8 * 4);
+    if (c->n_experts > kRouteOne) L.moe_logits = take((size_t)L.R_max * 256 * 4);
+    L.moe_w = take((size_t)L.R_max * 8 * 4);
+    L.moe_aslot = take((size_t)L.R_max * 8 * 4);
     L.moe_counts = take((size_t)c->n_experts * 4);
     L.moe_offsets = take((size_t)(c->n_experts + 1) * 4);
     L.moe_arow = take((size_t)L.amax * 4);
@@ -269,13 +271,14 @@ Layout make_prompt_layout(const dbt_config *c, const Layout &step) {
     part = std::max({part, prompt_part(L.g_sgu, 2 * L.fs, d, c->dtype, R, true), prompt_part(L.g_sd, d, L.fs, c->dtype, R, false)});
   else
     part = std::max({part, prompt_part(L.g_gu, 2 * L.f, d, c->dtype, R, true), prompt_part(L.g_d, d, L.f, c->dtype, R, false)});
+  L.part = part;
   L.P = take(part * 4);
   if (L.moe) {
     L.amax = R * c->top_k1;  // (the primary alone)
     L.moe_idx = take((size_t)R * 8 * 4);
     L.moe_tiles = take((size_t)(L.pack_rows * c->top_k1 / kTileExpert + c->n_experts + 1) * sizeof(int2));
     L.moe_ntiles = take(4);
-    if (c->n_experts > 128) L.moe_logits = take((size_t)R * 256 * 4);
+    if (c->n_experts > kRouteOne) L.moe_logits = take((size_t)R * 256 * 4);
     L.moe_w = take((size_t)R * 8 * 4);
     L.moe_aslot = take((size_t)R * 8 * 4);
     L.moe_arow = take((size_t)L.amax * 4);
@@ -317,7 +320,6 @@ struct dbt_model {
   std::vector<dbt_layer_weights> layers;
   char *ws = nullptr;
   Layout L, Lp;  // Lp: the buffers of the packed prompt passes
-  size_t noalloc_bytes = 0;  // see step_bytes
   std::vector<float> rope_host;
   bool dev_ready = false;
   // boundary state: set by dbt_prefill(run_boundary = 0)
@@ -624,6 +626,7 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
     if (c.prefill && gemm_tile_args_ok(tg, true)) {
       HIPCHK(launch_gemm_tile(tg, true, sst));
     } else {
+      if ((size_t)g_sgu.S * (size_t)st_gu > L.part) return fail(DBT_ERR_STATE, "internal: shared-expert slabs");
       HIPCHK(launch_gemm(gu, 2 * fs, d, cf.dtype, m->p(L.Xn) + (size_t)sxrow0 * d * es, d, sM,
                          P + (size_t)sxrow0 * 2 * fs, 2 * fs, st_gu, g_sgu, sst));
       HIPCHK(launch_swiglu_finish(P, st_gu, g_sgu.S, 2 * fs, fs, smode, srows, W.b, ret_h, keep, cf.dtype,
@@ -641,6 +644,9 @@ dbt_status run_moe_mlp(dbt_model *m, int l, const LayerCall &c, hipStream_t st) 
     if (c.prefill && gemm_tile_args_ok(td, false)) {
       td.splits = g_sd.S = gemm_tile_splits(d, fs, sM);
       td.y_stride = stride;
+    }
+    if ((size_t)g_sd.S * (size_t)stride > L.part) return fail(DBT_ERR_STATE, "internal: shared-expert slabs");
+    if (td.splits) {
       HIPCHK(launch_gemm_tile(td, false, sst));
     } else {
       HIPCHK(launch_gemm(sd, d, fs, cf.dtype, m->p(L.Xh) + (size_t)sxrow0 * fs * es, fs, sM, P + (size_t)sxrow0 * d,
@@ -807,8 +813,9 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
     if (c.prefill && cf.dtype == DBT_BF16 && gemm_tile_args_ok(tg, false)) {
       tg.splits = S = gemm_tile_splits(N, K, rows_M);
       tg.y_stride = y_stride;
-      return launch_gemm_tile(tg, false, st);
     }
+    if ((size_t)S * (size_t)y_stride > L.part) return hipErrorInvalidValue;  // (y_stride: the rows of every path)
+    if (tg.splits) return launch_gemm_tile(tg, false, st);
     return launch_gemm(segs, N, K, cf.dtype, X, ldx, rows_M, Y, ldy, y_stride, g, st);
   };
   const GemmConfig g_qkv = cfg(L.g_qkv), g_o = cfg(L.g_o), g_gu = cfg(L.g_gu), g_d = cfg(L.g_d);
@@ -1006,6 +1013,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
     stride = (long long)c.rows_layout * 2 * f;
     {
       Timed tm(m, DBT_STAGE_GATEUP, st);
+      if ((size_t)S_gu * (size_t)stride > L.part) return fail(DBT_ERR_STATE, "internal: gate/up slabs");
       HIPCHK(launch_gemm(gu, 2 * f, d, cf.dtype, Xn + (size_t)xrow0 * d * es, d, M, P + (size_t)xrow0 * 2 * f,
                          2 * f, stride, g_gu, st));
     }
@@ -1342,8 +1350,6 @@ dbt_status dbt_create(const dbt_config *cfg, const dbt_weights *w, void *workspa
   m->ws = (char *)workspace;
   m->L = make_layout(cfg);
   m->Lp = make_prompt_layout(cfg, m->L);
-  const Layout with_prompt = make_layout(cfg, cfg->max_prompt);
-  m->noalloc_bytes = with_prompt.step_total - with_prompt.state_total;
   m->step = m->ws + m->L.state_total;
   // RoPE table (Eq. (8)): angle pos * theta^(-2i/d_h), evaluated in double.
   const int half = cfg->head_dim / 2;
@@ -1667,7 +1673,7 @@ namespace dbt {
 
 dbt_status set_error(dbt_status s, const char *msg) { return fail(s, "%s", msg); }
 
-size_t step_bytes(const dbt_model *m) { return m->noalloc_bytes; }
+size_t step_bytes(const dbt_model *m) { return m->L.step_total - m->L.state_total; }
 
 dbt_status decode_step_in(dbt_model *m, dbt_kv *kv, const dbt_step_in *in, int32_t branch_on, dbt_step_out *out,
                           dbt_stream stream, char *step_mem) {

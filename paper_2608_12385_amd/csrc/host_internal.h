@@ -10,9 +10,8 @@ namespace dbt {
 // Sets the thread's dbt_last_error() message and returns s.
 dbt_status set_error(dbt_status s, const char *msg);
 
-// Bytes the allocation-free step requires for m: the buffers a decode step
-// writes and reads within the call (activations, split partials, logits and
-// their statistics, MoE lists), with room for its longest prompt's rows.
+// Bytes of the buffers a decode step of m writes and reads within the call
+// (activations, split partials, logits and their statistics, MoE lists).
 size_t step_bytes(const dbt_model *m);
 
 // dbt_decode_step with those buffers at step_mem (at least step_bytes(m)

@@ -365,6 +365,7 @@ hipError_t launch_mixture(const MixArgs &m, hipStream_t st);
 
 // ---- MoE (Sec. 3.2, Sec. 4.3, Sec. 5) ----
 // Per-row selections live in [2Bp][8] arrays (row = path*Bp + b, k <= 8).
+constexpr int kRouteOne = 128;  // experts one workgroup of the router takes
 struct MoeRoute {
   const float *Sbar;  // [2Bp][d] residual after attention (fp32)
   const float *g;     // MLP norm gain
@@ -374,7 +375,7 @@ struct MoeRoute {
   int E, k1, k2, replay;
   Rows rows;
   int mode;
-  float *logits;      // [2Bp][256] router logits, for more than 128 experts
+  float *logits;      // [2Bp][256] router logits, for more than kRouteOne experts
   int *idx;           // [2Bp][8] selected experts (logit descending)
   float *wts;         // [2Bp][8] renormalised weights
   const int *idx1_in; // branch mode + replay: retained primary selections [*, 8]

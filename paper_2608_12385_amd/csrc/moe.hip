@@ -3,9 +3,9 @@
 // Eq. (22)).
 //
 // 1. k_moe_route (above 128 experts followed by k_moe_select): the router
-//    logits of each sequence's primary and branch rows from the fp32 MLP input (RMSNorm of S_bar), top-k (logit descending, ties
-//    to the lower index) and the renormalised softmax weights of the selected
-//    experts.
+//    logits of each sequence's primary and branch rows from the fp32 MLP input
+//    (RMSNorm of S_bar), top-k (logit descending, ties to the lower index) and
+//    the renormalised softmax weights of the selected experts.
 // 2. k_moe_dispatch: per expert, the list of (path, sequence, slot)
 //    assignments in (path, sequence, slot) order; each assignment's
 //    position in the expert-grouped order.
@@ -54,7 +54,7 @@ __device__ __forceinline__ int prow(const Rows &r, int path, int b) { return pat
 // 64 sequences 229.4 and 206.2; at 128 experts one kernel (two before: 106.9
 // against 95.9 us for one sequence).
 constexpr int route_waves(int EB) { return EB <= 4 ? 16 : 8; }
-constexpr int kRouteOne = 128, kRouteGroup = 64;
+constexpr int kRouteGroup = 64;
 
 // Top-k of row (path p, sequence b) by one wave (logit descending, ties to the
 // lower index) by repeated wave argmax, and the softmax over all experts

@@ -47,6 +47,10 @@ def test_large_routers_are_read_by_several_workgroups(fake):
     run_child(fake, "router")
 
 
+def test_workspace_holds_every_pass_and_nothing_else(fake):
+    run_child(fake, "workspace")
+
+
 # ---------------------------------------------------------------------------
 # in the child
 # ---------------------------------------------------------------------------
@@ -68,6 +72,7 @@ class Program:
         for l in range(cfg.n_layers):
             for f, _ in B.dbt_layer_weights._fields_:
                 setattr(self.layers[l], f, FAKE)
+        self.bytes = B.dbt_workspace_bytes(cfg)
         w = B.dbt_weights(emb1=FAKE, emb2=FAKE, emb_norm=FAKE, final_norm=FAKE, lm_head=FAKE, h_layers=self.layers)
         self.model = B.dbt_create(cfg, w, FAKE)
         self.out = B.dbt_step_out(logits1=FAKE, logits2=FAKE, alpha=FAKE, next_token=FAKE, h1_out=FAKE, h2_out=FAKE)
@@ -186,9 +191,47 @@ def router(fk):
         assert sum("k_moe_select" in n for n in names) == (E > 128), E
 
 
+def workspace(fk):
+    """Every prompt pass finds room for its slabs (each projection checks the
+    room before its launch), the allocation-free step asks for the step's
+    buffers alone, and nothing is reserved that no launch uses."""
+    MB = 1 << 20
+    for d, nq, nkv, f in ((256, 2, 1, 384), (2048, 16, 4, 5632), (4096, 32, 8, 14336), (1024, 8, 8, 4096),
+                          (4224, 33, 11, 3200)):
+        for longest, batch in ((100, 1), (127, 2), (128, 2), (255, 1), (256, 1), (300, 3), (1100, 2), (3000, 3)):
+            p = Program("bf16", max_batch=batch, d_model=d, n_q_heads=nq, n_kv_heads=nkv, d_ff=f, n_layers=1,
+                        max_pos=longest, max_prompt=longest)
+            kv, _table = p.cache(1000, batch)
+            for n in sorted({1, 17, 128, 129, 255, 256, 257, 600, longest} & set(range(1, longest + 1))):
+                for b in range(batch):
+                    p.B.dbt_kv_truncate(kv, b, 0)
+                lens = [n] + [max(1, longest // 2)] * (batch - 1)
+                assert p.status(p.B.dbt_prefill, p.model, kv, FAKE, lens, batch, 1, p.out, 0) == 0, (d, longest, lens)
+            p.B.dbt_kv_destroy(kv)
+            p.B.dbt_destroy(p.model)
+    for longest in (256, 20000):  # a step does not use a prompt's buffers
+        p = Program("bf16", max_batch=2, d_model=2048, n_q_heads=16, n_kv_heads=4, d_ff=5632, n_layers=1,
+                    max_pos=20000, max_prompt=longest)
+        kv, _table = p.cache(1000, 2)
+        sin = p.B.dbt_step_in(tokens=FAKE, batch=1)
+        assert p.status(p.B.dbt_decode_step_noalloc, p.model, kv, sin, 1, p.out, 0) == 0, longest
+
+    def size(**kw):
+        return Program("bf16", **kw).bytes
+
+    # plain projections of short reductions or short prompts write one slab per row
+    for kw in (dict(max_prompt=100, max_batch=2), dict(max_prompt=256, max_batch=4)):
+        assert size(**kw) < 32 * MB, kw
+    # router logits in memory for routers of several workgroups alone
+    moe = dict(max_batch=512, max_prompt=0, n_layers=1, d_model=512, d_ff=0, d_ff_expert=128, d_ff_shared=128, top_k1=2,
+               top_k2=4)
+    few, many, more = (size(n_experts=E, **moe) for E in (127, 128, 129))
+    assert many - few < 4096 and more - many >= 2 * 512 * 1024
+
+
 if __name__ == "__main__":
     fk = ctypes.CDLL(sys.argv[2])
     fk.fake_kernel.restype = ctypes.c_char_p
     what, _, arg = sys.argv[1].partition("_")
-    dict(boundary=boundary, pages=pages, attention=attention, router=router)[what](*([fk, arg] if arg else [fk]))
+    dict(boundary=boundary, pages=pages, attention=attention, router=router, workspace=workspace)[what](*([fk, arg] if arg else [fk]))
     print("done")
