@@ -161,7 +161,9 @@ typedef struct {
 
 /* ---- host-only calls (no GPU needed) ---------------------------------- */
 
-/* Size in bytes of the device workspace dbt_create needs (0 on a bad config). */
+/* Size in bytes of the device workspace dbt_create needs (0 on a bad config).
+ * Models with prefill hold the activations of one pass over prompts, of
+ * max(max_prompt, min(max_batch * max_prompt, 8192)) rows. */
 size_t dbt_workspace_bytes(const dbt_config *cfg);
 
 /* Bytes of one of the two page arrays (K or V) for num_pages pages. */
@@ -215,7 +217,14 @@ dbt_status dbt_kv_fill(dbt_kv *kv, int32_t layer, int32_t b, int32_t start, int3
  * sequences 0..batch-1 must be empty.  run_boundary = 1 then evaluates the
  * branch once at the final prompt position (step 2; see dbt_boundary), and
  * out receives the mixture prediction of the first continuation token;
- * run_boundary = 0 fills out with the primary-only prediction. */
+ * run_boundary = 0 fills out with the primary-only prediction.
+ * Consecutive prompts share passes of up to max(max_prompt, 8192) rows.  The
+ * same prompts in the same order repeat their bits.  In a float32 model a
+ * prompt's cache and outputs are the same bits whatever prompts share the
+ * call; in bf16 the rows of a pass choose how its projections sum (streaming
+ * or tiled kernels, splits of the reduction), so they can differ by rounding
+ * from one batch to another (and an MoE row can select other experts where two
+ * router logits nearly tie). */
 dbt_status dbt_prefill(dbt_model *m, dbt_kv *kv, const int32_t *tokens,
                        const int32_t *h_prompt_lens, int32_t batch, int32_t run_boundary,
                        dbt_step_out *out, dbt_stream stream);

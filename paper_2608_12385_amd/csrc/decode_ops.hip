@@ -5,8 +5,10 @@
 // (Sec. 4.2, Eqs. (17)-(18)).
 //
 // Split-K partial slabs are always added in split order, and every reduction
-// has a fixed order, so results are deterministic and a row's value does not
-// depend on which other rows are active.
+// has a fixed order, so results are deterministic and a row's value depends on
+// its own slabs only, never on which other rows are active.  (How many slabs a
+// projection writes is fixed per model in a decode step; in a bf16 pass over
+// prompts it follows from the rows of the pass.)
 #include "common.h"
 #include "kernels.h"
 

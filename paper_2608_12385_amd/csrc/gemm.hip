@@ -8,8 +8,11 @@
 // chunks.
 // Optional split of the reduction across workgroups (grid.y) writes one fp32
 // slab per split; the consumer kernel adds the slabs in split order.  The
-// per-element arithmetic never depends on how many rows are stacked, so the
-// primary rows come out bit-identical with or without the branch rows.
+// arithmetic of an element depends on the configuration and the number of
+// splits only, never on how many rows are stacked; a decode step keeps both per
+// model, so the primary rows come out bit-identical with or without the branch
+// rows.  (Passes over prompts of fewer than 256 rows choose their splits by the
+// rows, and longer ones run prefill_gemm.hip.)
 //
 // fp32 weights: the same product on the fp32 matrix instruction, the reduction
 // split over the waves of a workgroup (small models).
@@ -592,9 +595,9 @@ __global__ __launch_bounds__(64 * kWavesF32) void k_gemm_f32(WSegs segs, int N, 
 
 // Launch configuration of a weight matrix of n_full rows and K columns:
 // row blocks per wave (RB), weight prefetch depth (PD) and reduction splits
-// (S).  It depends on the matrix shape only (never on the number of stacked
-// rows), so every output element is summed in the same order whichever paths
-// are active.
+// (S).  It depends on the matrix shape and the most rows a model can stack,
+// never on a call's rows, so every output element of a step is summed in the
+// same order whichever paths are active.
 // seg_gran: every segment boundary of the stacked matrices is a multiple of it.
 GemmConfig gemm_config(int n_full, int K, int dtype, int seg_gran, int max_rows) {
   GemmConfig g{1, 1, 1, 4};
