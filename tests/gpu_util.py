@@ -5,6 +5,26 @@ import numpy as np
 import synth
 
 
+# Prompt passes of 256 rows and more (d, query heads, KV heads, d_ff, prompt
+# lengths) that reach every form of the tiled projections; test_launches_cpu.py
+# checks what each launches.
+TILED_CASES = [
+    # 128 x 128 tiles: one, three, five and nine reduction steps, a partial last
+    # row tile, one head
+    (128, 1, 1, 640, [260, 1]),
+    (384, 3, 1, 1664, [257]),
+    (1152, 6, 2, 1408, [300, 90]),
+    # 256 x 256 gate/up tiles, W_O and down in two splits
+    (2048, 16, 4, 5632, [400, 601]),
+    # W_O in three splits of 8, 8 and 9 steps, down in four of 8, 8, 8 and 9
+    (256, 25, 5, 4224, [300]),
+    # 33 heads and 16.5 column tiles of 256, eight row tiles of 128 or of 256,
+    # the last one partial
+    (4224, 11, 11, 2176, [700, 303]),
+    (4224, 11, 11, 2176, [1100, 900]),
+]
+
+
 def device_params(weights):
     return {k: weights.device_array(k) for k in weights.values}
 

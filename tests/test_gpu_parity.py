@@ -170,9 +170,9 @@ def _layer_case(lengths, steps=2, vocab=512, seed_h=2, poison=0):
 
 
 # Lengths at and around page and power-of-two boundaries, caches of one
-# position and of one position into a new page, caches read in several
-# splits (with few sequences the splits are 16 pages long, so 1041 and 2063
-# positions end inside a split), and (last two sets) page bytes poisoned with
+# position and of one position into a new page, caches read in several splits
+# (with few sequences 24 pages is the target: 66 pages are read as three splits
+# of 22, 129 as six of 21 or 22), and (last two sets) page bytes poisoned with
 # 0xFF (bf16 0xFFFF, a NaN) so slots past each sequence's end hold NaN: they
 # must be masked, not multiplied by a zero probability.
 @pytest.mark.parametrize("lengths,poison", [([1, 15, 16, 17, 600], 0), ([511, 512, 513], 0),

@@ -5,7 +5,7 @@ import pytest
 
 import synth
 from oracle import Oracle
-from tests.gpu_util import check_readout, make_session, row_err, to_np
+from tests.gpu_util import TILED_CASES, check_readout, fill_cache, make_session, row_err, to_np
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -173,19 +173,40 @@ def test_step_outputs_in_place_and_copied(dtype, vocab, grouped):
     sess.close()
 
 
-# the tiled projections of 256 rows and more: one, three and five 128-element
-# reduction steps, a partial last row tile, an odd number of heads, splits of
-# unequal length; and a width whose gate/up tiles are the largest ones
-@pytest.mark.parametrize("d,nq,nkv,f,lens", [
-    (128, 1, 1, 640, [260, 1]),
-    (384, 3, 1, 1664, [257]),
-    (1152, 6, 2, 1408, [300, 90]),
-    (2048, 16, 4, 5632, [400, 601]),
-])
+@pytest.mark.parametrize("d,nq,nkv,f,lens", TILED_CASES)
 def test_bf16_tiled_projections(d, nq, nkv, f, lens):
     shape = synth.ModelShape(n_layers=1, d_model=d, n_q_heads=nq, n_kv_heads=nkv, head_dim=128, d_ff=f, vocab=512,
                              dtype="bf16", has_embeddings=True, std=0.03, coupling_std=0.5)
     prompts_and_steps(shape, lens, BF16_TOL, steps=1)
+
+
+# caches on both sides of the shortest split (24 pages, 384 positions): the
+# boundary of the longest prompt launches a merge with nothing to merge, the
+# steps cross into a second split
+def test_bf16_attention_around_the_shortest_split():
+    shape = synth.ModelShape(n_layers=2, d_model=256, n_q_heads=4, n_kv_heads=1, head_dim=128, d_ff=384, vocab=512,
+                             dtype="bf16", has_embeddings=True, std=0.05, coupling_std=0.5)
+    prompts_and_steps(shape, [384, 383, 17], BF16_TOL, steps=3)
+
+
+# a model made for more and longer sequences than the call has: splits of 24,
+# 86 (batch x KV heads >= 256) and 128 pages of an 8192-position window, caches
+# of one position to several splits
+@pytest.mark.parametrize("max_batch,nkv", [(4, 2), (64, 4), (8, 8)])
+def test_bf16_short_caches_of_a_large_model(max_batch, nkv):
+    shape = synth.ModelShape(n_layers=1, d_model=256, n_q_heads=nkv, n_kv_heads=nkv, head_dim=128, d_ff=256, vocab=0,
+                             dtype="bf16", has_embeddings=False, std=0.05, coupling_std=0.5)
+    W, lens = synth.make_weights(shape), [1, 383, 2049, 130]
+    sess, orc = make_session(shape, W, max_batch=max_batch, max_pos=8192, num_pages=200), Oracle(shape, W.values)
+    sess.k_pages.fill_(0xFF)
+    sess.v_pages.fill_(0xFF)
+    fill_cache(sess, orc, shape, lens)
+    for step in range(2):
+        h = synth.make_hidden(shape, len(lens), step=step)
+        outs, t = orc.decode_step(h1=h[0], h2=h[1]), sess.decode(h1=h[0], h2=h[1])
+        for key, ref in (("h1_out", "h1"), ("h2_out", "h2")):
+            assert row_err(to_np(t[key]), np.stack([o[ref] for o in outs])).max() <= BF16_TOL, (step, key)
+    sess.close()
 
 
 # expert counts around the router's 16-expert blocks and 64-lane rows, batches

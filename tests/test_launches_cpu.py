@@ -51,6 +51,10 @@ def test_workspace_holds_every_pass_and_nothing_else(fake):
     run_child(fake, "workspace")
 
 
+def test_tiled_projection_cases_reach_every_form(fake):
+    run_child(fake, "tiles")
+
+
 # ---------------------------------------------------------------------------
 # in the child
 # ---------------------------------------------------------------------------
@@ -191,6 +195,32 @@ def router(fk):
         assert sum("k_moe_select" in n for n in names) == (E > 128), E
 
 
+def tiles(fk):
+    """The GPU test's prompts of 256 rows and more run every tile shape of every
+    epilogue, and plain projections in one to four splits."""
+    import re
+    from tests.gpu_util import TILED_CASES
+    seen, splits = set(), set()
+    for d, nq, nkv, f, lens in TILED_CASES:
+        p = Program("bf16", max_batch=2, n_layers=1, d_model=d, n_q_heads=nq, n_kv_heads=nkv, d_ff=f,
+                    max_pos=max(lens) + 1, max_prompt=max(lens))
+        kv, _table = p.cache(200, 2)
+        fk.fake_reset(-1)
+        p.B.dbt_prefill(p.model, kv, FAKE, lens, len(lens), 0, p.out, 0)
+        T = sum(lens)
+        plain = [d, d]  # columns of W_O, down
+        for i in range(fk.fake_launches()):
+            m = re.search(r"k_gemm_tileILi(\d+)ELi(\d+)ELi(\d+)ELi(\d)ELb0", fk.fake_kernel(i).decode())
+            if m:
+                bm, bn, _bk, epi = map(int, m.groups())
+                seen.add((bm, bn, epi))
+                if epi == 0:
+                    n = plain.pop()
+                    splits.add(fk.fake_groups(i) // (-(-T // bm) * -(-n // bn)))
+    assert seen == {(bm, bn, e) for bm, bn in ((256, 256), (128, 256), (128, 128)) for e in (0, 1, 2)}, seen
+    assert splits == {1, 2, 3, 4}, splits
+
+
 def workspace(fk):
     """Every prompt pass finds room for its slabs (each projection checks the
     room before its launch), the allocation-free step asks for the step's
@@ -232,6 +262,8 @@ def workspace(fk):
 if __name__ == "__main__":
     fk = ctypes.CDLL(sys.argv[2])
     fk.fake_kernel.restype = ctypes.c_char_p
+    fk.fake_groups.restype = ctypes.c_uint
     what, _, arg = sys.argv[1].partition("_")
-    dict(boundary=boundary, pages=pages, attention=attention, router=router, workspace=workspace)[what](*([fk, arg] if arg else [fk]))
+    dict(boundary=boundary, pages=pages, attention=attention, router=router, tiles=tiles,
+         workspace=workspace)[what](*([fk, arg] if arg else [fk]))
     print("done")
