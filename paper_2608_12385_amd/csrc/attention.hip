@@ -13,7 +13,7 @@
 // operand layout of the value MFMA O^T = V^T P^T with reduction index
 // k = 8(2p+h) + j, and with V pages stored dim-major each lane loads its V^T
 // operand as one 16-byte piece.  Softmax is online per split (base-2
-// exponent, running max and sum), the four waves of a workgroup merge
+// exponent, running max and sum), the eight waves of a workgroup merge
 // through LDS, and a combine kernel merges the splits in split order.  A
 // sequence of P pages is read in ceil(P / target) splits of equal size (the
 // last at most one page shorter per split): a function of its own length
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     // issued before the wave's first page pair, which is requested from the
     // page table directly unless it holds the appended position; then the
     // sums wait only for the older loads and the pages stay in flight.
-    // Append threads beyond the workgroup (four waves) take a second pass.
+    // Append threads beyond the workgroup (G = 6 to 8) take a second pass.
     const QKVFinish &f = a.fin;
     const int t = threadIdx.x, pos = len - 1, np = a.rows.np;
     const bool prim = f.mode != MODE_BRANCH;  // then path p0 = 0 is the primary
@@ -377,8 +377,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
     if (appends)
       for (int t2 = t + NW * 64; t2 < G * (DH / 2) + DH / 2 + DH; t2 += NW * 64) {
-        const int u2 = t2 - G * (DH / 2);
-        if (u2 < 0) continue;  // queries: all in the first pass (G <= NW)
+        const int u2 = t2 - G * (DH / 2);  // (not negative: G <= NW)
         const int page2 = ptab[pos >> 4];
         const float2 cs2 = f.rope[(size_t)pos * (DH / 2) + u2 % (DH / 2)];
         const float rs0 = row_scale(f, b);

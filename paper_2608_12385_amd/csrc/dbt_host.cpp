@@ -188,8 +188,8 @@ Layout make_layout(const dbt_config *c) {
   const int maxpages = (c->max_pos + kPage - 1) / kPage;
   if (c->dtype == DBT_BF16) {
     const int pairs = c->max_batch * c->n_kv_heads;
-    const int want = (256 + pairs - 1) / pairs;  // splits per pair
-    L.split_target = pairs >= 256 ? std::min(std::max(maxpages, kSplitMinBf16), kSplitTargetBf16)
+    const int want = (kComputeUnits + pairs - 1) / pairs;  // splits per pair
+    L.split_target = pairs >= kComputeUnits ? std::min(std::max(maxpages, kSplitMinBf16), kSplitTargetBf16)
                                   : std::clamp((maxpages + want - 1) / want, kSplitMinBf16, kSplitMaxBf16);
   } else {
     L.split_target = kSplitTargetF32;
@@ -491,35 +491,28 @@ struct LayerCall {
   HOut ho;  // where the last layer leaves the states (see HOut)
 };
 
-// Whether the decode step's attention kernel finishes the QKV projection
-// (split-K sums, rotary embedding, query coupling, cache append) for a batch
-// of B sequences whose longest cache is maxlen positions after the append.
-bool attn_finishes_qkv(const dbt_model *m, int B, int maxlen, bool *single_out = nullptr);
+// Whether the decode attention of B sequences, the longest of maxlen positions
+// after the append, reads each (sequence, KV head) in one workgroup: bf16 where
+// the batch fills the chip (and the kernel holds the page ids), fp32 where no
+// sequence needs a second split.
+bool attn_single(const dbt_model *m, int B, int maxlen) {
+  const dbt_config &cf = m->cfg;
+  const int npages = (maxlen + kPage - 1) / kPage;
+  if (cf.dtype != DBT_BF16) return npages <= m->L.split_target;
+  return B * cf.n_kv_heads >= kComputeUnits && npages <= kSplitMaxBf16;
+}
 
 // Whether the first layer of a layer-only model takes its rows straight from
 // the step inputs (XNorm) for a decode step of B sequences.  Decided from
 // the model and batch only, so the grouped, primary-only and two-pass steps
 // (and a branch pass) all use the same arithmetic for a row.
-bool input_fold(const dbt_model *m, const dbt_kv *kv, int B);
-
-bool attn_finishes_qkv(const dbt_model *m, int B, int maxlen, bool *single_out) {
-  const dbt_config &cf = m->cfg;
-  const int npages = (maxlen + kPage - 1) / kPage;
-  // fp32: no sequence needs a second split (no partials to merge)
-  const bool single = cf.dtype == DBT_BF16 ? B * cf.n_kv_heads >= 256 && npages <= 1024 : npages <= m->L.split_target;
-  if (single_out) *single_out = single;
-  return cf.dtype == DBT_BF16;
-}
-
-bool input_fold(const dbt_model *m, const dbt_kv *kv, int B) {
+bool input_fold(const dbt_model *m, int B) {
   const dbt_config &cf = m->cfg;
   if (cf.has_embeddings || cf.dtype != DBT_BF16 || cf.d_model % 128) return false;
-  int maxlen = 0;
-  for (int b = 0; b < B; ++b) maxlen = std::max(maxlen, kv->len[b] + 1);
   // the largest call of a step: every path's rows, or the primary's alone
   // when only it attends (compute-matched)
   const int Bp = round16(B), M = (cf.compute_matched ? 1 : 1 + n_branches(cf)) * Bp;
-  return attn_finishes_qkv(m, B, maxlen) && gemm_xnorm_ok(m->L.g_qkv, M);
+  return gemm_xnorm_ok(m->L.g_qkv, M);
 }
 
 // MoE MLP of layer l for the active rows: route, dispatch, touched experts,
@@ -792,8 +785,8 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
     if (c.prefill) g.S = M < kTileRows && cf.dtype == DBT_BF16 ? prompt_splits(g, M) : 1;
     return g;
   };
-  // A projection of the active rows: the 256-row tiled kernel over a whole
-  // prompt, the weight-streaming kernel otherwise.
+  // A projection of the active rows: the tiled kernel over a pass of prompts
+  // (256 rows and more), the weight-streaming kernel otherwise.
   // S: its reduction splits.
   auto project = [&](const WSegs &segs, int N, int K, const char *X, int ldx, int rows_M, float *Y, int ldy,
                      long long y_stride, const GemmConfig &g, int &S) -> hipError_t {
@@ -877,8 +870,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
   int maxlen = 0;
   if (!c.prefill)
     for (int b = 0; b < c.rows.B; ++b) maxlen = std::max(maxlen, kv->len[b] + 1);  // (the boundary: one too many)
-  bool attn_single = false;
-  const bool finish_in_attn = !c.prefill && attn_finishes_qkv(m, c.rows.B, maxlen, &attn_single);
+  const bool finish_in_attn = !c.prefill && cf.dtype == DBT_BF16;
   const bool xin = l == 0 && c.hin && c.hin->h1;
   if (xin && (c.prefill || !finish_in_attn || cf.dtype != DBT_BF16 || !gemm_xnorm_ok(g_qkv, aM)))
     return fail(DBT_ERR_STATE, "internal: first-layer input fold on an unsupported call");
@@ -958,7 +950,7 @@ dbt_status run_layer(dbt_model *m, dbt_kv *kv, int l, const LayerCall &c, hipStr
     // When the batch fills the chip (B x n_kv >= 256 workgroups), each
     // (sequence, KV head) is read by one eight-wave workgroup and no partials
     // are merged.  The choice depends on the batch, never on the branch.
-    aa.single = attn_single;
+    aa.single = attn_single(m, c.rows.B, maxlen);
     aa.fin = qf;
     aa.O = O;
     aa.ldo = dq;
@@ -1272,7 +1264,7 @@ dbt_status decode_step_impl(dbt_model *m, dbt_kv *kv, const dbt_step_in *in, int
   const bool on = branch_on != 0;
   const int nb = n_branches(cf);
   const Rows rows{B, Bp, 0, on ? 1 + nb : 1};
-  const bool fold = input_fold(m, kv, B);
+  const bool fold = input_fold(m, B);
   const HIn hin{in->h1_in, in->h2_in, B};
   if (!fold && (s = load_inputs(m, kv, in, in->tokens, rows, st, &sb))) return s;
   LayerCall lc{};
@@ -1485,7 +1477,7 @@ dbt_status dbt_decode_step_ungrouped(dbt_model *m, dbt_kv *kv, const dbt_step_in
   if ((s = flush(kv, pos.data(), B, st, &sb))) return s;
   // pass 1: every primary layer, keeping Q1, H1, M1
   const Rows prim{B, Bp, 0, 1};
-  const bool fold = input_fold(m, kv, B);
+  const bool fold = input_fold(m, B);
   const HIn hin{in->h1_in, in->h2_in, B};
   if (!fold && (s = load_inputs(m, kv, in, in->tokens, prim, st, &sb))) return s;
   LayerCall lc{};

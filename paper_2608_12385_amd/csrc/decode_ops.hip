@@ -495,7 +495,7 @@ __global__ __launch_bounds__(256) void k_kv_fill(KVRef kv, int seq, int start, i
                                                  const E *vsrc) {
   constexpr int EP = VEC ? 16 / sizeof(E) : 1;  // elements per piece
   constexpr int PITCH = 128 + 8;                // rows of 8 positions half the banks apart
-  __shared__ E vt[16 * PITCH];
+  __shared__ __attribute__((aligned(16))) E vt[16 * PITCH];
   typedef E Piece __attribute__((ext_vector_type(EP)));
   const int t = threadIdx.x, g = blockIdx.y, DH = kv.d_h, pr = DH / EP;
   const int slot_page = start / 16 + blockIdx.x;

@@ -494,8 +494,8 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_bf16(WSegs segs, int K, const 
 // is bound by the latency of its chain of loads, not by bytes: the units of a
 // short reduction are then all in flight at once, where a 64-column tile
 // walking K through LDS waited for each 64-element step (256 x 683 for two
-// live rows: 77 us, this kernel 4.6 us; 768 x 256: 42 and 3.6 us).  The order of an element's sum
-// depends on K only, never on MB or on the stacked rows.
+// live rows: 77 us, this kernel 4.6 us; 768 x 256: 42 and 3.6 us).  The order
+// of an element's sum depends on K only, never on MB or on the stacked rows.
 // Rows need only 4-byte alignment (K may be odd), lane (r, gq) reads elements
 // 4 gq .. 4 gq + 3 of each 16-element piece of row r; the j-th of a piece's
 // four multiplies takes element j of every group, for both operands alike.
@@ -509,7 +509,7 @@ __global__ __launch_bounds__(64 * kWavesF32) void k_gemm_f32(WSegs segs, int N, 
                                                              int ldx, int M, float *__restrict__ Y, int ldy,
                                                              YRows yr) {
   constexpr int XR = 16 * MB, PITCH = 20;  // floats per staged output row (16-byte rows, four-bank steps)
-  __shared__ float red[kWavesF32][XR][PITCH];
+  __shared__ __attribute__((aligned(16))) float red[kWavesF32][XR][PITCH];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int r = lane & 15, gq = lane >> 4;
   const int n0 = blockIdx.x * 16, m0 = blockIdx.y * XR;
@@ -625,7 +625,7 @@ GemmConfig gemm_config(int n_full, int K, int dtype, int seg_gran, int max_rows)
     // 16 x 16, and a shorter finish).
     const int nc = K / kChunk;
     auto splits = [&](int tiles) {
-      int S = 256 / tiles;
+      int S = kComputeUnits / tiles;
       S = std::min(S, std::max(1, K / (2 * std::max(max_rows, 1))));
       return std::max(std::min({S, 16, std::max(nc, 1)}), 1);
     };
@@ -713,7 +713,7 @@ int gemm_stats_tiles(int N, const GemmConfig &g, int dtype) {
 // kernel after it; at 128 rows they lose (27-32 against 25 us).
 bool gemm_glu_ok(int f, int M, int np, int dtype) {
   if (dtype != 1) return false;
-  return (f % 64 == 0 && f / 64 >= 192 && (np == 1 || M <= 128)) || (f % 32 == 0 && f / 32 >= 128 && f / 32 <= 256 && M <= 64);
+  return (f % 64 == 0 && f / 64 >= 192 && (np == 1 || M <= 128)) || (f % 32 == 0 && f / 32 >= 128 && f / 32 <= kComputeUnits && M <= 64);
 }
 
 hipError_t launch_gemm_glu(const uint16_t *w_gate, const uint16_t *w_up, int f, int K, const void *X, int ldx, int M,
@@ -786,7 +786,7 @@ hipError_t launch_gemm(const WSegs &segs, int N, int K, int dtype, const void *X
     // every compute unit: a weight row is then read from HBM or L2 fewer times
     const int nt = (N + 15) / 16, mt = (M + 15) / 16;
     int MB = 1;
-    while (MB < 4 && (long long)nt * ((mt + 2 * MB - 1) / (2 * MB)) >= 256) MB *= 2;
+    while (MB < 4 && (long long)nt * ((mt + 2 * MB - 1) / (2 * MB)) >= kComputeUnits) MB *= 2;
     const dim3 grid(nt, (mt + MB - 1) / MB), block(64 * kWavesF32);
     const float *Xf = (const float *)X;
     switch (MB) {

@@ -24,6 +24,11 @@ struct Rows {
   int np;  // active paths (1 or 2)
 };
 
+// Compute units the launch rules fill.  A constant of the part (MI355X, not
+// partitioned) rather than a query: the workspace is sized from the same rules
+// by calls that need no GPU.
+constexpr int kComputeUnits = 256;
+
 enum Mode { MODE_GROUPED = 0, MODE_PRIMARY = 1, MODE_BRANCH = 2 };
 
 // Prompts of several sequences are packed into one pass: row r of the pass is
@@ -132,8 +137,9 @@ hipError_t launch_gemm(const WSegs &segs, int N, int K, int dtype, const void *X
 int gemm_stats_tiles(int N, const GemmConfig &g, int dtype);
 int gemm_tile_rows(const GemmConfig &g);  // weight rows (output columns) per workgroup
 
-// Projection of a whole prompt (M >= 256 rows, K a multiple of 128, N a
-// multiple of 16, bf16): 256-row tiles on the matrix cores.  Plain: Y (fp32,
+// Projection of a pass over prompts (M >= 256 rows, K a multiple of 128, N a
+// multiple of 16, bf16): tiles of 128 or 256 rows and columns on the matrix
+// cores.  Plain: Y (fp32,
 // [M][ldy]) = X W^T with W the stacked segments w[0..2] (rows[0..2] rows).
 // GLU: w[0] = gate, w[1] = up (N = f rows each); writes H (bf16, [M][ldh]) =
 // silu(X Wg^T) * (X Wu^T), and keeps rows of H in fp32 (ret).  QKV (rope !=
@@ -168,8 +174,8 @@ struct TileGemm {
 bool gemm_tile_ok(int N, int K, int M, int dtype);
 // Prompt rows from which launch_gemm_tile is used.
 constexpr int kTileRows = 256;
-// Reduction splits launch_gemm_tile should run a plain projection with; every
-// slab together has at most kTileSlabs elements more than one.
+// Reduction splits launch_gemm_tile should run a plain projection with; the
+// slabs of more than one have at most kTileSlabs elements together.
 int gemm_tile_splits(int N, int K, int M);
 constexpr int kTileSlabs = 256 * 256 * 256;
 // Everything launch_gemm_tile requires of g (the shape test above, segment

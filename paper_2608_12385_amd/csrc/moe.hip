@@ -125,7 +125,7 @@ __device__ __forceinline__ void route_select(const MoeRoute &a, const float *lg,
 template <int EB, bool LOGITS = false>
 __global__ __launch_bounds__(64 * route_waves(EB)) void k_moe_route(MoeRoute a) {
   constexpr int PITCH = 16 * EB + 4, kRouteWaves = route_waves(EB);
-  __shared__ float red[kRouteWaves][16][PITCH];
+  __shared__ __attribute__((aligned(16))) float red[kRouteWaves][16][PITCH];
   __shared__ float ssr[kRouteWaves][16];
   const bool prim = a.mode != MODE_BRANCH, br = a.mode != MODE_PRIMARY;
   const bool both = prim && br;

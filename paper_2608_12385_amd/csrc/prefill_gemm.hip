@@ -394,8 +394,8 @@ struct TileShape {
 // about 0.7 of a full one, since they share the caches with nobody.
 TileShape tile_shape(int M, int N) {
   auto cost = [&](int bm, int bn, double c) {
-    const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), full = tiles / 256, rest = tiles % 256;
-    return c * (full + (rest ? 0.7 + 0.3 * rest / 256 : 0.0));
+    const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), full = tiles / kComputeUnits, rest = tiles % kComputeUnits;
+    return c * (full + (rest ? 0.7 + 0.3 * rest / kComputeUnits : 0.0));
   };
   const double a = cost(256, 256, 1.41), b = cost(128, 256, 0.86), c = cost(128, 128, 0.6);
   if (a <= b && a <= c) return {256, 256};
@@ -410,7 +410,7 @@ TileShape tile_shape(int M, int N) {
 int gemm_tile_splits(int N, int K, int M) {
   const TileShape t = tile_shape(M, N);
   const int tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-  return std::max(1, std::min({256 / tiles, 4, K / 1024}));
+  return std::max(1, std::min({kComputeUnits / tiles, 4, K / 1024}));
 }
 
 bool gemm_tile_ok(int N, int K, int M, int dtype) {
