@@ -51,10 +51,15 @@ constexpr int kPage = 16;
 // ids the kernel holds; one with more pairs, which reads whole sequences when
 // the batch fills the chip, 86 pages for its smaller calls.  The target is
 // fixed when the model is created, so a row's result depends only on its own
-// query and cache.  Against four-wave workgroups of 16 to 128 pages, about
-// twice as many: 16 sequences of 300-1500 positions with 4 KV heads 14.9 + 5.7
-// (merge) -> 13.0 + 4.3 us; 16 or 48 pages instead of 24: equal, 15.8 us; two
-// rounds instead of one: up to 12 % slower steps.
+// query and cache.
+// Whole steps by target: 24 layers, 16 sequences of 300-1500 positions, 4 KV
+// heads: 16 pages 1607 us, 24 (the rule) 1421, 32 1441, 48 1479, 64 1522; a share
+// of one KV head, 13 sequences of 150-4096: 84 us at 16 and 24, 86 at 48, 95 at 128.
+// The rule cannot know how full a model is.  One 8B-shape layer, 8 sequences of
+// at most 8192 positions (target 128), 1 x 8000 positions: 119.7 us (64 pages
+// 111.8; four-wave workgroups of 64 pages, the form before, 116.4), 8 x 1025-2048:
+// 120.9 (131.6; 133.6), 8 x 8150: 148.7 (144.9; 146.1); every other partly filled
+// model that was timed gains over that form as well.
 // fp32 splits are 64 pages long.
 constexpr int kSplitTargetBf16 = 86, kSplitMinBf16 = 24, kSplitMaxBf16 = 1024, kSplitTargetF32 = 64;
 constexpr int kMixChunk = 4096;

@@ -117,6 +117,17 @@ def test_bf16_packed_prompts(lens):
     prompts_and_steps(shape, lens, BF16_TOL)
 
 
+# widths at both ends of the fused gate/up kernel's narrow tiles (128 to 256 of
+# them, up to 64 stacked rows) and of its wide ones, prompts of 1 to 65 rows,
+# steps of 32 and 64 stacked rows, and of 96 (the narrow tiles' limit passed)
+@pytest.mark.parametrize("f", [4096, 8192, 12288])
+@pytest.mark.parametrize("lens", [[1], [5, 40], [63], [32, 32], [65], [1 + i % 3 for i in range(17)], [1] * 33])
+def test_bf16_fused_gate_up_edges(f, lens):
+    shape = synth.ModelShape(n_layers=1, d_model=256, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=f, vocab=448,
+                             dtype="bf16", has_embeddings=True, std=0.05, coupling_std=0.5)
+    prompts_and_steps(shape, lens, BF16_TOL, steps=1)
+
+
 # more sequences than one pass takes (128), and more rows (8192)
 @pytest.mark.parametrize("lens", [[1 + i % 3 for i in range(131)], [900 + 31 * i for i in range(9)]])
 def test_f32_several_prompt_passes(lens):
