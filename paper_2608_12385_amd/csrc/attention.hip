@@ -87,7 +87,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   const uint16_t *kbase = (const uint16_t *)a.kv.k;
   const uint16_t *vbase = (const uint16_t *)a.kv.v;
 
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kNoScore, l_run = 0.f;
   floatx4 acc[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -198,18 +198,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     // (the wave merge below works for any common base).
     const bool grow = mt > m_run + kLazyMargin;
     const float m_new = grow ? mt : m_run;
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;  // no score above -inf yet
     float p[8];
     float ps = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      p[i] = __builtin_amdgcn_exp2f(sc[i] - m_use);
+      p[i] = __builtin_amdgcn_exp2f(sc[i] - m_new);
       ps += p[i];
     }
     // rescale the running sums only when some row's base moved (wave-uniform
     // test; a factor of exactly 1 for the other rows)
     if (__any(grow)) {
-      const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
+      const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
       l_run *= corr;
 #pragma unroll
       for (int c = 0; c < 8; ++c) acc[c] = acc[c] * corr;
@@ -441,19 +440,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   const size_t obase = (((size_t)b * n_kv + g) * a.max_splits + split) * 16;
   for (int e = threadIdx.x; e < nrows * DH; e += NW * 64) {
     const int qr = e / DH, dh = e % DH;
-    float mx = -INFINITY;
+    // (a wave without pages has sums of zero; one whose scores were all NaN has
+    // no maximum either, but its sums are NaN and count)
+    float mx = kNoScore;
 #pragma unroll
     for (int w = 0; w < NW; ++w) mx = fmaxf(mx, sm[w][qr]);
     float o = 0.f, l = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      // (a wave whose scores were all NaN has no maximum, but its sums are NaN
-      // and count; one without pages has sums of zero)
-      if (sm[w][qr] != -INFINITY || sl[w][qr] != 0.f) {
-        const float f = exp2f(sm[w][qr] - mx);
-        o += so[w][dh][qr] * f;
-        l += sl[w][qr] * f;
-      }
+      const float f = exp2f(sm[w][qr] - mx);
+      o += so[w][dh][qr] * f;
+      l += sl[w][qr] * f;
     }
     if (SINGLE || npages <= a.pages_per_split) {  // no other split: nothing to merge
       const int path = a.rows.p0 + qr / G, head = g * G + qr % G;
@@ -489,7 +486,7 @@ __global__ __launch_bounds__(64 * kWavesF32Attn) void k_attn_decode_f32(AttnArgs
   const int r = threadIdx.x & 15;
   __shared__ F32Merge<NC> mg;
   const float *qp = a.Q + row_of(r < nrows ? r : 0, 0);
-  attn_f32<NC, false>(mg, qp, r < nrows, len, len, len, (const float *)a.kv.k, (const float *)a.kv.v,
+  attn_f32<NC, false>(mg, qp, r < nrows, len, len, (const float *)a.kv.k, (const float *)a.kv.v,
                a.kv.page_table + (size_t)b * a.kv.mpps, pb, pe, n_kv, g, DH);
   const size_t obase = (((size_t)b * n_kv + g) * a.max_splits + split) * 16;
   for (int e = threadIdx.x; e < nrows * DH; e += 64 * kWavesF32Attn) {

@@ -27,29 +27,28 @@ struct F32Merge {
   float o[kWavesF32Attn][16 * NC][17];
   float m[kWavesF32Attn][16], l[kWavesF32Attn][16];
   // the sums of query row qr over all waves, relative to their maximum mx
-  // (a wave whose scores were all NaN has no maximum either, but its sums are
-  // NaN and count; one without keys has sums of zero)
+  // (a wave without keys has sums of zero; one whose scores were all NaN has no
+  // maximum either, but its sums are NaN and count)
   __device__ __forceinline__ void merged(int qr, int dh, float &os, float &ls, float &mx) const {
-    mx = -INFINITY;
+    mx = kNoScore;
 #pragma unroll
     for (int w = 0; w < kWavesF32Attn; ++w) mx = fmaxf(mx, m[w][qr]);
     os = ls = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWavesF32Attn; ++w)
-      if (m[w][qr] != -INFINITY || l[w][qr] != 0.f) {
-        const float f = exp2f(m[w][qr] - mx);
-        os += o[w][dh][qr] * f;
-        ls += l[w][qr] * f;
-      }
+    for (int w = 0; w < kWavesF32Attn; ++w) {
+      const float f = exp2f(m[w][qr] - mx);
+      os += o[w][dh][qr] * f;
+      ls += l[w][qr] * f;
+    }
   }
 };
 
 // qp: this lane's query row (row r = lane & 15; live = false: a stand-in whose
 // results are not used); it sees keys 0 .. seen - 1.  Pages [pb, pe) of ptab;
 // positions >= valid hold no key (stale slots).  CAUSAL: rows see different
-// numbers of keys, the fewest `first`.  Ends with a barrier.
+// numbers of keys, but all of those before the last page.  Ends with a barrier.
 template <int NC, bool CAUSAL>
-__device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool live, int seen, int first, int valid,
+__device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool live, int seen, int valid,
                                          const float *kbase, const float *vbase, const int *ptab, int pb, int pe,
                                          int n_kv, int g, int DH) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -67,7 +66,7 @@ __device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool
     q[c] = *(const floatx4 *)(qp + (d0 < DH ? d0 : 0));
     if (d0 >= DH || !live) q[c] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kNoScore, l_run = 0.f;
   floatx4 acc[NC], k[NC], v[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -82,6 +81,8 @@ __device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool
   int j = pb + wave;
   int next = j + kWavesF32Attn < pe ? ptab[j + kWavesF32Attn] : 0;  // page ids run one turn further ahead
   if (j < pe) load(ptab[j]);
+  float p[4] = {0.f, 0.f, 0.f, 0.f};
+  bool apart = false;  // the last page holds values that are not finite (CAUSAL)
   for (; j < pe; j += kWavesF32Attn) {
     floatx4 s = {0.f, 0.f, 0.f, 0.f};
     if (16 * NC > DH && 16 * (NC - 1) + 4 * gq >= DH) k[NC - 1] = floatx4{0.f, 0.f, 0.f, 0.f};  // (infinity * 0)
@@ -103,13 +104,11 @@ __device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool
       mt = fmaxf(mt, s[i]);
     }
     const float m_new = fmaxf(m_run, rows4_max(mt));
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;  // no key of this row yet
-    const float corr = m_run == -INFINITY ? 0.f : exp2f(m_run - m_use);
-    float p[4];
+    const float corr = exp2f(m_run - m_new);
     l_run *= corr;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      p[i] = exp2f(s[i] - m_use);
+      p[i] = exp2f(s[i] - m_new);
       l_run += p[i];
     }
     m_run = m_new;
@@ -120,34 +119,42 @@ __device__ __forceinline__ void attn_f32(F32Merge<NC> &mg, const float *qp, bool
         for (int i = 0; i < 4; ++i)
           if (p0 + i >= valid) vc[c][i] = 0.f;
     }
-    bool apart = false;  // a value that some row of the tile must not see is not finite
-    if (CAUSAL && 16 * j + 16 > first) {
+    if (CAUSAL && j == pe - 1) {
+      // the page of the tile's own positions: a probability of zero would not
+      // hide a value that is not finite from the rows before it, so such
+      // values are taken out here and added below
       bool odd = false;
 #pragma unroll
       for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) odd |= !(fabsf(vc[c][i]) < INFINITY);
+        for (int i = 0; i < 4; ++i)
+          if (!(fabsf(vc[c][i]) < INFINITY)) {
+            vc[c][i] = 0.f;
+            odd = true;
+          }
       apart = __any(odd);
     }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) acc[c] = acc[c] * corr;
-    if (!apart) {
+    for (int c = 0; c < NC; ++c) {
+      acc[c] = acc[c] * corr;
 #pragma unroll
-      for (int c = 0; c < NC; ++c)
+      for (int i = 0; i < 4; ++i) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[c][i], p[i], acc[c], 0, 0, 0);
+    }
+  }
+  if (CAUSAL && apart) {  // row by row, the keys it sees
+    const int p0 = 16 * (pe - 1) + 4 * gq;
+    const float *vp = vbase + ((size_t)ptab[pe - 1] * n_kv + g) * 16 * DH;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[c][i], p[i], acc[c], 0, 0, 0);
-    } else {  // row by row: its keys only, for a probability of zero does not hide such a value
+    for (int c = 0; c < NC; ++c) {
+      const floatx4 w = *(const floatx4 *)(vp + voff[c]);
 #pragma unroll 1
       for (int row = 0; row < 16; ++row) {
-        const int see = __shfl(seen, row, 64);
+        const int see = min(__shfl(seen, row, 64), valid);
+        floatx4 o = acc[c];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          floatx4 o = acc[c];
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            o = __builtin_amdgcn_mfma_f32_16x16x4f32(p0 + i < see ? vc[c][i] : 0.f, p[i], o, 0, 0, 0);
-          if (r == row) acc[c] = o;
-        }
+        for (int i = 0; i < 4; ++i)
+          o = __builtin_amdgcn_mfma_f32_16x16x4f32(p0 + i < see && !(fabsf(w[i]) < INFINITY) ? w[i] : 0.f, p[i], o, 0, 0, 0);
+        if (r == row) acc[c] = o;
       }
     }
   }

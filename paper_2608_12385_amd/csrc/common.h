@@ -50,6 +50,11 @@ __device__ __forceinline__ float rows4_max(float x) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// Maximum of no scores yet: below every finite score and above -infinity, so
+// that a masked or infinitely low one weighs exp2(-inf - m) = 0 beside it, while
+// sums over NaN scores are NaN whatever the maximum.
+constexpr float kNoScore = -3.402823466e38f;
+
 // Maximum over the wave without LDS: rotations within each row of 16 lanes,
 // then rows4_max.
 __device__ __forceinline__ float wave_max_dpp(float x) {

@@ -412,7 +412,7 @@ __global__ __launch_bounds__(64 * kWavesF32Attn) void k_attn_prefill_f32(PromptA
   float *O = (float *)a.O + (size_t)tile.row0 * a.ldo;
   const int qpos = q0 + (threadIdx.x & 15);
   __shared__ F32Merge<NC> mg;
-  attn_f32<NC, true>(mg, Q + (size_t)min(qpos, T - 1) * a.ldq + head * DH, qpos < T, qpos + 1, q0 + 1, T, (const float *)kv.k,
+  attn_f32<NC, true>(mg, Q + (size_t)min(qpos, T - 1) * a.ldq + head * DH, qpos < T, qpos + 1, T, (const float *)kv.k,
                (const float *)kv.v, kv.page_table + (size_t)seq * kv.mpps, 0, (min(q0 + 15, T - 1) >> 4) + 1, kv.n_kv,
                g, DH);
   for (int e = threadIdx.x; e < 16 * DH; e += 64 * kWavesF32Attn) {
