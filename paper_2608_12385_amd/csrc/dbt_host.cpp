@@ -1070,7 +1070,7 @@ struct Span {
 };
 
 bool overlap(const Span &a, const Span &b) {
-  return a.p && b.p && (uintptr_t)a.p < (uintptr_t)b.p + b.bytes && (uintptr_t)b.p < (uintptr_t)a.p + a.bytes;
+  return (uintptr_t)a.p < (uintptr_t)b.p + b.bytes && (uintptr_t)b.p < (uintptr_t)a.p + a.bytes;
 }
 
 // direct1 / direct2: whether the primary's / the branches' outputs may leave
@@ -1086,16 +1086,32 @@ Sinks make_sinks(const dbt_model *m, int B, int Bp, const dbt_step_out *out, boo
   if (!out) return k;
   const size_t rows = (size_t)cf.n_layers * B * 4, k1 = rows * cf.top_k1, k2 = rows * (cf.replay ? cf.top_k1 : cf.top_k2),
                re = rows * cf.n_experts;
-  const Span all[] = {{out->logits1, zrow}, {out->logits2, zrow * nb}, {out->h1_out, hrow}, {out->h2_out, hrow * nb},
-                      {out->alpha, (size_t)B * 4}, {out->next_token, (size_t)B * 4}, {out->route_idx1, k1},
-                      {out->route_idx2, k2}, {out->route_w1, k1}, {out->route_w2, k2}, {out->route_logits1, re},
-                      {out->route_logits2, re}, late};
+  Span all[13];
+  int n = 0;
+  auto add = [&](const void *p, size_t bytes) {
+    if (p) all[n++] = Span{p, bytes};
+  };
+  add(out->logits1, zrow);
+  add(out->logits2, zrow * nb);
+  add(out->h1_out, hrow);
+  add(out->h2_out, hrow * nb);
+  add(out->alpha, (size_t)B * 4);
+  add(out->next_token, (size_t)B * 4);
+  if (cf.n_experts > 0) {
+    add(out->route_idx1, k1);
+    add(out->route_idx2, k2);
+    add(out->route_w1, k1);
+    add(out->route_w2, k2);
+    add(out->route_logits1, re);
+    add(out->route_logits2, re);
+  }
+  add(late.p, late.bytes);
   auto fits = [&](const void *p) {  // one of the first four
     if (!p || (uintptr_t)p % 16) return false;
-    for (const Span &a : all)
-      if (a.p == p)
-        for (const Span &b : all)
-          if (&a != &b && overlap(a, b)) return false;
+    for (int i = 0; i < n; ++i)
+      if (all[i].p == p)
+        for (int j = 0; j < n; ++j)
+          if (i != j && overlap(all[i], all[j])) return false;
     return true;
   };
   k.copy_z1 = V > 0 && out->logits1;
