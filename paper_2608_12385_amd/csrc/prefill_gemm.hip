@@ -22,7 +22,8 @@
 // outstanding, which is when the next phase's operands are complete.
 // Measured on 8192 rows of width 2048, against one barrier and one full wait
 // per step with the two waves of a SIMD in lockstep: gate/up with 5632 units
-// 325 -> 300 us (1.26 PFLOP/s; a library product of the same size 0.97), W_O
+// 325 -> 300 us (1.26 PFLOP/s; a library product of the same size 0.97; 319
+// since its SwiGLU takes expf and a divide), W_O
 // and down 64 + 165 -> 58 + 134 us.  Without its loads gate/up takes 227 us,
 // without the half-phase offset 344 us.
 //
