@@ -351,6 +351,10 @@ struct dbt_kv {
   struct Upd { int b, slot, page; };
   std::vector<Upd> pending;
 
+  // whether the next position of sequence b is on a page it does not hold (a
+  // failed step leaves the pages it took for the next one)
+  bool needs_page(int b) const { return (size_t)len[b] == table[b].size() * kPage; }
+
   int take_page() {
     const int p = free_pages.top();
     free_pages.pop();
@@ -421,8 +425,9 @@ dbt_status flush(dbt_kv *kv, const int *h_pos, int npos, hipStream_t st, StepBeg
     fold->n_pos = fold->n_pt = 0;
     fold->b0 = 0;
   }
-  // The list itself is left as it is until everything is enqueued: after a
-  // failure the next call sends it again.
+  // The list itself is left as it is until everything is enqueued (with `fold`:
+  // until the step is, see step_done): after a failure the next call sends it
+  // again.
   const std::vector<dbt_kv::Upd> &up = kv->pending;
   auto run_end = [&](size_t i) {  // end of the run of consecutive pages from entry i
     size_t e = i + 1;
@@ -471,7 +476,7 @@ dbt_status flush(dbt_kv *kv, const int *h_pos, int npos, hipStream_t st, StepBeg
     }
     if (fold && singles == 0 && ipos >= npos) {
       *fold = sb;
-      break;
+      return DBT_OK;
     }
     HIPCHK(launch_step_begin(sb, m->at<int>(m->L.pos), kv->page_table, kv->mpps, st));
   }
@@ -1214,7 +1219,7 @@ dbt_status check_step_in(dbt_model *m, dbt_kv *kv, const dbt_step_in *in, int ne
   int need = 0;
   for (int b = 0; b < in->batch; ++b) {
     if (kv->len[b] + 1 > cf.max_pos) return fail(DBT_ERR_SHAPE, "sequence %d would exceed max_pos", b);
-    if (kv->len[b] % kPage == 0) {
+    if (kv->needs_page(b)) {
       if (kv->len[b] / kPage >= kv->mpps) return fail(DBT_ERR_NO_PAGES, "sequence %d page table full", b);
       ++need;
     }
@@ -1229,13 +1234,20 @@ std::vector<int> begin_step(dbt_kv *kv, int B) {
   std::vector<int> pos(B);
   for (int b = 0; b < B; ++b) {
     pos[b] = kv->len[b];
-    if (kv->len[b] % kPage == 0) {
+    if (kv->needs_page(b)) {
       const int p = kv->take_page();
       kv->table[b].push_back(p);
       kv->pending.push_back({b, (int)kv->table[b].size() - 1, p});
     }
   }
   return pos;
+}
+
+// Everything of a step is enqueued: the sequences grow.
+dbt_status step_done(dbt_kv *kv, int B) {
+  kv->pending.clear();
+  for (int b = 0; b < B; ++b) kv->len[b] += 1;
+  return DBT_OK;
 }
 
 dbt_status copy_rows(float *dst, const float *src, int B, int d, hipStream_t st) {
@@ -1306,13 +1318,12 @@ dbt_status decode_step_impl(dbt_model *m, dbt_kv *kv, const dbt_step_in *in, int
   for (int l = 0; l < cf.n_layers; ++l)
     if ((s = run_layer(m, kv, l, lc, st))) return s;
   if (cf.vocab > 0 && (s = lm_head(m, rows, k, st))) return s;
-  for (int b = 0; b < B; ++b) kv->len[b] += 1;
   if (out) {
     if ((s = readout(m, B, Bp, on, out, k, st))) return s;
     if (k.copy_h1 && (s = copy_rows(out->h1_out, m->at<float>(m->L.S), B, cf.d_model, st))) return s;
     if (on && k.copy_h2 && (s = copy_branch_rows(m, out->h2_out, B, Bp, st))) return s;
   }
-  return DBT_OK;
+  return step_done(kv, B);
 }
 
 }  // namespace
@@ -1522,13 +1533,12 @@ dbt_status dbt_decode_step_ungrouped(dbt_model *m, dbt_kv *kv, const dbt_step_in
   const Rows br{B, Bp, 1, n_branches(cf)};
   if (!fold && (s = load_inputs(m, kv, in, in->tokens, br, st))) return s;
   if ((s = branch_pass(m, kv, B, Bp, k, st, out, fold ? &hin : nullptr))) return s;
-  for (int b = 0; b < B; ++b) kv->len[b] += 1;
   if (out) {
     if ((s = readout(m, B, Bp, true, out, k, st))) return s;
     if (k.copy_h1 && (s = copy_rows(out->h1_out, m->at<float>(m->L.S), B, cf.d_model, st))) return s;
     if (k.copy_h2 && (s = copy_branch_rows(m, out->h2_out, B, Bp, st))) return s;
   }
-  return DBT_OK;
+  return step_done(kv, B);
 }
 
 // The boundary after a prefill whose primary logits are at k, or, as part of

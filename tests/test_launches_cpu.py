@@ -55,6 +55,11 @@ def test_tiled_projection_cases_reach_every_form(fake):
     run_child(fake, "tiles")
 
 
+@pytest.mark.parametrize("form", ["tokens", "states"])
+def test_steps_after_failed_launches(fake, form):
+    run_child(fake, "steps_" + form)
+
+
 # ---------------------------------------------------------------------------
 # in the child
 # ---------------------------------------------------------------------------
@@ -69,9 +74,9 @@ class Program:
         size = dict(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=256, vocab=512)
         if dtype == "f32":
             size = dict(d_model=48, n_q_heads=4, n_kv_heads=2, head_dim=16, d_ff=96, vocab=64)
-        cfg = B.dbt_config(dtype=B.DBT_BF16 if dtype == "bf16" else B.DBT_F32, has_embeddings=1, max_batch=max_batch,
-                           rms_eps=1e-5, rope_theta=1e4,
-                           **dict(dict(size, n_layers=2, max_pos=256, max_prompt=64), **kw))
+        cfg = B.dbt_config(dtype=B.DBT_BF16 if dtype == "bf16" else B.DBT_F32, max_batch=max_batch, rms_eps=1e-5,
+                           rope_theta=1e4,
+                           **dict(dict(size, n_layers=2, has_embeddings=1, max_pos=256, max_prompt=64), **kw))
         self.layers = (B.dbt_layer_weights * cfg.n_layers)()
         for l in range(cfg.n_layers):
             for f, _ in B.dbt_layer_weights._fields_:
@@ -159,6 +164,40 @@ def pages(fk):
             assert at > 4, at  # several launches of each kind were tried
             return
     raise AssertionError("the flush never went through")
+
+
+def steps(fk, form):
+    """A step that fails at any launch leaves its sequences as they were, its
+    new pages' table entries are still sent, and the step that follows it takes
+    those pages and no more."""
+    p = Program("bf16", n_layers=1, **(dict() if form == "tokens" else dict(has_embeddings=0, max_prompt=0)))
+    B, lens = p.B, [16, 5, 32, 48]
+    sin = B.dbt_step_in(batch=4, **(dict(tokens=FAKE) if form == "tokens" else dict(h1_in=FAKE, h2_in=FAKE)))
+    calls = [lambda kv: p.status(B.dbt_decode_step, p.model, kv, sin, 1, p.out, 0),
+             lambda kv: p.status(B.dbt_decode_step_ungrouped, p.model, kv, sin, p.out, 0)]
+    for call in calls:
+        at, n = 0, 1
+        while at < n:
+            kv, table = p.cache(16)
+            for b, length in enumerate(lens):
+                B.dbt_kv_reserve(kv, b, length)
+            assert p.status(B.dbt_kv_fill, kv, 0, 0, 0, 1, FAKE, FAKE, 0) == 0  # the entries so far are written
+            fk.fake_reset(at)
+            assert call(kv) == 6, at
+            assert [B.dbt_kv_length(kv, b) for b in range(4)] == lens, at
+            fk.fake_reset(-1)
+            assert p.status(B.dbt_kv_fill, kv, 0, 0, 0, 1, FAKE, FAKE, 0) == 0
+            for b in range(4):
+                want = B.dbt_kv_pages(kv, b)
+                assert list(table[b * p.mpps:b * p.mpps + len(want)]) == want, (at, b)
+            fk.fake_reset(-1)
+            assert call(kv) == 0
+            n = fk.fake_launches()
+            assert [B.dbt_kv_length(kv, b) for b in range(4)] == [x + 1 for x in lens]
+            assert [len(B.dbt_kv_pages(kv, b)) for b in range(4)] == [x // 16 + 1 for x in lens], at
+            B.dbt_kv_destroy(kv)
+            at += 1
+        assert at > 6
 
 
 def attention(fk):
@@ -264,6 +303,6 @@ if __name__ == "__main__":
     fk.fake_kernel.restype = ctypes.c_char_p
     fk.fake_groups.restype = ctypes.c_uint
     what, _, arg = sys.argv[1].partition("_")
-    dict(boundary=boundary, pages=pages, attention=attention, router=router, tiles=tiles,
+    dict(boundary=boundary, pages=pages, steps=steps, attention=attention, router=router, tiles=tiles,
          workspace=workspace)[what](*([fk, arg] if arg else [fk]))
     print("done")
